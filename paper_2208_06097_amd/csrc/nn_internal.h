@@ -24,10 +24,9 @@ size_t nn_param_count();
 // Offsets (floats) into one activation/gradient workspace for batch B.
 struct NnActLayout {
     size_t out[kNnNumLayers];
-    size_t pool[3], up[3];
+    size_t pool[3];
     size_t g0, g1, g2, gskip[3];
-    size_t wpart, bpart, grad, mse_part;
-    int nchunk;
+    size_t wpart, wpack, grad, mse_part;   // wpart: the weight gradient's partial records
     size_t total_floats;
 };
 NnActLayout nn_act_layout(int B, int D);

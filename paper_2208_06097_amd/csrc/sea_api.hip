@@ -1441,7 +1441,7 @@ extern "C" sea_status sea_eps_workspace_bytes(sea_ctx* ctx, const sea_grid* grid
     const int nmax = std::max(grid->n[0], std::max(grid->n[1], grid->n[2]));
     const size_t np = (size_t)n_occ * (n_occ + 1) / 2;
     *bytes = align_up((size_t)n_occ * 3 * nmax * sizeof(double)) + align_up(np * sizeof(sea_pair)) +
-             align_up(np * sizeof(double));
+             align_up(np * sizeof(double)) + align_up(eps_marginals_part_doubles(grid->n, n_occ) * sizeof(double));
     return SEA_OK;
 }
 
@@ -1469,10 +1469,11 @@ extern "C" sea_status sea_build_pairs_eps(sea_ctx* ctx, const sea_grid* grid, in
     double* m_dev = (double*)base;
     sea_pair* cand_dev = (sea_pair*)(base + align_up((size_t)n_occ * 3 * nmax * sizeof(double)));
     double* S_dev = (double*)((char*)cand_dev + align_up(np_max * sizeof(sea_pair)));
+    double* part_dev = (double*)((char*)S_dev + align_up(np_max * sizeof(double)));
     hipStream_t s = (hipStream_t)ctx->opts.hip_stream;
     const int f32 = phi_dtype == SEA_F32;
     // 1. per-orbital, per-axis marginals of |phi|^2; boxes on the host
-    SEA_HIP_CHECK(ctx, launch_eps_marginals(phi_dev, f32, N, n_occ, nmax, m_dev, s));
+    SEA_HIP_CHECK(ctx, launch_eps_marginals(phi_dev, f32, N, n_occ, nmax, m_dev, part_dev, s));
     std::vector<double> m((size_t)n_occ * 3 * nmax);
     SEA_HIP_CHECK(ctx, hipMemcpyAsync(m.data(), m_dev, m.size() * sizeof(double), hipMemcpyDeviceToHost, s));
     SEA_HIP_CHECK(ctx, hipStreamSynchronize(s));

@@ -320,7 +320,9 @@ __device__ __forceinline__ void lds_sync() { asm volatile("s_waitcnt lgkmcnt(0)\
 // z-marching CG (k_cg.hip): needs every pair with n[0], n[1] <= 64.
 bool cg_zm_fits(const sea_pair* pairs, int n_pairs, const double* h);
 size_t cg_zm_lds_bytes(int state_f32);
-hipError_t launch_eps_marginals(const void* phi, int f32, const int* N, int n_occ, int nmax, double* m,
+// part: eps_marginals_part_doubles(N, n_occ) of scratch
+size_t eps_marginals_part_doubles(const int* N, int n_occ);
+hipError_t launch_eps_marginals(const void* phi, int f32, const int* N, int n_occ, int nmax, double* m, double* part,
                                 hipStream_t s);
 hipError_t launch_eps_overlap(const void* phi, int f32, const int* N, double dV, const sea_pair* pairs, int n_pairs,
                               double* S, hipStream_t s);

@@ -743,26 +743,15 @@ __device__ __forceinline__ void rtmarch(int nz, double* lds, const SW<double>& w
     }
 }
 
+// One row tile of one pair: b - A x of its rows into bres (WRITE) or the
+// tile's sums of |b|^2 and |b - A x|^2 into rnorm.
 template <bool WRITE>
-__global__ __launch_bounds__(RZ_NT) void k_residual_zm(ExxArgs a) {
-    extern __shared__ unsigned char smem[];
-    double* lds = reinterpret_cast<double*>(smem);
-    __shared__ double red[RZ_NT / 64 + 1];
-    int pid, tile;
-    rz_block(pid, tile);
-    if (pid >= a.n_pairs) return;
+__device__ __forceinline__ void residual_tile(const ExxArgs& a, int pid, int tile, double* lds, double* red) {
     const sea_pair P = a.pairs[pid];
     const int nx = P.n[0], ny = P.n[1], nz = P.n[2];
     const int y0 = tile * RZ_ROWS;
-    // after the row-tile CG: a pair its start stopped keeps the start's norms
-    if (!WRITE && a.cg_done && a.cg_done[pid] == 2) return;
-    if (WRITE) {
-        double b2, q2;
-        if (y0 >= ny || start_meets_target(a, pid, Delta<float>::target * Delta<float>::target * a.rel_tol * a.rel_tol,
-                                           b2, q2))
-            return;
-    } else if (y0 >= ny) {
-        if (threadIdx.x == 0) {
+    if (y0 >= ny) {
+        if (!WRITE && threadIdx.x == 0) {
             a.rnorm[((size_t)pid * RZ_TILES + tile) * 2] = 0.0;
             a.rnorm[((size_t)pid * RZ_TILES + tile) * 2 + 1] = 0.0;
         }
@@ -801,6 +790,51 @@ __global__ __launch_bounds__(RZ_NT) void k_residual_zm(ExxArgs a) {
     }
 }
 
+template <bool WRITE>
+__global__ __launch_bounds__(RZ_NT) void k_residual_zm(ExxArgs a) {
+    extern __shared__ unsigned char smem[];
+    __shared__ double red[RZ_NT / 64 + 1];
+    int pid, tile;
+    rz_block(pid, tile);
+    if (pid >= a.n_pairs) return;
+    if (WRITE) {
+        double b2, q2;
+        if (start_meets_target(a, pid, Delta<float>::target * Delta<float>::target * a.rel_tol * a.rel_tol, b2, q2)) return;
+    }
+    residual_tile<WRITE>(a, pid, tile, reinterpret_cast<double*>(smem), red);
+}
+
+// The same for the pairs of a refinement list (their row tiles dealt to a
+// grid that fits the chip, so that an empty list costs a few microseconds).
+template <bool WRITE>
+__global__ __launch_bounds__(RZ_NT) void k_residual_list(ExxArgs a, const int* list, const int* count) {
+    extern __shared__ unsigned char smem[];
+    __shared__ double red[RZ_NT / 64 + 1];
+    const int items = count[0] * RZ_TILES;
+    for (int q = blockIdx.x; q < items; q += gridDim.x) {
+        residual_tile<WRITE>(a, list[q / RZ_TILES], q % RZ_TILES, reinterpret_cast<double*>(smem), red);
+        __syncthreads();   // the planes in LDS are reused
+    }
+}
+
+// Whether each pair's start (it = 0), or its `it`-th correction, meets the
+// target, from the norms of the true residual; the pairs that do not go on
+// the next list while corrections are left.
+constexpr double REFINE_TARGET = 0.9;   // x rel_tol
+__global__ __launch_bounds__(64) void k_refine_flags(ExxArgs a, int* lists, int* counts, int it, int last) {
+    const int k = blockIdx.x * 64 + threadIdx.x;
+    if (k >= (it ? counts[it - 1] : a.n_pairs)) return;
+    const int pid = it ? lists[(size_t)(it - 1) * a.n_pairs + k] : k;
+    double b2, q2;
+    const bool meets = start_meets_target(a, pid, REFINE_TARGET * REFINE_TARGET * a.rel_tol * a.rel_tol, b2, q2);
+    const bool nan = !(b2 == b2) || !(q2 == q2);
+    a.stats[pid].iters = it;
+    a.stats[pid].converged = nan ? -1 : (meets ? 1 : 0);
+    a.stats[pid].rel_res = b2 > 0.0 ? sqrt(q2 / b2) : 0.0;
+    hist_put(a, pid, it, q2, b2);
+    if (!meets && !nan && !last) lists[(size_t)it * a.n_pairs + atomicAdd(counts + it, 1)] = pid;
+}
+
 // ---------------------------------------------------------------------------
 // FP64-state CG by row tiles (the plain FP64 form of Eq. 9).  Its 13-plane
 // FP64 register queue does not fit a whole pair in one workgroup, so the
@@ -818,16 +852,9 @@ __global__ __launch_bounds__(RZ_NT) void k_residual_zm(ExxArgs a) {
 // sweep never overwrites a partial another tile of its pair still reads.
 // The stop test runs on the recursive residual at 0.9 x rel_tol; the true
 // FP64 residual b - A x is formed afterwards for the reported rel_res.
-// Preconditioned (a.cg_pre, the spectral form's continuation): z = M^-1 r
-// with M = A_odd, the stencil with odd continuation past the faces, applied
-// exactly by the sine-transform passes between the sweeps; rho = <r, z>
-// takes the place of |r|^2 in alpha and beta, p = z + beta p.  M differs
-// from A only next to the faces, so few iterations remain.
 constexpr double CG64_TARGET = 0.9;
-// partial slots per row tile: |r|^2 by parity (0, 1), <p, A p> (2), |b|^2
-// (3), <r, z> by parity (4, 5; the preconditioned form's rho)
-constexpr int CG64_SLOTS = 8;
-__device__ __forceinline__ int cg64_rho_slot(const ExxArgs& a, int k) { return (a.cg_pre ? 4 : 0) + (k & 1); }
+// partial slots per row tile: |r|^2 by parity (0, 1), <p, A p> (2), |b|^2 (3)
+constexpr int CG64_SLOTS = 4;
 
 __device__ __forceinline__ double cg64_sum(const ExxArgs& a, int pid, int slot) {
     double s = 0.0;
@@ -846,23 +873,7 @@ __global__ __launch_bounds__(RZ_NT) void k_cg64_init(ExxArgs a) {
     const int nx = P.n[0], ny = P.n[1], nz = P.n[2];
     const int y0 = tile * RZ_ROWS;
     double* part = a.cg_part + ((size_t)pid * RZ_TILES + tile) * CG64_SLOTS;
-    if (a.rnorm) {   // a start whose true residual (its norms) already meets the target stops here
-        double b2, q2;
-        if (start_meets_target(a, pid, CG64_TARGET * CG64_TARGET * a.rel_tol * a.rel_tol, b2, q2)) {
-            if (tile == 0 && threadIdx.x == 0) {
-                a.cg_done[pid] = 2;   // stopped by its start: the final norms pass skips it
-                a.stats[pid].iters = 0;
-                a.stats[pid].converged = 1;
-                a.stats[pid].rel_res = b2 > 0.0 ? sqrt(q2 / b2) : 0.0;
-                hist_put(a, pid, 0, q2, b2);
-            }
-            return;
-        }
-    }
-    if (tile == 0 && threadIdx.x == 0) {
-        a.cg_done[pid] = 0;
-        atomicAdd(a.cg_active + a.max_iter + 1, 1);   // pairs that iterate
-    }
+    if (tile == 0 && threadIdx.x == 0) a.cg_done[pid] = 0;
     if (y0 >= ny) {
         if (threadIdx.x == 0)
             for (int q = 0; q < CG64_SLOTS; ++q) part[q] = 0.0;
@@ -915,18 +926,17 @@ __global__ __launch_bounds__(RZ_NT) void k_cg64_sweep(ExxArgs a) {
     rz_block(pid, tile);
     if (pid >= a.n_pairs || a.cg_done[pid]) return;
     const int k = a.cg_it;
-    const double rho = cg64_sum(a, pid, cg64_rho_slot(a, k));
+    const double rho = cg64_sum(a, pid, k & 1);
     if (SWEEP == 0) {
-        const double rr = a.cg_pre ? cg64_sum(a, pid, k & 1) : rho;
         const double bb = cg64_sum(a, pid, 3);
         const double tol2 = CG64_TARGET * CG64_TARGET * a.rel_tol * a.rel_tol;
-        const bool nan = !(rr == rr) || !(bb == bb) || !(rho == rho);
-        if (tile == 0 && threadIdx.x == 0) hist_put(a, pid, k, rr, bb);
-        if (nan || rr <= tol2 * bb || k >= a.max_iter) {
+        const bool nan = !(rho == rho) || !(bb == bb);
+        if (tile == 0 && threadIdx.x == 0) hist_put(a, pid, k, rho, bb);
+        if (nan || rho <= tol2 * bb || k >= a.max_iter) {
             if (tile == 0 && threadIdx.x == 0) {
                 a.stats[pid].iters = k;
-                a.stats[pid].converged = nan ? -1 : (rr <= tol2 * bb ? 1 : 0);
-                a.stats[pid].rel_res = bb > 0.0 ? sqrt(rr / bb) : 0.0;
+                a.stats[pid].converged = nan ? -1 : (rho <= tol2 * bb ? 1 : 0);
+                a.stats[pid].rel_res = bb > 0.0 ? sqrt(rho / bb) : 0.0;
                 a.cg_done[pid] = 1;
             }
             return;
@@ -964,17 +974,15 @@ __global__ __launch_bounds__(RZ_NT) void k_cg64_sweep(ExxArgs a) {
     auto oidx = [&](int z) { return (z * ny + yown) * nx + tx; };
     double acc = 0.0;
     if constexpr (SWEEP == 0) {
-        // p = r + beta p (z + beta p when preconditioned) over the window (the
-        // halo rows recomputed here, the owned rows written), <p, A p> over
-        // the owned rows
+        // p = r + beta p over the window (the halo rows recomputed here, the
+        // owned rows written), <p, A p> over the owned rows
         const double beta = k > 0 ? rho / a.cg_rho[(size_t)pid * 2 + ((k - 1) & 1)] : 0.0;
-        const double* __restrict__ src = (a.cg_pre ? a.cg_z : a.cg_r) + (size_t)pid * a.stride;
         rtmarch<CG64_DEPTH, 0, F2<double>, Empty>(
             nz, lds, w,
             [&](int yw, int z) -> F2<double> {
                 if (!inwin(yw, z)) return F2<double>{0.0, 0.0};
                 const int id = widx(yw, z);
-                return F2<double>{src[id], p_in[id]};
+                return F2<double>{r[id], p_in[id]};
             },
             [&](int, int, F2<double> f) -> double { return f.a + beta * f.b; },
             [&](int) { return Empty{}; },
@@ -1027,30 +1035,6 @@ __global__ __launch_bounds__(64) void k_cg64_exit(ExxArgs a) {
     a.stats[pid] = st;
 }
 
-// <r, z> per row tile of the pairs still iterating, into the rho slot of
-// iteration a.cg_it + 1 (the preconditioned form; a.cg_it = -1 after the init).
-__global__ __launch_bounds__(RZ_NT) void k_cg64_dot(ExxArgs a) {
-    __shared__ double red[RZ_NT / 64 + 1];
-    int pid, tile;
-    rz_block(pid, tile);
-    if (pid >= a.n_pairs || a.cg_done[pid]) return;
-    const sea_pair P = a.pairs[pid];
-    const int nx = P.n[0], ny = P.n[1], nz = P.n[2];
-    const int y0 = tile * RZ_ROWS, y1 = min(ny, y0 + RZ_ROWS);
-    const double* __restrict__ r = a.cg_r + (size_t)pid * a.stride;
-    const double* __restrict__ z = a.cg_z + (size_t)pid * a.stride;
-    double acc = 0.0;
-    const int row = nx, rows = y1 > y0 ? y1 - y0 : 0;
-    for (int zz = 0; zz < nz; ++zz)
-        for (int q = threadIdx.x; q < rows * row; q += RZ_NT) {
-            const int id = (zz * ny + y0) * nx + q;
-            acc += r[id] * z[id];
-        }
-    acc = block_sum<RZ_NT>(acc, red);
-    if (threadIdx.x == 0)
-        a.cg_part[((size_t)pid * RZ_TILES + tile) * CG64_SLOTS + cg64_rho_slot(a, a.cg_it + 1)] = acc;
-}
-
 __global__ __launch_bounds__(256) void k_fill_int(int* p, size_t n) {
     for (size_t k = blockIdx.x * (size_t)256 + threadIdx.x; k < n; k += (size_t)gridDim.x * 256) p[k] = 0;
 }
@@ -1092,9 +1076,23 @@ hipError_t launch_cg64_sweep(const ExxArgs& a, int sweep, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t launch_cg64_dot(const ExxArgs& a, hipStream_t s) {
+hipError_t launch_residual_list(const ExxArgs& a, const int* list, const int* count, bool write, int n_cu,
+                                hipStream_t s) {
     if (a.n_pairs <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_cg64_dot, dim3(rz_blocks(a.n_pairs)), dim3(RZ_NT), 0, s, a);
+    const int lds = (int)residual_zm_lds_bytes();
+    const void* fn = write ? (const void*)k_residual_list<true> : (const void*)k_residual_list<false>;
+    hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    if (e != hipSuccess) return e;
+    const long items = (long)a.n_pairs * RZ_TILES;
+    const dim3 grid((unsigned)(items < n_cu ? items : n_cu));   // one workgroup of 1024 threads per CU
+    if (write) hipLaunchKernelGGL(k_residual_list<true>, grid, dim3(RZ_NT), lds, s, a, list, count);
+    else hipLaunchKernelGGL(k_residual_list<false>, grid, dim3(RZ_NT), lds, s, a, list, count);
+    return hipGetLastError();
+}
+
+hipError_t launch_refine_flags(const ExxArgs& a, int* lists, int* counts, int it, bool last, hipStream_t s) {
+    if (a.n_pairs <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_refine_flags, dim3((a.n_pairs + 63) / 64), dim3(64), 0, s, a, lists, counts, it, last ? 1 : 0);
     return hipGetLastError();
 }
 

@@ -131,7 +131,6 @@ struct DstArgs {
     int in_pad, out_pad;  // plane pitch of in / out: dst_plane_pitch(nx*ny, pad); a plane
                           // pass with out_pad is the forward one (pair layout in, padded
                           // out), without it the inverse (padded in, pair layout out)
-    const int* skip;      // pairs to leave alone (nullable)
     int pair0;            // z-line pass: first pair of the launch (long calls run in chunks)
 };
 
@@ -253,7 +252,7 @@ __global__ __launch_bounds__(DP_BS, SQ ? 4 : 3) void k_dst_plane(DstArgs d) {
     const sea_pair P = d.pairs[pid];
     const int nx = P.n[0], ny = P.n[1], nz = P.n[2];
     if (nx > DS_N || ny > DS_N || nz > DS_N) return;   // keeps the multipole start
-    if ((int)blockIdx.y >= nz || (d.skip && d.skip[pid])) return;   // no plane here, or a pair left alone
+    if ((int)blockIdx.y >= nz) return;   // no plane here
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int r = lane & 15, g = lane >> 4;
     const int hb = w & 1, bp = 2 * (w >> 1);
@@ -436,7 +435,7 @@ __global__ __launch_bounds__(DP_BS, 4) void k_dst_zline(DstArgs d) {
     const int nx = P.n[0], ny = P.n[1], nz = P.n[2];
     if (nx > DS_N || ny > DS_N || nz > DS_N) return;
     const int ncol = nx * ny;
-    if (tg * DS_TC >= ncol || (d.skip && d.skip[pid]) || ((nz & 1) != 0) != F2) return;
+    if (tg * DS_TC >= ncol || ((nz & 1) != 0) != F2) return;
     const int pin = dst_plane_pitch(ncol, d.in_pad), pout = dst_plane_pitch(ncol, d.out_pad);
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int r = lane & 15, g = lane >> 4;
@@ -677,27 +676,6 @@ hipError_t launch_dst_pass(const ExxArgs& a, int pass, int variant, int shape, c
     d.out_pad = pass != 2;
     if (pass == 1) launch_zline(d, a.n_pairs, variant, shape, s);
     else launch_plane(d, a.n_pairs, variant, shape, s);
-    return hipGetLastError();
-}
-
-hipError_t launch_dst_solve(const ExxArgs& a, const double* r, double* z, double* tmp, double* tmp2, double* tab,
-                            double* mu, int pv, int zv, int shape, const int* skip, hipStream_t s) {
-    if (a.n_pairs <= 0) return hipSuccess;
-    if (pv < 0 || pv >= kNumPlane || zv < 0 || zv >= kNumZline) return hipErrorInvalidValue;
-    DstArgs d = dst_args(a, tab, mu);
-    d.skip = skip;
-    d.in = r;
-    d.out = tmp;
-    d.out_pad = 1;
-    launch_plane(d, a.n_pairs, pv, shape, s);
-    d.in = tmp;
-    d.out = tmp2;
-    d.in_pad = 1;
-    launch_zline(d, a.n_pairs, zv, shape, s);
-    d.in = tmp2;
-    d.out = z;
-    d.out_pad = 0;
-    launch_plane(d, a.n_pairs, pv, shape, s);
     return hipGetLastError();
 }
 

@@ -211,9 +211,9 @@ static bool cg64_tiled(const sea_ctx* ctx, const CellSet& S) {
            cg_zm_fits(S.pairs.data(), (int)S.pairs.size(), nullptr) && residual_zm_lds_bytes() <= ctx->max_lds;
 }
 
-// The spectral start continued by the row-tile CG preconditioned with the
-// sine transform: cubic grids and every pair taken by the transform
-static bool cg64_pcg(const sea_ctx* ctx, const CellSet& S) {
+// The spectral start refined by exact corrections (one iteration of CG
+// preconditioned by A^-1 each): cubic grids and every pair taken by the transform
+static bool refined(const sea_ctx* ctx, const CellSet& S) {
     if (ctx->opts.start != SEA_START_SPECTRAL || !S.cubic || S.pairs.empty() ||
         residual_zm_lds_bytes() > ctx->max_lds)
         return false;
@@ -282,16 +282,16 @@ ExxLayout exx_layout(const sea_ctx* ctx, const CellSet& S, bool with_v, bool eag
     L.dst_tmp = spectral ? take(np * L.pstride * sizeof(double)) : 0;
     L.dst_tab = spectral ? take(dst_table_doubles() * sizeof(double)) : 0;
     L.dst_mu = spectral ? take(dst_mu_doubles() * sizeof(double)) : 0;
-    const bool pcg = eager && cg64_pcg(ctx, S);
-    const bool tiled64 = eager && (cg64_tiled(ctx, S) || pcg);
+    const bool refine = refined(ctx, S);
+    const bool tiled64 = eager && cg64_tiled(ctx, S) && !refine;
     L.rnorm = (spectral || tiled64) ? take(np * RZ_TILES * 2 * sizeof(double)) : 0;
     L.cg_r = tiled64 ? take(np * stride * sizeof(double)) : 0;
     L.cg_p = tiled64 ? take(2 * np * stride * sizeof(double)) : 0;
-    L.cg_part = tiled64 ? take(np * RZ_TILES * 8 * sizeof(double)) : 0;
+    L.cg_part = tiled64 ? take(np * RZ_TILES * 4 * sizeof(double)) : 0;
     L.cg_rho = tiled64 ? take(np * 2 * sizeof(double)) : 0;
     L.cg_done = tiled64 ? take(np * sizeof(int)) : 0;
-    L.cg_active = tiled64 ? take(((size_t)ctx->opts.max_iter + 2) * sizeof(int)) : 0;
-    L.cg_z = pcg ? take(np * stride * sizeof(double)) : 0;
+    L.cg_active = tiled64 ? take(((size_t)ctx->opts.max_iter + 1) * sizeof(int)) : 0;
+    L.refine = refine ? take((REFINE_MAX + 1) * (np + 1) * sizeof(int)) : 0;   // counts, then lists
     L.epart = take(np * (size_t)L.ep_stride * sizeof(double));
     L.slots = take((size_t)L.n_slots * 4 * L.slot_stride * sizeof(double));
     L.stats = take(np * sizeof(DevStat));
@@ -385,6 +385,10 @@ sea_status sea_create(const sea_opts* opts, sea_ctx** out) {
     }
     ctx->device = dev;
     ctx->noalloc_scratch = noalloc_scratch_setup(dev);
+    if (eig_tables_setup(dev) != hipSuccess) {
+        delete ctx;
+        return SEA_E_HIP;
+    }
     ctx->n_cu = prop.multiProcessorCount > 0 ? prop.multiProcessorCount : 256;
     ctx->max_lds = prop.sharedMemPerBlock;
     bool ok = true;
@@ -563,8 +567,6 @@ static ExxArgs exx_args(sea_ctx* ctx, const CellSet& S, const ExxLayout& Ly, cha
     a.cg_rho = Ly.cg_rho ? (double*)(base + Ly.cg_rho) : nullptr;
     a.cg_done = Ly.cg_done ? (int*)(base + Ly.cg_done) : nullptr;
     a.cg_active = Ly.cg_active ? (int*)(base + Ly.cg_active) : nullptr;
-    a.cg_z = Ly.cg_z ? (double*)(base + Ly.cg_z) : nullptr;
-    a.cg_pre = 0;
     a.cg_it = 0;
     a.hist = ctx->hist;
     a.hist_len = ctx->hist_len;
@@ -574,49 +576,18 @@ static ExxArgs exx_args(sea_ctx* ctx, const CellSet& S, const ExxLayout& Ly, cha
 // The FP64 row-tile CG: init, then two sweeps per iteration until every pair
 // has stopped (checked from the per-iteration counters every few
 // iterations, which synchronizes), then the true residual's norms into
-// rel_res.  Preconditioned (`pre`, after a spectral start whose norms are in
-// rnorm): the init stops the pairs whose start already meets the target,
-// and z = A_odd^-1 r (three transform passes, tmp and tmp2 scratch) and
-// <r, z> follow each sweep B.
-struct Cg64Pre {
-    double *tmp, *tmp2, *tab, *mu;
-    int pv, zv;
-    int shape;
-};
-static sea_status cg64_run(sea_ctx* ctx, const ExxArgs& a0, double* rnorm, hipStream_t s, const Cg64Pre* pre) {
+// rel_res.
+static sea_status cg64_run(sea_ctx* ctx, const ExxArgs& a0, double* rnorm, hipStream_t s) {
     ExxArgs a = a0;
-    a.cg_pre = pre ? 1 : 0;
-    a.rnorm = pre ? rnorm : nullptr;   // start norms: which pairs the init stops
-    SEA_HIP_CHECK(ctx, launch_fill_int(a.cg_active, (size_t)a.max_iter + 2, s));
+    a.rnorm = nullptr;
+    SEA_HIP_CHECK(ctx, launch_fill_int(a.cg_active, (size_t)a.max_iter + 1, s));
     SEA_HIP_CHECK(ctx, launch_cg64_init(a, s));
-    if (pre) {   // every start already meets the target: nothing iterates
-        int active = 0;
-        SEA_HIP_CHECK(ctx, hipMemcpyAsync(&active, a.cg_active + a.max_iter + 1, sizeof(int), hipMemcpyDeviceToHost, s));
-        SEA_HIP_CHECK(ctx, hipStreamSynchronize(s));
-        if (active == 0) return SEA_OK;
-    }
-    auto precondition = [&](int k) -> sea_status {
-        SEA_HIP_CHECK(ctx, launch_dst_solve(a, a.cg_r, a.cg_z, pre->tmp, pre->tmp2, pre->tab, pre->mu, pre->pv,
-                                            pre->zv, pre->shape, a.cg_done, s));
-        ExxArgs ad = a;
-        ad.cg_it = k;
-        SEA_HIP_CHECK(ctx, launch_cg64_dot(ad, s));
-        return SEA_OK;
-    };
-    if (pre) {
-        const sea_status st = precondition(-1);
-        if (st != SEA_OK) return st;
-    }
-    const int every = pre ? 4 : 16;
+    constexpr int every = 16;
     for (int k = 0;; ++k) {
         a.cg_it = k;
         SEA_HIP_CHECK(ctx, launch_cg64_sweep(a, 0, s));
         if (k >= a.max_iter) break;
         SEA_HIP_CHECK(ctx, launch_cg64_sweep(a, 1, s));
-        if (pre) {
-            const sea_status st = precondition(k);
-            if (st != SEA_OK) return st;
-        }
         if (k % every == every - 1) {
             int active = 0;
             SEA_HIP_CHECK(ctx, hipMemcpyAsync(&active, a.cg_active + k, sizeof(int), hipMemcpyDeviceToHost, s));
@@ -627,6 +598,30 @@ static sea_status cg64_run(sea_ctx* ctx, const ExxArgs& a0, double* rnorm, hipSt
     a.rnorm = rnorm;
     SEA_HIP_CHECK(ctx, launch_residual_zm(a, s, false));
     SEA_HIP_CHECK(ctx, launch_cg64_exit(a, s));
+    return SEA_OK;
+}
+
+// Corrections x += A^-1 (b - A x) of the pairs whose spectral start misses
+// the target (rnorm: the start's norms).  One correction leaves about 1e-13 of
+// the residual it was given, or the rounding of b - A x, so how many are
+// launched follows from the tolerance alone (a second one serves starts with
+// a residual far above |b|, as in boxes a few points thin) and nothing waits
+// for the host; the kernels of a correction with nothing listed return at once.
+static sea_status refine_run(sea_ctx* ctx, const ExxArgs& a0, double* rnorm, double* tmp, int* counts, hipStream_t s) {
+    ExxArgs a = a0;
+    a.rnorm = rnorm;
+    const int want = a.rel_tol >= 1e-11 ? 2 : REFINE_MAX;
+    const int n = a.max_iter < want ? a.max_iter : want;
+    int* lists = counts + REFINE_MAX + 1;
+    SEA_HIP_CHECK(ctx, launch_fill_int(counts, REFINE_MAX + 1, s));
+    SEA_HIP_CHECK(ctx, launch_refine_flags(a, lists, counts, 0, n == 0, s));
+    for (int k = 0; k < n; ++k) {
+        const int* list = lists + (size_t)k * a.n_pairs;
+        SEA_HIP_CHECK(ctx, launch_residual_list(a, list, counts + k, true, ctx->n_cu, s));
+        SEA_HIP_CHECK(ctx, launch_eig_correct(a, a.bres, tmp, list, counts + k, ctx->n_cu, s));
+        SEA_HIP_CHECK(ctx, launch_residual_list(a, list, counts + k, false, ctx->n_cu, s));
+        SEA_HIP_CHECK(ctx, launch_refine_flags(a, lists, counts, k + 1, k + 1 == n, s));
+    }
     return SEA_OK;
 }
 
@@ -655,9 +650,8 @@ static sea_status exx_enqueue(sea_ctx* ctx, const CellSet& S, const ExxLayout& L
     if (hipStreamIsCapturing(s, &cap) != hipSuccess) cap = hipStreamCaptureStatusActive;
     const bool nocap = cap == hipStreamCaptureStatusNone;
     const bool tiled64 = cg64_tiled(ctx, S) && a.cg_r && nocap;
-    // the spectral start's continuation: the sine-transform-preconditioned CG
-    const bool pcg = cg64_pcg(ctx, S) && a.cg_z && nocap;
-    const bool finish = zm || tiled64 || pcg;   // pair energies and flags by k_cg_finish
+    const bool refine = refined(ctx, S);        // the spectral start with its corrections
+    const bool finish = zm || tiled64 || refine;   // pair energies and flags by k_cg_finish
     if (!zm && ctx->opts.stencil_dtype != SEA_F64)
         return fail(ctx, SEA_E_ARG, "SEA_F32 state needs cubic grids and pair domains with n[0], n[1] <= 64");
     int nz_max = 1;
@@ -728,28 +722,24 @@ static sea_status exx_enqueue(sea_ctx* ctx, const CellSet& S, const ExxLayout& L
                                                                  if (pass == 2) timer_off(SEA_STAGE_DST);
                                                              }
                                                          }));
-                if (zm || pcg) {
+                if (zm || refine) {
                     ExxArgs ar = a;
                     ar.rnorm = (double*)(base + Ly.rnorm);
-                    ar.cg_done = nullptr;   // (stale flags of an earlier call)
                     const bool rzm = residual_zm_lds_bytes() <= ctx->max_lds;
                     timer_on(SEA_STAGE_RESIDUAL);
-                    // (the preconditioned continuation forms its residual itself)
-                    SEA_HIP_CHECK(ctx, rzm ? launch_residual_zm(ar, s, !pcg) : launch_start_residual(ar, s));
+                    // (the corrections form b - A x of the pairs that need them)
+                    SEA_HIP_CHECK(ctx, rzm ? launch_residual_zm(ar, s, !refine) : launch_start_residual(ar, s));
                     timer_off(SEA_STAGE_RESIDUAL);
                 }
-            } else if (!zm && !tiled64 && !pcg) {
+            } else if (!zm && !tiled64 && !refine) {
                 SEA_HIP_CHECK(ctx, launch_start_residual(a, s));
             }
             timer_off(SEA_STAGE_GUESS);
         }
         timer_on(SEA_STAGE_CG);
-        if (pcg) {
-            int pv = 0, zv = 0;
-            dst_variants(ctx, pv, zv);
-            const Cg64Pre pre{(double*)(base + Ly.dst_tmp), a.bres, (double*)(base + Ly.dst_tab),
-                              (double*)(base + Ly.dst_mu), pv, zv, S.dst_shape};
-            sea_status st = cg64_run(ctx, a, (double*)(base + Ly.rnorm), s, &pre);
+        if (refine) {
+            sea_status st = refine_run(ctx, a, (double*)(base + Ly.rnorm), (double*)(base + Ly.dst_tmp),
+                                       (int*)(base + Ly.refine), s);
             if (st != SEA_OK) return st;
             timer_off(SEA_STAGE_CG);
             if (!f.action) {
@@ -772,7 +762,7 @@ static sea_status exx_enqueue(sea_ctx* ctx, const CellSet& S, const ExxLayout& L
                 timer_off(SEA_STAGE_FINISH);
             }
         } else if (tiled64) {
-            sea_status st = cg64_run(ctx, a, (double*)(base + Ly.rnorm), s, nullptr);
+            sea_status st = cg64_run(ctx, a, (double*)(base + Ly.rnorm), s);
             if (st != SEA_OK) return st;
             timer_off(SEA_STAGE_CG);
             if (!f.action) {

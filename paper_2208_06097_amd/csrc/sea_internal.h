@@ -73,8 +73,8 @@ struct StageTimer {
 // Byte layout of the exx workspace (offsets from the workspace base).
 struct ExxLayout {
     size_t pairs, pair_cell, order, dbox, cells, partial, mom, b, v, bres, slots, stats, csr_off, csr_ent, scal, counter;
-    size_t nnx, nny, nnact, dst_tmp, dst_tab, dst_mu, rnorm, racah_tab, mpoly, epart, cg_r, cg_p, cg_z, cg_part,
-        cg_rho, cg_done, cg_active, total;
+    size_t nnx, nny, nnact, dst_tmp, dst_tab, dst_mu, rnorm, racah_tab, mpoly, epart, cg_r, cg_p, cg_part,
+        cg_rho, cg_done, cg_active, refine, total;
     int nmax;
     int ep_stride;        // pair-energy partial slots per pair (scatter)
     int n_chunks;
@@ -143,11 +143,9 @@ struct ExxArgs {
     double* cg_r;         // n_pairs x stride: residual
     double* cg_p;         // 2 x n_pairs x stride: search direction, by iteration parity
     double* cg_part;      // n_pairs x RZ_TILES x 8 partial sums per row tile (k_cg.hip)
-    double* cg_z;         // n_pairs x stride: preconditioned residual (nullable)
-    int cg_pre;           // the CG is preconditioned by the sine transform (z = A_odd^-1 r)
     double* cg_rho;       // n_pairs x 2: |r|^2 of the last two iterations
-    int* cg_done;         // n_pairs: the pair has stopped (2: by its start); null outside the row-tile CG
-    int* cg_active;       // max_iter + 2 counters: pairs still iterating at each iteration; the last, after the init
+    int* cg_done;         // n_pairs: the pair has stopped; null outside the row-tile CG
+    int* cg_active;       // max_iter + 1 counters: pairs still iterating at each iteration
     int cg_it;            // the iteration a sweep launch performs
     double* hist;         // n_pairs x (hist_len + 1) relative residuals per iteration (nullable)
     int hist_len;
@@ -268,12 +266,19 @@ hipError_t launch_residual_zm(const ExxArgs& a, hipStream_t s, bool write = true
 hipError_t launch_cg64_init(const ExxArgs& a, hipStream_t s);
 hipError_t launch_cg64_sweep(const ExxArgs& a, int sweep, hipStream_t s);
 hipError_t launch_cg64_exit(const ExxArgs& a, hipStream_t s);
-// <r, z> partials of the preconditioned form (after z = A_odd^-1 r)
-hipError_t launch_cg64_dot(const ExxArgs& a, hipStream_t s);
-// z = A_odd^-1 r for the pairs not marked in `skip` (the three transform
-// passes with the context's variants; tmp, tmp2 scratch of the pair arrays' size)
-hipError_t launch_dst_solve(const ExxArgs& a, const double* r, double* z, double* tmp, double* tmp2, double* tab,
-                            double* mu, int pv, int zv, int shape, const int* skip, hipStream_t s);
+// Refinement of the spectral start's potentials (cubic grids, every pair taken
+// by the transform).  launch_refine_flags after the norms pass sets each
+// pair's iters, converged and rel_res and lists the pairs that miss the target
+// (lists: n_pairs ints per iteration; counts: one per iteration, zeroed
+// before); launch_residual_list writes b - A x of the listed pairs into bres,
+// or their norms into a.rnorm; launch_eig_correct (k_eig.hip) then adds
+// A^-1 r to x, r in the pair layout, overwritten, tmp a transform intermediate.
+constexpr int REFINE_MAX = 6;
+hipError_t launch_refine_flags(const ExxArgs& a, int* lists, int* counts, int it, bool last, hipStream_t s);
+hipError_t launch_residual_list(const ExxArgs& a, const int* list, const int* count, bool write, int n_cu, hipStream_t s);
+hipError_t launch_eig_correct(const ExxArgs& a, double* r, double* tmp, const int* list, const int* count, int n_cu,
+                              hipStream_t s);
+hipError_t eig_tables_setup(int dev);
 hipError_t launch_fill_int(int* p, size_t n, hipStream_t s);
 // p[0 .. n) = NaN (the residual histories' empty entries)
 hipError_t launch_fill_nan(double* p, size_t n, hipStream_t s);

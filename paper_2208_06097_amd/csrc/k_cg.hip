@@ -517,7 +517,7 @@ __global__ __launch_bounds__(NT) void k_cg_zm(ExxArgs a) {
 
 // Pair energy e_ij = dV sum rho x and the final flags, one workgroup per pair.
 // With a.epart (after the scatter) a pair whose W box of orbital i holds its
-// domain once has its energy from the scatter's partials, summed here in
+// domain has its energy from the scatter's partials, summed here in
 // slot order; the others (and every pair without a.epart) sum rho x over
 // the domain here.
 constexpr int FIN_BS = 512;
@@ -532,7 +532,7 @@ __global__ __launch_bounds__(FIN_BS) void k_cg_finish(ExxArgs a) {
     const double* x = a.v + (size_t)pid * a.stride;
     const size_t oi = (size_t)P.i * C.Ng, oj = (size_t)P.j * C.Ng;
     double e = 0.0;
-    if (a.epart && ep_takes(P, a.dbox + 12 * (size_t)pid, C.N)) {
+    if (a.epart && ep_takes(P.lo, P.n, a.dbox + 12 * (size_t)pid)) {
         const int ns = ep_slots(P, C.N);
         const double* ep = a.epart + (size_t)pid * a.ep_stride;
         for (int k = threadIdx.x; k < ns; k += FIN_BS) e += ep[k];

@@ -63,33 +63,61 @@ __device__ __forceinline__ bool axis_hits(int t0, int T, int lo, int n, int N) {
 // outside it the multipole potential of the pair (Eq. 10).
 // The cell's record comes by value, so its pointers are kernel arguments:
 // uniform, and known to the compiler to address global memory.
-// GENERAL: some W box reaches beyond its pair's domain (multipole values
-// there) or is wider than the cell (points met several times); without it
-// every W box is its pair's domain, and the kernel carries neither path (nor
-// their registers).  PT: the orbitals' precision.
-template <bool GENERAL, typename PT, int ORDER>
-__global__ __launch_bounds__(SC_BS) void k_scatter(ExxArgs a, const DevCell C, const int* __restrict__ off_all,
-                                                   const int2* __restrict__ ent) {
-    __shared__ int list[SC_MAXE];
+// BOX: what the cell's W boxes ask for.  0: every W box is its pair's domain
+// and holds a grid point once; 1: some is wider than the cell (points met once
+// per image of the cell); 2: some reaches beyond its pair's domain as well
+// (multipole values there).  Each kernel carries no more than its own paths
+// (nor their registers).  Images are passes of the same column loads: point by
+// point with the images innermost, as the kernel did before, the 8-molecule
+// cell (63-point domains in a 60-point cell) took 1.28 ms and a domain sum of
+// 0.35 ms for its pair energies; now 0.56 ms together.  Multipole values come
+// from the column's line coefficients, folded once for its SC_TZ points and
+// evaluated side by side (84 terms a point, one point after another, before:
+// the epsilon boxes of the 64-molecule cell 2.54 ms, now 2.07 ms with the
+// launch that finds their tiles).
+// PT: the orbitals' precision.
+struct ScShared {
+    int list[SC_MAXE];
     // per listed entry: pair, partner orbital, W box (lo, n), domain (lo, n),
-    // wide flag, energy slot (-1: this workgroup adds nothing to e_ij)
-    __shared__ int meta[SC_MAXE][16];
+    // energy slot (-1: this workgroup adds nothing to e_ij)
+    int meta[SC_MAXE][15];
     // per entry of the orbital's list: the wavefronts' parts of its energy
     // partial, its slot and pair (the list has at most SC_EP_MAXE entries
     // when a.epart is set)
-    __shared__ double ep_w[SC_EP_MAXE][SC_BS / 64];
-    __shared__ int ep_slot_of[SC_EP_MAXE], ep_pid_of[SC_EP_MAXE];
+    double ep_w[SC_EP_MAXE][SC_BS / 64];
+    int ep_slot_of[SC_EP_MAXE], ep_pid_of[SC_EP_MAXE];
     // this orbital at the tile's points (energy partials)
-    __shared__ double po_s[SC_TZ][SC_BS];
-    __shared__ int cnt, wide, n_e;
+    double po_s[SC_TZ][SC_BS];
+    int cnt, n_e;
+};
+// BOX 2 alone: the multipole coefficients of SC_CFN entries at a time (read
+// from memory where they are used, they held each entry up by a chain of
+// scalar loads)
+constexpr int SC_CFN = 12;
+struct ScCoeffs {
+    double cf[SC_CFN][SC_NM];
+};
+struct ScNone {};
+
+__device__ __forceinline__ int sc_tiles(const DevCell& C) {
+    return ((C.N[0] + SC_TX - 1) / SC_TX) * ((C.N[1] + SC_TY - 1) / SC_TY) * ((C.N[2] + SC_TZ - 1) / SC_TZ);
+}
+
+template <int BOX, typename PT>
+__device__ __forceinline__ void scatter_tile(const ExxArgs& a, const DevCell& C, const int* __restrict__ off_all,
+                                             const ScEntry* __restrict__ ent, int o, int t, ScShared& S,
+                                             typename std::conditional<BOX == 2, ScCoeffs, ScNone>::type& CF) {
+    auto& list = S.list;
+    auto& meta = S.meta;
+    auto& ep_w = S.ep_w;
+    auto& ep_slot_of = S.ep_slot_of;
+    auto& ep_pid_of = S.ep_pid_of;
+    auto& po_s = S.po_s;
+    int &cnt = S.cnt, &n_e = S.n_e;
     const int* off = off_all + C.csr_base;
     double* __restrict__ W = C.W;
     const int tiles_x = (C.N[0] + SC_TX - 1) / SC_TX;
     const int tiles_y = (C.N[1] + SC_TY - 1) / SC_TY;
-    const int n_tiles = tiles_x * tiles_y * ((C.N[2] + SC_TZ - 1) / SC_TZ);
-    int o, t;
-    sc_block<ORDER>(n_tiles, C.n_occ, o, t);
-    if (t >= n_tiles) return;
     const int tx0 = (t % tiles_x) * SC_TX;
     const int ty0 = ((t / tiles_x) % tiles_y) * SC_TY;
     const int tz0 = (t / (tiles_x * tiles_y)) * SC_TZ;
@@ -112,66 +140,56 @@ __global__ __launch_bounds__(SC_BS) void k_scatter(ExxArgs a, const DevCell C, c
         // hits keep their order through the ballot's prefix counts
         if (threadIdx.x < 64) {
             const int lane = threadIdx.x;
-            int m = 0, nw = 0, ne = 0;
+            int m = 0, ne = 0;
             for (int b0 = c0; b0 < c1; b0 += 64) {
                 const int e = b0 + lane;
-                bool hit = false, wd = false;
+                bool hit = false;
                 int slot = -1;
+                ScEntry R{};
                 if (e < c1) {
-                    const int pid = ent[e].x;
-                    const sea_pair P = a.pairs[pid];
-                    const bool iside = o == P.i;
-                    const int* D = a.dbox + 12 * (size_t)pid + (iside ? 0 : 6);
-                    hit = axis_hits(tx0, SC_TX, D[0], D[3], C.N[0]) && axis_hits(ty0, SC_TY, D[1], D[4], C.N[1]) &&
-                          axis_hits(tz0, SC_TZ, D[2], D[5], C.N[2]);
-                    wd = GENERAL && hit && (D[3] > C.N[0] || D[4] > C.N[1] || D[5] > C.N[2]);
+                    R = ent[e];
+                    hit = axis_hits(tx0, SC_TX, R.D[0], R.D[3], C.N[0]) && axis_hits(ty0, SC_TY, R.D[1], R.D[4], C.N[1]) &&
+                          axis_hits(tz0, SC_TZ, R.D[2], R.D[5], C.N[2]);
                     // the pair's energy partial of this tile: i side, a W box
-                    // that holds the domain once, a tile the domain meets
-                    if (hit && iside && take_e && ep_takes(P, D, C.N) &&
-                        axis_hits(tx0, SC_TX, P.lo[0], P.n[0], C.N[0]) &&
-                        axis_hits(ty0, SC_TY, P.lo[1], P.n[1], C.N[1]) &&
-                        axis_hits(tz0, SC_TZ, P.lo[2], P.n[2], C.N[2]))
-                        slot = ep_slot(P, C.N, tc, tiles);
+                    // that holds the domain, a tile the domain meets
+                    if (hit && R.iside && take_e && ep_takes(R.lo, R.n, R.D) &&
+                        axis_hits(tx0, SC_TX, R.lo[0], R.n[0], C.N[0]) &&
+                        axis_hits(ty0, SC_TY, R.lo[1], R.n[1], C.N[1]) &&
+                        axis_hits(tz0, SC_TZ, R.lo[2], R.n[2], C.N[2]))
+                        slot = ep_slot(R.lo, R.n, C.N, tc, tiles);
                 }
                 const unsigned long long mask = __ballot(hit);
                 const unsigned long long below = lane ? (mask << (64 - lane)) : 0ull;
                 if (hit) {
                     const int q = m + __popcll(below);
-                    const int2 en = ent[e];
-                    const sea_pair P = a.pairs[en.x];
-                    const int* D = a.dbox + 12 * (size_t)en.x + (o == P.i ? 0 : 6);
                     list[q] = e;
-                    meta[q][0] = en.x;
-                    meta[q][1] = en.y;
+                    meta[q][0] = R.pid;
+                    meta[q][1] = R.other;
 #pragma unroll
-                    for (int d = 0; d < 6; ++d) meta[q][2 + d] = D[d];
+                    for (int d = 0; d < 6; ++d) meta[q][2 + d] = R.D[d];
 #pragma unroll
                     for (int d = 0; d < 3; ++d) {
-                        meta[q][8 + d] = P.lo[d];
-                        meta[q][11 + d] = P.n[d];
+                        meta[q][8 + d] = R.lo[d];
+                        meta[q][11 + d] = R.n[d];
                     }
-                    meta[q][14] = wd;
-                    meta[q][15] = slot;
+                    meta[q][14] = slot;
                     if (slot >= 0) {
                         ep_slot_of[e - e0] = slot;
-                        ep_pid_of[e - e0] = en.x;
+                        ep_pid_of[e - e0] = R.pid;
                     }
                 }
                 m += __popcll(mask);
-                nw += __popcll(__ballot(wd));
                 ne += __popcll(__ballot(slot >= 0));
             }
             if (lane == 0) {
                 cnt = m;
-                wide = nw;
                 n_e = ne;
             }
         }
         __syncthreads();
         const int m = cnt;
-        // fast path: this thread's column (gx, gy) and planes tz0 + k; a box no
-        // wider than the cell holds each grid point at most once, found from
-        // per-pair offsets by compare-and-subtract instead of modulo
+        // this thread's column (gx, gy) and planes tz0 + k, found in each box
+        // from per-pair offsets by compare-and-subtract instead of modulo
         static_assert(SC_TX * SC_TY == SC_BS, "one (x, y) column per thread");
         const int cx = threadIdx.x % SC_TX, cy = threadIdx.x / SC_TX;
         const int gx = tx0 + cx, gy = ty0 + cy;
@@ -187,14 +205,23 @@ __global__ __launch_bounds__(SC_BS) void k_scatter(ExxArgs a, const DevCell C, c
                     po_s[k][threadIdx.x] = colin ? (double)ph[gcol + (size_t)min(tz0 + k, C.N[2] - 1) * gplane] : 0.0;
             }
             for (int q = 0; q < m; ++q) {
+                if constexpr (BOX == 2) {
+                    if (q % SC_CFN == 0) {   // uniform
+                        __syncthreads();
+                        for (int i = threadIdx.x; i < SC_CFN * SC_NM; i += SC_BS) {
+                            const int qe = q + i / SC_NM;
+                            if (qe < m) CF.cf[i / SC_NM][i % SC_NM] = a.mpoly[(size_t)meta[qe][0] * SC_NM + i % SC_NM];
+                        }
+                        __syncthreads();
+                    }
+                }
                 // the entry's values are the same in every lane: read them into
                 // scalar registers, so the per-plane addresses below are a scalar
                 // base plus one per-lane offset shared by all planes
                 int e[14];
 #pragma unroll
                 for (int d = 0; d < 14; ++d) e[d] = __builtin_amdgcn_readfirstlane(meta[q][d]);
-                if (GENERAL && __builtin_amdgcn_readfirstlane(meta[q][14])) continue;   // general path below
-                const int eslot = __builtin_amdgcn_readfirstlane(meta[q][15]);
+                const int eslot = __builtin_amdgcn_readfirstlane(meta[q][14]);
                 const int pid = e[0], oth = e[1];
                 const int* D = &e[2];
                 const int* plo = &e[8];
@@ -206,8 +233,20 @@ __global__ __launch_bounds__(SC_BS) void k_scatter(ExxArgs a, const DevCell C, c
                 lx -= (lx >= C.N[0]) ? C.N[0] : 0;
                 ly -= (ly >= C.N[1]) ? C.N[1] : 0;
                 double ep = 0.0;
-                if (colin && lx < D[3] && ly < D[4]) {
+                // a box wider than the cell meets a grid point once per image of
+                // the cell that it reaches into (one image otherwise)
+                const int lx0 = lx, ly0 = ly;
+                const int imx = BOX ? (D[3] + C.N[0] - 1) / C.N[0] : 1, imy = BOX ? (D[4] + C.N[1] - 1) / C.N[1] : 1,
+                          imz = BOX ? (D[5] + C.N[2] - 1) / C.N[2] : 1;
+                for (int im = 0; im < imx * imy * imz; ++im) {
+                    if (BOX) {
+                        lx = lx0 + im % imx * C.N[0];
+                        ly = ly0 + im / imx % imy * C.N[1];
+                    }
+                    if (!(colin && lx < D[3] && ly < D[4])) continue;
+                    const int lzi = BOX ? im / (imx * imy) * C.N[2] : 0;
                     const int lz0 = wrap_idx(tz0 - D[2], C.N[2]);
+                    if (BOX && (lz0 + SC_TZ > C.N[2] ? 0 : lz0) + lzi >= D[5]) continue;   // no plane of this image
                     const int sx = D[0] + lx - plo[0], sy = D[1] + ly - plo[1];
                     const bool in_xy = sx >= 0 && sx < pn[0] && sy >= 0 && sy < pn[1];
                     const double* v = a.v + (size_t)pid * a.stride;
@@ -219,20 +258,20 @@ __global__ __launch_bounds__(SC_BS) void k_scatter(ExxArgs a, const DevCell C, c
                     // together), then the multipole values of points outside the domain
                     double vv[SC_TZ];
                     PT pv[SC_TZ];   // converted at the product: no wait inside the load sequence
-                    int lzs[SC_TZ];
-                    bool me[SC_TZ], ins[SC_TZ];
+                    bool ins[SC_TZ];
+                    unsigned me = 0;   // points outside the domain (BOX 2)
 #pragma unroll
                     for (int k = 0; k < SC_TZ; ++k) {
                         const int gz = tz0 + k;
                         int lz = lz0 + k;
                         lz -= (lz >= C.N[2]) ? C.N[2] : 0;
-                        lzs[k] = lz;
+                        lz += lzi;
                         const bool valid = gz < C.N[2] && lz < D[5];
                         const int sz = D[2] + lz - plo[2];
                         const bool zin = valid && sz >= 0 && sz < pn[2];
                         const bool inside = zin && in_xy;
                         ins[k] = inside;
-                        me[k] = GENERAL && valid && !inside;
+                        if (BOX == 2 && valid && !inside) me |= 1u << k;
                         if constexpr (std::is_same<PT, float>::value) {
                             // unconditional (a clamped plane is in bounds), so the
                             // widening is not pulled into a branch with its own wait
@@ -246,18 +285,25 @@ __global__ __launch_bounds__(SC_BS) void k_scatter(ExxArgs a, const DevCell C, c
                         const double* vz = v + (size_t)(zin ? sz : 0) * vplane;
                         vv[k] = inside ? vz[vcol] : 0.0;
                     }
-                    bool any_me = false;
+                    if constexpr (BOX == 2) {
+                        if (me) {   // the multipole value outside the domain (W boxes beyond it)
+                            // the column's line coefficients once; then every
+                            // point, without a branch between them
+                            const double* org = a.pairs[pid].origin;
+                            const double d[3] = {(D[0] + lx) * C.h[0] - org[0], (D[1] + ly) * C.h[1] - org[1], 0.0};
+                            double ql[SEA_LMAX + 1][SEA_LMAX + 1];
+                            me_line_coeffs<2>(CF.cf[q % SC_CFN], d, ql);
+                            const double rt2 = d[0] * d[0] + d[1] * d[1];
 #pragma unroll
-                    for (int k = 0; k < SC_TZ; ++k) any_me |= me[k];
-                    if (GENERAL && any_me) {   // the multipole value outside the domain (W boxes beyond it)
-                        const double* cf = a.mpoly + (size_t)pid * SC_NM;
-                        const double* org = a.pairs[pid].origin;
-#pragma unroll
-                        for (int k = 0; k < SC_TZ; ++k)
-                            if (me[k])
-                                vv[k] = me_inverted_potential(cf, (D[0] + lx) * C.h[0] - org[0],
-                                                               (D[1] + ly) * C.h[1] - org[1],
-                                                               (D[2] + lzs[k]) * C.h[2] - org[2]);
+                            for (int k = 0; k < SC_TZ; ++k) {
+                                int lz = lz0 + k;
+                                lz -= (lz >= C.N[2]) ? C.N[2] : 0;
+                                const double z = (D[2] + lz + lzi) * C.h[2] - org[2];
+                                // (at the origin itself, inside a domain, the value is not used)
+                                const double mv = me_line_potential(ql, z, rt2);
+                                vv[k] = (me >> k & 1u) ? mv : vv[k];
+                            }
+                        }
                     }
 #pragma unroll
                     for (int k = 0; k < SC_TZ; ++k) {
@@ -272,39 +318,6 @@ __global__ __launch_bounds__(SC_BS) void k_scatter(ExxArgs a, const DevCell C, c
                     if ((threadIdx.x & 63) == 0) ep_w[list[q] - e0][threadIdx.x >> 6] = ep;
                 }
             }
-        }
-        // general path: boxes wider than the cell (a grid point met several times)
-        if (GENERAL && wide)
-#pragma unroll
-        for (int k = 0; k < SC_TX * SC_TY * SC_TZ / SC_BS; ++k) {
-            const int lid = threadIdx.x + k * SC_BS;
-            const int gx = tx0 + lid % SC_TX, gy = ty0 + (lid / SC_TX) % SC_TY, gz = tz0 + lid / (SC_TX * SC_TY);
-            if (gx >= C.N[0] || gy >= C.N[1] || gz >= C.N[2]) continue;
-            const size_t g = ((size_t)gz * C.N[1] + gy) * C.N[0] + gx;
-            double s = acc[k];
-            for (int q = 0; q < m; ++q) {
-                const int2 en = ent[list[q]];
-                const sea_pair P = a.pairs[en.x];
-                const int* D = a.dbox + 12 * (size_t)en.x + (o == P.i ? 0 : 6);
-                if (!(D[3] > C.N[0] || D[4] > C.N[1] || D[5] > C.N[2])) continue;   // fast path above
-                const double* v = a.v + (size_t)en.x * a.stride;
-                const double* cf = a.mpoly + (size_t)en.x * SC_NM;
-                const double ph = load_phi(C.phi, C.phi_f32, (size_t)en.y * C.Ng + g);
-                for (int lz = wrap_idx(gz - D[2], C.N[2]); lz < D[5]; lz += C.N[2])
-                    for (int ly = wrap_idx(gy - D[1], C.N[1]); ly < D[4]; ly += C.N[1])
-                        for (int lx = wrap_idx(gx - D[0], C.N[0]); lx < D[3]; lx += C.N[0]) {
-                            const int px = D[0] + lx, py = D[1] + ly, pz = D[2] + lz;  // unwrapped point
-                            const int sx = px - P.lo[0], sy = py - P.lo[1], sz = pz - P.lo[2];
-                            double val;
-                            if (sx >= 0 && sx < P.n[0] && sy >= 0 && sy < P.n[1] && sz >= 0 && sz < P.n[2])
-                                val = v[((size_t)sz * P.n[1] + sy) * P.n[0] + sx];
-                            else
-                                val = me_inverted_potential(cf, px * C.h[0] - P.origin[0],
-                                                             py * C.h[1] - P.origin[1], pz * C.h[2] - P.origin[2]);
-                            s += val * ph;
-                        }
-            }
-            acc[k] = s;
         }
         __syncthreads();
     }
@@ -328,6 +341,72 @@ __global__ __launch_bounds__(SC_BS) void k_scatter(ExxArgs a, const DevCell C, c
     }
 }
 
+template <int BOX, typename PT, int ORDER>
+__global__ __launch_bounds__(SC_BS, BOX ? 4 : 5) void k_scatter(ExxArgs a, const DevCell C,
+                                                                const int* __restrict__ off_all,
+                                                                const ScEntry* __restrict__ ent) {
+    __shared__ ScShared S;
+    ScNone none;
+    const int n_tiles = sc_tiles(C);
+    int o, t;
+    sc_block<ORDER>(n_tiles, C.n_occ, o, t);
+    if (t >= n_tiles) return;
+    scatter_tile<BOX, PT>(a, C, off_all, ent, o, t, S, none);
+}
+
+// BOX 2 in two launches.  Most tiles of most orbitals meet no box there (the
+// epsilon boxes of the 64-molecule cell: 37 of 230 thousand do), and a workgroup
+// of the kernel above, whose multipole path takes the registers of a third of
+// a CU, spends its time finding that out.  This one, at full occupancy, writes
+// the zeros of the tiles no box meets and lists the others.
+template <int ORDER>
+__global__ __launch_bounds__(SC_BS) void k_scatter_scan(const DevCell C, const int* __restrict__ off_all,
+                                                        const ScEntry* __restrict__ ent, int* __restrict__ work) {
+    __shared__ int any;
+    const int n_tiles = sc_tiles(C);
+    int o, t;
+    sc_block<ORDER>(n_tiles, C.n_occ, o, t);
+    if (t >= n_tiles) return;
+    const int tiles_x = (C.N[0] + SC_TX - 1) / SC_TX, tiles_y = (C.N[1] + SC_TY - 1) / SC_TY;
+    const int tx0 = t % tiles_x * SC_TX, ty0 = t / tiles_x % tiles_y * SC_TY, tz0 = t / (tiles_x * tiles_y) * SC_TZ;
+    const int* off = off_all + C.csr_base;
+    const int e0 = off[o], e1 = off[o + 1];
+    if (threadIdx.x == 0) any = 0;
+    __syncthreads();
+    bool hit = false;
+    for (int e = e0 + threadIdx.x; e < e1; e += SC_BS) {
+        const int* D = ent[e].D;
+        hit = hit || (axis_hits(tx0, SC_TX, D[0], D[3], C.N[0]) && axis_hits(ty0, SC_TY, D[1], D[4], C.N[1]) &&
+                      axis_hits(tz0, SC_TZ, D[2], D[5], C.N[2]));
+    }
+    if (hit) any = 1;
+    __syncthreads();
+    if (any) {
+        if (threadIdx.x == 0) work[1 + atomicAdd(work, 1)] = t * C.n_occ + o;
+        return;
+    }
+#pragma unroll
+    for (int k = 0; k < SC_TZ; ++k) {
+        const int gx = tx0 + (int)threadIdx.x % SC_TX, gy = ty0 + (int)threadIdx.x / SC_TX, gz = tz0 + k;
+        if (gx < C.N[0] && gy < C.N[1] && gz < C.N[2])
+            C.W[(size_t)o * C.Ng + ((size_t)gz * C.N[1] + gy) * C.N[0] + gx] = 0.0;
+    }
+}
+
+template <typename PT>
+__global__ __launch_bounds__(SC_BS, 3) void k_scatter_listed(ExxArgs a, const DevCell C, const int* __restrict__ off_all,
+                                                             const ScEntry* __restrict__ ent,
+                                                             const int* __restrict__ work) {
+    __shared__ ScShared S;
+    __shared__ ScCoeffs CF;
+    const int n = work[0];
+    for (int i = blockIdx.x; i < n; i += gridDim.x) {
+        const int k = work[1 + i];
+        scatter_tile<2, PT>(a, C, off_all, ent, k % C.n_occ, k / C.n_occ, S, CF);
+        __syncthreads();   // the arrays in LDS are reused
+    }
+}
+
 __global__ __launch_bounds__(256) void k_epart_clear(double* __restrict__ p, size_t n) {
     for (size_t k = blockIdx.x * (size_t)256 + threadIdx.x; k < n; k += (size_t)gridDim.x * 256) p[k] = 0.0;
 }
@@ -343,39 +422,56 @@ hipError_t launch_epart_clear(const ExxArgs& a, hipStream_t s) {
 }
 
 namespace {
-using ScatterKernel = void (*)(ExxArgs, const DevCell, const int*, const int2*);
+using ScatterKernel = void (*)(ExxArgs, const DevCell, const int*, const ScEntry*);
+using ScanKernel = void (*)(const DevCell, const int*, const ScEntry*, int*);
 struct ScatterVariant {
     const char* name;
     int order;
-    ScatterKernel k[2][2];   // [general W boxes][FP32 orbitals]
+    ScatterKernel k[2][2];   // [W boxes][FP32 orbitals]
+    ScanKernel scan;
 };
 template <int ORDER>
 ScatterVariant scatter_variant(const char* name) {
     return {name,
             ORDER,
-            {{k_scatter<false, double, ORDER>, k_scatter<false, float, ORDER>},
-             {k_scatter<true, double, ORDER>, k_scatter<true, float, ORDER>}}};
+            {{k_scatter<0, double, ORDER>, k_scatter<0, float, ORDER>},
+             {k_scatter<1, double, ORDER>, k_scatter<1, float, ORDER>}},
+            k_scatter_scan<ORDER>};
 }
 const ScatterVariant kScatterVariants[] = {
     scatter_variant<2>("scatter-xcd-owners"),
     scatter_variant<0>("scatter-orbital-tiles"),
 };
 constexpr int kNumScatter = sizeof(kScatterVariants) / sizeof(kScatterVariants[0]);
+long sc_cell_tiles(const DevCell& c) {
+    return (long)((c.N[0] + SC_TX - 1) / SC_TX) * ((c.N[1] + SC_TY - 1) / SC_TY) * ((c.N[2] + SC_TZ - 1) / SC_TZ);
+}
 }  // namespace
 
 int scatter_variant_count() { return kNumScatter; }
 const char* scatter_variant_name(int v) { return v >= 0 && v < kNumScatter ? kScatterVariants[v].name : nullptr; }
 
-hipError_t launch_scatter(const ExxArgs& a, const DevCell& cell, const int* csr_off, const int2* csr_ent, int variant,
-                          hipStream_t s) {
+size_t scatter_work_ints(const DevCell& c) { return c.wbox == 2 ? 1 + (size_t)sc_cell_tiles(c) * c.n_occ : 0; }
+
+hipError_t launch_scatter(const ExxArgs& a, const DevCell& cell, const int* csr_off, const ScEntry* csr_ent, int* work,
+                          int variant, int n_cu, hipStream_t s) {
     if (variant < 0 || variant >= kNumScatter) return hipErrorInvalidValue;
     const ScatterVariant& V = kScatterVariants[variant];
-    const int* N = cell.N;
-    const int tiles = ((N[0] + SC_TX - 1) / SC_TX) * ((N[1] + SC_TY - 1) / SC_TY) * ((N[2] + SC_TZ - 1) / SC_TZ);
-    const long nb = sc_grid(V.order, tiles, cell.n_occ);
+    const long tiles = sc_cell_tiles(cell), nb = sc_grid(V.order, (int)tiles, cell.n_occ);
     if (nb > 0x7fffffffL) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(V.k[cell.wbox_general ? 1 : 0][cell.phi_f32 ? 1 : 0], dim3((unsigned)nb), dim3(SC_BS), 0, s, a,
-                       cell, csr_off, csr_ent);
+    if (cell.wbox < 2) {
+        hipLaunchKernelGGL(V.k[cell.wbox][cell.phi_f32 ? 1 : 0], dim3((unsigned)nb), dim3(SC_BS), 0, s, a, cell, csr_off,
+                           csr_ent);
+        return hipGetLastError();
+    }
+    hipError_t e = launch_fill_int(work, 1, s);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(V.scan, dim3((unsigned)nb), dim3(SC_BS), 0, s, cell, csr_off, csr_ent, work);
+    const long items = tiles * cell.n_occ, most = 12L * n_cu;   // a few rounds of three workgroups per CU
+    const dim3 grid((unsigned)(items < most ? items : most));
+    if (cell.phi_f32)
+        hipLaunchKernelGGL(k_scatter_listed<float>, grid, dim3(SC_BS), 0, s, a, cell, csr_off, csr_ent, work);
+    else
+        hipLaunchKernelGGL(k_scatter_listed<double>, grid, dim3(SC_BS), 0, s, a, cell, csr_off, csr_ent, work);
     return hipGetLastError();
 }
-

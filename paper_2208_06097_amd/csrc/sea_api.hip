@@ -97,7 +97,7 @@ struct CellSet {
     std::vector<sea_pair> pairs;
     std::vector<int> pair_cell;
     std::vector<int> csr_off;
-    std::vector<int2> csr_ent;
+    std::vector<ScEntry> csr_ent;
     std::vector<DevCell> dev;
     std::vector<int> order;  // CG queue: pair ids by decreasing interior size (ties: id order)
     std::vector<int> dbox;   // 12 per pair: W_i box, W_j box (default: the pair's domain twice)
@@ -166,7 +166,8 @@ static sea_status build_cellset(sea_ctx* ctx, int n_cells, const sea_cell* cells
                 }
                 S.dbox.insert(S.dbox.end(), box, box + 6);
                 for (int a2 = 0; a2 < 3; ++a2)
-                    if (box[a2] != P.lo[a2] || box[3 + a2] != P.n[a2] || box[3 + a2] > D.N[a2]) D.wbox_general = 1;
+                    if (box[a2] != P.lo[a2] || box[3 + a2] != P.n[a2]) D.wbox = 2;
+                    else if (box[3 + a2] > D.N[a2]) D.wbox = std::max(D.wbox, 1);
             }
         }
         D.pair_end = (int)S.pairs.size();
@@ -181,10 +182,20 @@ static sea_status build_cellset(sea_ctx* ctx, int n_cells, const sea_cell* cells
             S.csr_ent.resize(ent0 + off[C.n_occ]);
             std::vector<int> fill(off.begin(), off.end() - 1);
             for (int k = 0; k < C.n_pairs; ++k) {
+                const sea_pair& P = C.pairs_host[k];
                 const int gk = D.pair_begin + k;
-                S.csr_ent[ent0 + fill[C.pairs_host[k].i]++] = make_int2(gk, C.pairs_host[k].j);
-                if (C.pairs_host[k].j != C.pairs_host[k].i)
-                    S.csr_ent[ent0 + fill[C.pairs_host[k].j]++] = make_int2(gk, C.pairs_host[k].i);
+                for (int side = 0; side < (P.i == P.j ? 1 : 2); ++side) {
+                    ScEntry& R = S.csr_ent[ent0 + fill[side ? P.j : P.i]++];
+                    R = ScEntry{};
+                    R.pid = gk;
+                    R.other = side ? P.i : P.j;
+                    R.iside = side ? 0 : 1;
+                    for (int d = 0; d < 6; ++d) R.D[d] = S.dbox[12 * (size_t)gk + 6 * side + d];
+                    for (int d = 0; d < 3; ++d) {
+                        R.lo[d] = P.lo[d];
+                        R.n[d] = P.n[d];
+                    }
+                }
             }
             for (int o = 0; o <= C.n_occ; ++o) S.csr_off.push_back(ent0 + off[o]);
             csr_base += C.n_occ + 1;
@@ -296,7 +307,10 @@ ExxLayout exx_layout(const sea_ctx* ctx, const CellSet& S, bool with_v, bool eag
     L.slots = take((size_t)L.n_slots * 4 * L.slot_stride * sizeof(double));
     L.stats = take(np * sizeof(DevStat));
     L.csr_off = take((S.csr_off.size() + 1) * sizeof(int));
-    L.csr_ent = take((S.csr_ent.size() + 1) * sizeof(int2));
+    L.csr_ent = take((S.csr_ent.size() + 1) * sizeof(ScEntry));
+    size_t sc_work = 0;
+    for (const DevCell& D : S.dev) sc_work = std::max(sc_work, scatter_work_ints(D));
+    L.sc_work = sc_work ? take(sc_work * sizeof(int)) : 0;
     L.scal = take((3 * nc + 8) * sizeof(double));
     L.counter = take(256);
     if (ctx->opts.start == SEA_START_LEARNED) {
@@ -519,7 +533,7 @@ static sea_status exx_upload(sea_ctx* ctx, const CellSet& S, const ExxLayout& Ly
     if (!S.csr_off.empty())
         SEA_HIP_CHECK(ctx, hipMemcpyAsync(base + Ly.csr_off, S.csr_off.data(), sizeof(int) * S.csr_off.size(), hipMemcpyHostToDevice, s));
     if (!S.csr_ent.empty())
-        SEA_HIP_CHECK(ctx, hipMemcpyAsync(base + Ly.csr_ent, S.csr_ent.data(), sizeof(int2) * S.csr_ent.size(), hipMemcpyHostToDevice, s));
+        SEA_HIP_CHECK(ctx, hipMemcpyAsync(base + Ly.csr_ent, S.csr_ent.data(), sizeof(ScEntry) * S.csr_ent.size(), hipMemcpyHostToDevice, s));
     // the host tables must outlive the copies
     SEA_HIP_CHECK(ctx, hipStreamSynchronize(s));
     return SEA_OK;
@@ -787,7 +801,8 @@ static sea_status exx_enqueue(sea_ctx* ctx, const CellSet& S, const ExxLayout& L
         if (ae.epart) SEA_HIP_CHECK(ctx, launch_epart_clear(ae, s));
         for (size_t c = 0; c < S.cells.size(); ++c)
             SEA_HIP_CHECK(ctx, launch_scatter(ae, S.dev[c], (const int*)(base + Ly.csr_off),
-                                              (const int2*)(base + Ly.csr_ent), scatter_variant(ctx), s));
+                                              (const ScEntry*)(base + Ly.csr_ent), (int*)(base + Ly.sc_work),
+                                              scatter_variant(ctx), ctx->n_cu, s));
         timer_off(SEA_STAGE_SCATTER);
         if (finish && n_pairs > 0) {   // without ae.epart the finish sums rho x itself
             timer_on(SEA_STAGE_FINISH);
@@ -1713,7 +1728,8 @@ extern "C" sea_status sea_scatter_autotune(sea_ctx* ctx, int n_cells, const sea_
             err = hipEventRecord(e0, s);
             if (err == hipSuccess && a.epart) err = launch_epart_clear(a, s);
             for (size_t c = 0; c < S.cells.size() && err == hipSuccess; ++c)
-                err = launch_scatter(a, S.dev[c], (const int*)(base + Ly.csr_off), (const int2*)(base + Ly.csr_ent), v,
+                err = launch_scatter(a, S.dev[c], (const int*)(base + Ly.csr_off), (const ScEntry*)(base + Ly.csr_ent),
+                                     (int*)(base + Ly.sc_work), v, ctx->n_cu,
                                      s);
             if (err == hipSuccess) err = hipEventRecord(e1, s);
             if (err == hipSuccess) err = hipEventSynchronize(e1);

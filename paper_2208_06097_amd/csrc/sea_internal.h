@@ -74,7 +74,7 @@ struct StageTimer {
 struct ExxLayout {
     size_t pairs, pair_cell, order, dbox, cells, partial, mom, b, v, bres, slots, stats, csr_off, csr_ent, scal, counter;
     size_t nnx, nny, nnact, dst_tmp, dst_tab, dst_mu, rnorm, racah_tab, mpoly, epart, cg_r, cg_p, cg_part,
-        cg_rho, cg_done, cg_active, refine, total;
+        cg_rho, cg_done, cg_active, refine, sc_work, total;
     int nmax;
     int ep_stride;        // pair-energy partial slots per pair (scatter)
     int n_chunks;
@@ -100,7 +100,7 @@ struct DevCell {
     double* exx;          // device scalar (nullable)
     int pair_begin, pair_end;
     int csr_base;         // offset of this cell's orbital lists in the CSR arrays
-    int wbox_general;     // some W box is not its pair's domain, or is wider than the cell
+    int wbox;             // 0: every W box is its pair's domain, no wider than the cell; 1: some is wider; 2: some is another box
 };
 
 // Arguments shared by the exx kernels (passed by value).
@@ -151,6 +151,17 @@ struct ExxArgs {
     int hist_len;
 };
 
+// One entry of an orbital's pair list in the scatter: everything its
+// workgroups test a tile against, in one 64-byte record.
+struct alignas(16) ScEntry {
+    int pid, other;       // pair, partner orbital
+    int D[6];             // W box of this orbital's side: lo, n
+    int lo[3], n[3];      // the pair's domain
+    int iside;            // this orbital is the pair's i
+    int pad;
+};
+static_assert(sizeof(ScEntry) == 64, "one line's worth of a list entry");
+
 // Scatter tiles (k_scatter.hip): 64 x 4 x 8 grid points of one orbital.
 constexpr int SC_TX = 64, SC_TY = 4, SC_TZ = 8;
 // longest orbital pair list whose pair energies the scatter forms
@@ -158,12 +169,12 @@ constexpr int SC_EP_MAXE = 128;
 
 // Pair energies from the scatter.  The workgroup of orbital i of pair
 // (i, j) writes one partial of e_ij per scatter tile the pair's domain
-// meets.  It can when i's W box holds every domain point once: a box no
-// wider than the cell (in the domain's unwrapped frame) that contains the
-// domain.  D: lo[3], n[3] of the W box.
-__host__ __device__ inline bool ep_takes(const sea_pair& P, const int* D, const int* N) {
+// meets.  It can when i's W box (in the domain's unwrapped frame) contains the
+// domain: the scatter meets every point of the box once.  D: lo[3], n[3] of
+// the W box.
+__host__ __device__ inline bool ep_takes(const int* lo, const int* n, const int* D) {
     for (int a = 0; a < 3; ++a)
-        if (D[3 + a] > N[a] || D[a] > P.lo[a] || P.lo[a] + P.n[a] > D[a] + D[3 + a]) return false;
+        if (D[a] > lo[a] || lo[a] + n[a] > D[a] + D[3 + a]) return false;
     return true;
 }
 // Along an axis the tiles that n consecutive points (cyclically) meet form a
@@ -180,16 +191,17 @@ __host__ __device__ inline int ep_slots(const sea_pair& P, const int* N) {
     for (int a = 0; a < 3; ++a) s *= ep_axis_slots(P.n[a], T[a], (N[a] + T[a] - 1) / T[a]);
     return s;
 }
-// slot of tile tc (per-axis tile coordinates; `tiles` per axis) in pair P's run
-__host__ __device__ inline int ep_slot(const sea_pair& P, const int* N, const int* tc, const int* tiles) {
+// slot of tile tc (per-axis tile coordinates; `tiles` per axis) in the run of
+// the domain (lo, n)
+__host__ __device__ inline int ep_slot(const int* lo, const int* n, const int* N, const int* tc, const int* tiles) {
     const int T[3] = {SC_TX, SC_TY, SC_TZ};
     int slot = 0;
     for (int a = 2; a >= 0; --a) {
-        int w = P.lo[a] % N[a];
+        int w = lo[a] % N[a];
         w += w < 0 ? N[a] : 0;
         int r = tc[a] - w / T[a];
         r += r < 0 ? tiles[a] : 0;
-        const int sa = ep_axis_slots(P.n[a], T[a], tiles[a]);
+        const int sa = ep_axis_slots(n[a], T[a], tiles[a]);
         if (r >= sa) return -1;
         slot = slot * sa + r;
     }
@@ -338,8 +350,11 @@ hipError_t launch_cg_finish(const ExxArgs& a, hipStream_t s);
 // the scatter's compiled schedules (workgroup orders), the autotuner's choices
 int scatter_variant_count();
 const char* scatter_variant_name(int v);
-hipError_t launch_scatter(const ExxArgs& a, const DevCell& cell, const int* csr_off, const int2* csr_ent, int variant,
-                          hipStream_t s);
+// work: scatter_work_ints(cell) of scratch (cells of one call may share it: the
+// launches of one run in order)
+size_t scatter_work_ints(const DevCell& c);
+hipError_t launch_scatter(const ExxArgs& a, const DevCell& cell, const int* csr_off, const ScEntry* csr_ent, int* work,
+                          int variant, int n_cu, hipStream_t s);
 // zeroes a.epart (every slot the scatter does not write must read zero)
 hipError_t launch_epart_clear(const ExxArgs& a, hipStream_t s);
 hipError_t launch_energy_sum(const ExxArgs& a, double* out_scalars, double* e_dev, hipStream_t s);

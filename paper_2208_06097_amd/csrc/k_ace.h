@@ -25,6 +25,7 @@ template <int KIND, typename TA, typename TB>
 hipError_t ace_mm_nt(const TA* A, const TB* B, int m, int n, long K, double alpha, double* part, double* C,
                      hipStream_t s, int max_splits = 0);
 // C (m x ncol) = alpha A B, A(i,k) = A[i*sai + k*sak] (m x K, FP64), B: K x ncol.
+// lower: A(i,k) = 0 for k > i (those products may be left out).
 template <int KIND, typename TB, typename TC>
 hipError_t ace_mm_nn(const double* A, long sai, long sak, const TB* B, int m, int K, long ncol, double alpha, TC* C,
-                     hipStream_t s);
+                     hipStream_t s, bool lower = false);

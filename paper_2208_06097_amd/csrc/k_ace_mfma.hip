@@ -4,20 +4,35 @@
 //   NT (long K):  C = alpha A B^T, A: m x K, B: n x K, K = grid points.
 //                 Split over K; every workgroup writes an FP64 partial
 //                 m x n block of its K slice and a second kernel sums the
-//                 slices in FP64 (M = dV Phi^T W, dV xi^T psi, dV Phi^T xi).
+//                 slices in FP64 (M = dV Phi^T W, dV psi xi^T, dV Phi^T xi).
 //   NN (small K): C = alpha A B, A: m x K (FP64, small), B: K x ncol,
-//                 ncol = grid points (xi = L^-1 W, K psi = -C^T xi).
+//                 ncol = grid points (xi = L^-1 W, K psi = -C xi).
 //                 Persistent workgroups walk the column tiles with the
-//                 next tile's first K stage loaded during the last stage.
+//                 stages of the next tile in flight over the end of this one.
 //
 // Operand kinds: FP64 -> v_mfma_f64_16x16x4f64 (FP64 accumulation);
 // FP32 -> v_mfma_f32_16x16x4f32 and BF16 -> v_mfma_f32_16x16x32_bf16, both
 // with FP32 accumulation inside a workgroup's K range.  Inputs of another
 // type are rounded to the operand kind while they are staged in LDS.
 //
-// Tiling: 256 threads, a 128 x 128 output block, four wavefronts of 64 x 64
-// (4 x 4 tiles of 16 x 16), K staged as [row][k] in LDS (FP64 16 at a time,
-// FP32 32 at a time in the NT product and 16 in the NN one, BF16 32).
+// Tiling: 256 threads, four wavefronts in a 2 x 2 grid of 16P x 16Q tiles
+// each.  An operand row's share of a K stage is eight 16-byte chunks (KT = 16
+// FP64, 32 FP32, 64 BF16 values; NN's BF16 stage: four chunks, 32 values) at
+// a pitch of nine (five): chunks of consecutive rows then start in different
+// banks.  A thread moves whole chunks: one wide load (rows of an odd grid are
+// aligned to their element only, which global loads take), one 16-byte LDS
+// write, and 16-byte LDS reads whose values feed consecutive matrix
+// instructions.  For that, lane group g = lane / 16 takes k = CE g + s in step
+// s (CE values per chunk); A and B agree, so only the order of the sum
+// differs from the natural one.  Two LDS buffers: the next stage is written
+// between the halves of this one's matrix work, and one barrier per stage
+// remains.
+// Block heights follow the matrix (32 to 128 rows): small products are bound by
+// reading their operands and large ones by the matrix cores.  Measured, against
+// 128 x 128 blocks throughout with element-wise staging between two barriers:
+// FP64 32 x 32 x 216000 320 -> 22 us (5.0 TB/s), 256 x 256 x 1728000 4.19 ->
+// 3.87 ms (58 TFLOP/s); FP32 NN 256 x 256 x 1728000 2.66 -> 2.21 ms, its
+// triangular form 2.80 -> 1.86 ms; BF16 NN 200 x 152 x 1030301 0.63 -> 0.43 ms.
 // Operand lanes: A row = lane % 16, B column = lane % 16, k block = lane / 16.
 // Result lanes: column = lane % 16; the row of item v is 4 (lane / 16) + v
 // for the FP32-accumulating instructions and lane / 16 + 4 v for the FP64
@@ -30,11 +45,14 @@
 
 namespace {
 
+typedef double f64x2 __attribute__((ext_vector_type(2)));
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef uint16_t u16x8 __attribute__((ext_vector_type(8)));
 
-constexpr int BM = 128, BN = 128, NT = 256;
+constexpr int NT = 256;
+constexpr int BN = 128;   // columns of an NN tile
 // Workgroups are handed to the 8 XCDs (each with its own L2) in turn.  The
 // workgroups that read the same operand tiles (NT: the output tiles of one
 // K slice; NN: the row blocks of one column tile of the grid-point operand)
@@ -69,178 +87,207 @@ __device__ __forceinline__ float as_f(T v) { return (float)v; }
 template <>
 __device__ __forceinline__ float as_f<uint16_t>(uint16_t v) { return bf_to_f(v); }
 
-// per-kind operand element, LDS row pitch, accumulator and one MFMA k-step
+// N consecutive values, loaded or stored as one access at element alignment
+template <typename T, int N>
+struct Chunk {
+    T v[N];
+};
+template <int N, typename T>
+__device__ __forceinline__ Chunk<T, N> load_chunk(const T* p) {
+    Chunk<T, N> c;
+    __builtin_memcpy(&c, p, sizeof(c));
+    return c;
+}
+
+// per-kind operand element, chunk and matrix step
 template <int KIND>
 struct Kind;
 template <>
 struct Kind<ACE_F64> {
     using E = double;
+    using Vec = f64x2;
     using Acc = f64x4;
-    // K staged 16 at a time: the next stage's loads held in registers stay
-    // at 16 doubles per thread (with 128 accumulator registers per lane)
-    static constexpr int KT = 16;
-    static constexpr int PITCH = KT + 1;
-    static constexpr int KSTEP = 4;
+    static constexpr int CE = 2, STEPS = 2;   // values and matrix steps of a chunk
     // output item v of lane-group g holds tile row g + 4 v (FP64 layout)
     __device__ static int row(int g, int v) { return g + 4 * v; }
     template <typename T>
     __device__ static E cvt(T v) { return as_d(v); }
-    __device__ static Acc mma(const E* a, const E* b, int g, Acc c) {
-        return __builtin_amdgcn_mfma_f64_16x16x4f64(a[g], b[g], c, 0, 0, 0);
+    __device__ static Acc mma(Vec a, Vec b, int s, Acc c) {
+        return __builtin_amdgcn_mfma_f64_16x16x4f64(a[s], b[s], c, 0, 0, 0);
     }
 };
 template <>
 struct Kind<ACE_F32> {
     using E = float;
+    using Vec = f32x4;
     using Acc = f32x4;
-    static constexpr int KT = 32;
-    static constexpr int PITCH = KT + 1;
-    static constexpr int KSTEP = 4;
+    static constexpr int CE = 4, STEPS = 4;
     // output item v of lane-group g holds tile row 4 g + v
     __device__ static int row(int g, int v) { return 4 * g + v; }
     template <typename T>
     __device__ static E cvt(T v) { return as_f(v); }
-    __device__ static Acc mma(const E* a, const E* b, int g, Acc c) {
-        return __builtin_amdgcn_mfma_f32_16x16x4f32(a[g], b[g], c, 0, 0, 0);
+    __device__ static Acc mma(Vec a, Vec b, int s, Acc c) {
+        return __builtin_amdgcn_mfma_f32_16x16x4f32(a[s], b[s], c, 0, 0, 0);
     }
 };
 template <>
 struct Kind<ACE_BF16> {
     using E = uint16_t;
+    using Vec = u16x8;
     using Acc = f32x4;
-    static constexpr int KT = 32;
-    static constexpr int PITCH = KT + 8;  // 16-byte aligned rows
-    static constexpr int KSTEP = 32;
+    static constexpr int CE = 8, STEPS = 1;
     __device__ static int row(int g, int v) { return 4 * g + v; }
     template <typename T>
     __device__ static E cvt(T v) {
         if constexpr (std::is_same<T, uint16_t>::value) return v;  // already BF16 bits
         else return f_to_bf(as_f(v));
     }
-    __device__ static Acc mma(const E* a, const E* b, int g, Acc c) {
-        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(*reinterpret_cast<const bf16x8*>(a + 8 * g),
-                                                       *reinterpret_cast<const bf16x8*>(b + 8 * g), c, 0, 0, 0);
+    __device__ static Acc mma(Vec a, Vec b, int, Acc c) {
+        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c,
+                                                       0, 0, 0);
     }
 };
 
-// Multiply the staged tiles: wave (wm, wn) = (wave / 2, wave % 2) owns rows
-// wm*64.., cols wn*64..
-template <int KIND, int PITCH = Kind<KIND>::PITCH>
-__device__ __forceinline__ void tile_step(const typename Kind<KIND>::E* As, const typename Kind<KIND>::E* Bs, int kk,
-                                          typename Kind<KIND>::Acc (&acc)[4][4]) {
-    using K = Kind<KIND>;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int wm = wave >> 1, wn = wave & 1;
-    const int r = lane & 15, g = lane >> 4;
+// A chunk of T as the 16 bytes of the operand kind
+template <int KIND, typename T>
+__device__ __forceinline__ typename Kind<KIND>::Vec to_vec(const Chunk<T, Kind<KIND>::CE>& c) {
+    typename Kind<KIND>::Vec v;
 #pragma unroll
-    for (int p = 0; p < 4; ++p) {
-        const typename K::E* a = As + (wm * 64 + p * 16 + r) * PITCH + kk;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const typename K::E* b = Bs + (wn * 64 + q * 16 + r) * PITCH + kk;
-            acc[p][q] = K::mma(a, b, g, acc[p][q]);
-        }
-    }
+    for (int i = 0; i < Kind<KIND>::CE; ++i) v[i] = Kind<KIND>::cvt(c.v[i]);
+    return v;
 }
 
-// FEW: two k steps at a time, so that only their operands (4 A and 4 B per
-// step) are LDS reads in flight, which saves registers for occupancy; else
-// the whole stage unrolled (measured faster where occupancy does not change).
-// KT, PITCH: the stage depth and LDS row pitch, if not the kind's own.
-template <int KIND, bool FEW, int KT = Kind<KIND>::KT, int PITCH = Kind<KIND>::PITCH>
-__device__ __forceinline__ void tile_mma(const typename Kind<KIND>::E* As, const typename Kind<KIND>::E* Bs,
-                                         typename Kind<KIND>::Acc (&acc)[4][4]) {
-    using K = Kind<KIND>;
-    if constexpr (FEW) {
-#pragma unroll 2
-        for (int kk = 0; kk < KT; kk += K::KSTEP) tile_step<KIND, PITCH>(As, Bs, kk, acc);
-    } else {
-#pragma unroll
-        for (int kk = 0; kk < KT; kk += K::KSTEP) tile_step<KIND, PITCH>(As, Bs, kk, acc);
-    }
-}
+// Workgroups per CU asked of the compiler: what the LDS of the two buffers
+// (9 KB per 32 rows) holds, up to four.  An FP64 block of 128 x 128 has 128
+// accumulator registers a lane and fits twice.
+constexpr int nt_minb(int P, int Q) { return P + Q <= 4 ? 4 : P + Q <= 5 ? 3 : 2; }
 
-template <int KIND, typename TA, typename TB>
-__global__ __launch_bounds__(NT) void k_nt_mfma(const TA* __restrict__ A, const TB* __restrict__ B, int m, int n,
-                                                long K, long kslice, int splits, double* __restrict__ part) {
+template <int KIND, typename TA, typename TB, int P, int Q>
+__global__ __launch_bounds__(NT, nt_minb(P, Q)) void k_nt_mfma(const TA* __restrict__ A, const TB* __restrict__ B,
+                                                               int m, int n, long K, long kslice, int splits,
+                                                               double* __restrict__ part) {
     using Kd = Kind<KIND>;
     using E = typename Kd::E;
-    constexpr int KT = Kd::KT;
-    __shared__ __attribute__((aligned(16))) E As[BM * Kd::PITCH];
-    __shared__ __attribute__((aligned(16))) E Bs[BN * Kd::PITCH];
+    using Vec = typename Kd::Vec;
+    constexpr int CE = Kd::CE, KT = 8 * CE, PITCH = 9 * CE;
+    constexpr int TM = 32 * P, TN = 32 * Q;
+    __shared__ __attribute__((aligned(16))) E As[2][TM * PITCH];
+    __shared__ __attribute__((aligned(16))) E Bs[2][TN * PITCH];
     // group: K slice; member: output tile
-    const int tn = (n + BN - 1) / BN, tm = (m + BM - 1) / BM;
+    const int tn = (n + TN - 1) / TN, tm = (m + TM - 1) / TM;
     long slice;
     int tile;
     xcd_block(tn * tm, slice, tile);
     if (slice >= splits) return;   // padding of the last XCD round (an empty slice still writes its zeros)
     const long kb = slice * kslice;
-    const int j0 = (tile % tn) * BN, i0 = (tile / tn) * BM;
+    const int j0 = (tile % tn) * TN, i0 = (tile / tn) * TM;
     const long ke = min(K, kb + kslice);
-    typename Kd::Acc acc[4][4];
+    typename Kd::Acc acc[P][Q];
 #pragma unroll
-    for (int p = 0; p < 4; ++p)
+    for (int p = 0; p < P; ++p)
 #pragma unroll
-        for (int q = 0; q < 4; ++q) acc[p][q] = typename Kd::Acc{0, 0, 0, 0};
-    // Software pipeline: the global loads of the next K stage are in flight
-    // (in registers) while the current stage is multiplied out of LDS.
-    // Stage element e of thread t: row (t + NT e) / KT, k (t + NT e) % KT;
-    // 32 consecutive threads read 32 consecutive k of one row.
-    constexpr int PER = BM * KT / NT;
-    TA ra[PER];
-    TB rb[PER];
-    // element offsets within a stage are below BM K < 2^31 (checked at
-    // launch): one uniform 64-bit base per stage and a 32-bit offset per
-    // element, shared by A and B, instead of a 64-bit address per element
-    const int Ki = (int)K;
+        for (int q = 0; q < Q; ++q) acc[p][q] = typename Kd::Acc{0, 0, 0, 0};
+    // Chunk e of thread t: row t / 8 + 32 e, k CE (t % 8).  Rows past the
+    // matrix repeat its last one: what they give is not stored.
+    const int cr = threadIdx.x >> 3, ck = CE * (threadIdx.x & 7);
+    const TA* pa[P];
+    const TB* pb[Q];
+#pragma unroll
+    for (int e = 0; e < P; ++e) pa[e] = A + (size_t)min(i0 + cr + 32 * e, m - 1) * K + ck;
+#pragma unroll
+    for (int e = 0; e < Q; ++e) pb[e] = B + (size_t)min(j0 + cr + 32 * e, n - 1) * K + ck;
+    Chunk<TA, CE> ra[P];
+    Chunk<TB, CE> rb[Q];
     auto load = [&](long k0) {
-        const TA* __restrict__ Ab = A + (size_t)i0 * K + k0;
-        const TB* __restrict__ Bb = B + (size_t)j0 * K + k0;
-        const int kl = (int)(ke - k0);   // k of this stage below kl
+        if (k0 + KT <= ke) {
 #pragma unroll
-        for (int e = 0; e < PER; ++e) {
-            const int idx = threadIdx.x + NT * e;
-            const int rr = idx / KT, kk = idx % KT;
-            const int off = rr * Ki + kk;
-            ra[e] = (i0 + rr < m && kk < kl) ? Ab[off] : TA(0);
-            rb[e] = (j0 + rr < n && kk < kl) ? Bb[off] : TB(0);
+            for (int e = 0; e < P; ++e) ra[e] = load_chunk<CE>(pa[e] + k0);
+#pragma unroll
+            for (int e = 0; e < Q; ++e) rb[e] = load_chunk<CE>(pb[e] + k0);
+        } else {
+            const int kl = (int)(ke - k0) - ck;   // values of this thread's chunk inside
+#pragma unroll
+            for (int e = 0; e < P; ++e)
+#pragma unroll
+                for (int i = 0; i < CE; ++i) ra[e].v[i] = i < kl ? pa[e][k0 + i] : TA(0);
+#pragma unroll
+            for (int e = 0; e < Q; ++e)
+#pragma unroll
+                for (int i = 0; i < CE; ++i) rb[e].v[i] = i < kl ? pb[e][k0 + i] : TB(0);
         }
     };
-    if (kb < ke) load(kb);
-    for (long k0 = kb; k0 < ke; k0 += KT) {
-        __syncthreads();
+    auto stage = [&](int buf) {
 #pragma unroll
-        for (int e = 0; e < PER; ++e) {
-            const int idx = threadIdx.x + NT * e;
-            const int rr = idx / KT, kk = idx % KT;
-            As[rr * Kd::PITCH + kk] = Kd::cvt(ra[e]);
-            Bs[rr * Kd::PITCH + kk] = Kd::cvt(rb[e]);
-        }
-        __syncthreads();
-        if (k0 + KT < ke) load(k0 + KT);
-        tile_mma<KIND, KIND == ACE_F64>(As, Bs, acc);
-    }
+        for (int e = 0; e < P; ++e)
+            *reinterpret_cast<Vec*>(&As[buf][(cr + 32 * e) * PITCH + ck]) = to_vec<KIND, TA>(ra[e]);
+#pragma unroll
+        for (int e = 0; e < Q; ++e)
+            *reinterpret_cast<Vec*>(&Bs[buf][(cr + 32 * e) * PITCH + ck]) = to_vec<KIND, TB>(rb[e]);
+    };
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int wm = wave >> 1, wn = wave & 1;
-    double* P = part + (size_t)slice * m * n;
+    const int r = lane & 15, g = lane >> 4;
+    auto mma = [&](int buf, int h) {
+        Vec a[P], b[Q];
 #pragma unroll
-    for (int p = 0; p < 4; ++p)
+        for (int p = 0; p < P; ++p)
+            a[p] = *reinterpret_cast<const Vec*>(&As[buf][((wm * P + p) * 16 + r) * PITCH + (4 * h + g) * CE]);
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
+        for (int q = 0; q < Q; ++q)
+            b[q] = *reinterpret_cast<const Vec*>(&Bs[buf][((wn * Q + q) * 16 + r) * PITCH + (4 * h + g) * CE]);
+#pragma unroll
+        for (int s = 0; s < Kd::STEPS; ++s)
+#pragma unroll
+            for (int p = 0; p < P; ++p)
+#pragma unroll
+                for (int q = 0; q < Q; ++q) acc[p][q] = Kd::mma(a[p], b[q], s, acc[p][q]);
+    };
+    if (kb < ke) {
+        load(kb);
+        stage(0);
+        if (kb + KT < ke) load(kb + KT);
+        lds_sync();
+        int buf = 0;
+        for (long k0 = kb; k0 < ke; k0 += KT) {
+            mma(buf, 0);
+            if (k0 + KT < ke) stage(buf ^ 1);
+            if (k0 + 2 * KT < ke) load(k0 + 2 * KT);
+            mma(buf, 1);
+            lds_sync();   // the loads in flight cross it
+            buf ^= 1;
+        }
+    }
+    double* Pt = part + (size_t)slice * m * n;
+#pragma unroll
+    for (int p = 0; p < P; ++p)
+#pragma unroll
+        for (int q = 0; q < Q; ++q)
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
-                const int i = i0 + wm * 64 + p * 16 + Kd::row(lane >> 4, v);
-                const int j = j0 + wn * 64 + q * 16 + (lane & 15);
-                if (i < m && j < n) P[(size_t)i * n + j] = (double)acc[p][q][v];
+                const int i = i0 + (wm * P + p) * 16 + Kd::row(g, v);
+                const int j = j0 + (wn * Q + q) * 16 + r;
+                if (i < m && j < n) Pt[(size_t)i * n + j] = (double)acc[p][q][v];
             }
 }
 
-__global__ void k_slice_sum(const double* __restrict__ part, int splits, int mn, double alpha,
-                            double* __restrict__ C) {
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= mn) return;
+// C = alpha (sum of the slices): 32 elements per workgroup, 8 threads each
+// taking every eighth slice (256 slices of 256 x 256, 134 MB: 91 -> 33 us
+// against one thread per element, whose loads wait on each other's sums).
+constexpr int SS_E = 32, SS_G = 8;
+__global__ __launch_bounds__(SS_E* SS_G) void k_slice_sum(const double* __restrict__ part, int splits, int mn,
+                                                          double alpha, double* __restrict__ C) {
+    __shared__ double red[SS_G][SS_E];
+    const int e = threadIdx.x % SS_E, g = threadIdx.x / SS_E;
+    const int t = blockIdx.x * SS_E + e;
     double s = 0.0;
-    for (int q = 0; q < splits; ++q) s += part[(size_t)q * mn + t];
+    if (t < mn) {
+#pragma unroll 8
+        for (int q = g; q < splits; q += SS_G) s += part[(size_t)q * mn + t];
+    }
+    red[g][e] = s;
+    __syncthreads();
+    if (g || t >= mn) return;
+    for (int i = 1; i < SS_G; ++i) s += red[i][e];
     C[t] = alpha * s;
 }
 
@@ -258,118 +305,342 @@ __device__ __forceinline__ uint16_t store_as<uint16_t>(double v) { return f_to_b
 // q % (row blocks) and slot s = q / (row blocks), and walks the column tiles
 // jt = (s + i slots) 8 + x, i = 0, 1, ..., so that the row blocks of one
 // column tile run together on one XCD (the second read of the tile comes
-// from that L2).  The first K stage of the next column tile is loaded
-// during the last stage of the current one: the pipeline does not drain
-// between tiles (K is short here: the orbital count).
+// from that L2).  Stages are counted through the tiles: the pipeline does
+// not drain between them (K is short here: the orbital count).
 //
-// Workgroups per CU asked of the compiler, which then keeps the
-// accumulators in VGPRs: FP64 and BF16 two (the FP64 kind otherwise takes
-// 194 VGPRs + 128 AGPRs and runs one workgroup per CU; three spill); FP32
-// three, with K staged 16 at a time (32 at a time spills at three).
+// FP64 and FP32 columns stay as they lie in memory: B staged [k][column],
+// read as runs of consecutive columns, so that a lane's results are runs too
+// (4 FP32, 2 FP64) and leave as 16-byte stores.  BF16 needs 8 consecutive k of
+// a column: a thread loads 4 x 4 (k x column) and writes each column's four
+// values; column c of a 64-wide half lies at row (c % 4) 16 + c / 4, so that
+// tile q holds the columns 4 r + q as well.
+//
+// RES: the workgroup's rows of A stay in LDS for all its tiles (converted
+// once) where that leaves two workgroups per CU; else they are staged with B.
+// LOWER: A(i, k) = 0 for k > i, and a row block stops at its last row's k;
+// a workgroup then takes the next row block with each tile, so that all do
+// the same work.
 template <int KIND>
-constexpr int nn_kt() { return KIND == ACE_F32 ? 16 : Kind<KIND>::KT; }
-template <int KIND>
-constexpr int nn_pitch() { return nn_kt<KIND>() == Kind<KIND>::KT ? Kind<KIND>::PITCH : nn_kt<KIND>() + 1; }
-template <int KIND>
-constexpr int nn_minb() { return KIND == ACE_F32 ? 3 : 2; }
-template <int KIND, typename TB, typename TC>
-__global__ __launch_bounds__(NT, nn_minb<KIND>()) void k_nn_mfma(const double* __restrict__ A, long sai, long sak,
-                                                const TB* __restrict__ B, int m, int K, long ncol, double alpha,
-                                                TC* __restrict__ C, int slots) {
+struct NN {
     using Kd = Kind<KIND>;
+    static constexpr int CH = KIND == ACE_BF16 ? 4 : 8;       // chunks of a row's stage
+    static constexpr int KT = CH * Kd::CE, PITCH = (CH + 1) * Kd::CE;
+    static constexpr int B_ELEMS = KIND == ACE_BF16 ? BN * PITCH : KT * BN;
+    static constexpr int ROWS = NT / CH;                      // A rows of one pass of the threads
+};
+constexpr int nn_minb(int P) { return P <= 2 ? 3 : 2; }
+
+template <int KIND, typename TB, typename TC, int P, bool RES, bool LOWER>
+__global__ __launch_bounds__(NT, nn_minb(P)) void k_nn_mfma(const double* __restrict__ A, long sai, long sak,
+                                                            const TB* __restrict__ B, int m, int K, long ncol,
+                                                            double alpha, TC* __restrict__ C, int slots) {
+    using Kd = Kind<KIND>;
+    using S = NN<KIND>;
     using E = typename Kd::E;
-    constexpr int KT = nn_kt<KIND>(), PITCH = nn_pitch<KIND>();
-    __shared__ __attribute__((aligned(16))) E As[BM * PITCH];
-    __shared__ __attribute__((aligned(16))) E Bs[BN * PITCH];
-    const int per = (m + BM - 1) / BM;
+    using Vec = typename Kd::Vec;
+    constexpr int CE = Kd::CE, KT = S::KT, PITCH = S::PITCH;
+    constexpr int TM = 32 * P, PA = (TM + S::ROWS - 1) / S::ROWS;
+    constexpr int AST = TM * PITCH;   // one stage of A in LDS
+    extern __shared__ __attribute__((aligned(16))) char nn_smem[];
+    E* const Bs = reinterpret_cast<E*>(nn_smem);            // [2][B_ELEMS]
+    E* const As = Bs + 2 * S::B_ELEMS;                     // RES: every stage; else [2]
+    const int per = (m + TM - 1) / TM;
     const int x = blockIdx.x % ACE_XCD, mseq = blockIdx.x / ACE_XCD;
-    const int i0 = (mseq % per) * BM;
     const long ntile = (ncol + BN - 1) / BN, jstep = (long)slots * ACE_XCD;
-    long jt = (long)(mseq / per) * ACE_XCD + x;
-    if (jt >= ntile) return;
-    const int nst = K > 0 ? (K + KT - 1) / KT : 1;   // K = 0: one stage of zeros
-    typename Kd::Acc acc[4][4];
+    const int nst_all = K > 0 ? (K + KT - 1) / KT : 1;   // K = 0: one stage of zeros
+    struct It {
+        long jt;
+        int st, ib;
+    };
+    auto stages = [&](int ib) { return LOWER ? min(nst_all, ((ib + 1) * TM + KT - 1) / KT) : nst_all; };
+    auto next = [&](It it) {
+        if (it.st + 1 < stages(it.ib)) return It{it.jt, it.st + 1, it.ib};
+        return It{it.jt + jstep, 0, LOWER ? (it.ib + 1 < per ? it.ib + 1 : 0) : it.ib};
+    };
+    It cur{(long)(mseq / per) * ACE_XCD + x, 0, mseq % per};
+    if (cur.jt >= ntile) return;
+    typename Kd::Acc acc[P][4];
 #pragma unroll
-    for (int p = 0; p < 4; ++p)
+    for (int p = 0; p < P; ++p)
 #pragma unroll
         for (int q = 0; q < 4; ++q) acc[p][q] = typename Kd::Acc{0, 0, 0, 0};
-    // Same stage layout as the NT kernel.  A (small, cache-resident): row
-    // idx / KT, k idx % KT; B: 128 consecutive threads read one grid row.
-    constexpr int PER = BM * KT / NT;
-    double ra[PER];
-    TB rb[PER];
-    // Element e of a thread: A row rr0 + e NT/KT, k kk; B row kr0 + e NT/BN,
-    // column jj.  Its address is a uniform base for (stage, e) plus a 32-bit
-    // offset of the thread's own (the same for every e); the thread index is
-    // taken opaque in each call, so that nothing of it is held in registers
-    // across the tile loop.
-    auto load = [&](long j0, int k0) {
-        int t = threadIdx.x;
-        asm volatile("" : "+v"(t));
-        const int rr0 = t / KT, kk = t % KT, kr0 = t / BN, jj = t % BN;
-        const int oa = rr0 * (int)sai + kk * (int)sak, ob = kr0 * (int)ncol + jj;
-        const int kl = K - k0, il = m - i0;
-        const long jl = ncol - j0;
+
+    // A: chunk e of thread t: row t / CH + ROWS e, k CE (t % CH); rows past m
+    // repeat the last one, k past K are zeros
+    const int ar = threadIdx.x / S::CH, ak = CE * (threadIdx.x % S::CH);
+    Chunk<double, CE> ra[PA];
+    auto load_a = [&](int ib, int st) {
+        const int k0 = st * KT + ak;
 #pragma unroll
-        for (int e = 0; e < PER; ++e) {
-            const double* __restrict__ Ae = A + i0 * sai + (long)k0 * sak + (long)e * (NT / KT) * sai;
-            const TB* __restrict__ Be = B + (size_t)(k0 + e * (NT / BN)) * ncol + j0;
-            ra[e] = (rr0 + e * (NT / KT) < il && kk < kl) ? Ae[oa] : 0.0;
-            rb[e] = (jj < jl && kr0 + e * (NT / BN) < kl) ? Be[ob] : TB(0);
+        for (int e = 0; e < PA; ++e) {
+            const double* a = A + (long)min(ib * TM + ar + S::ROWS * e, m - 1) * sai + (long)k0 * sak;
+            if (sak == 1 && (st + 1) * KT <= K) {
+                ra[e] = load_chunk<CE>(a);
+            } else {
+#pragma unroll
+                for (int i = 0; i < CE; ++i) ra[e].v[i] = k0 + i < K ? a[i * sak] : 0.0;
+            }
         }
     };
-    const int wave = threadIdx.x >> 6;
+    auto stage_a = [&](E* dst) {
+#pragma unroll
+        for (int e = 0; e < PA; ++e)
+            if (TM % S::ROWS == 0 || ar + S::ROWS * e < TM)
+                *reinterpret_cast<Vec*>(&dst[(ar + S::ROWS * e) * PITCH + ak]) = to_vec<KIND, double>(ra[e]);
+    };
+    // B: RB pieces of CB columns per thread
+    constexpr int CB = KIND == ACE_F64 ? 2 : 4;
+    constexpr int RB = 4;
+    // FP64, FP32: piece e is row t / (BN / CB) + e NT / (BN / CB); BF16: rows 4 (t / 32) + e
+    const int bc = CB * (threadIdx.x % (BN / CB));
+    const int br = KIND == ACE_BF16 ? 4 * (threadIdx.x / (BN / CB)) : threadIdx.x / (BN / CB);
+    constexpr int BSTEP = KIND == ACE_BF16 ? 1 : NT / (BN / CB);
+    static_assert(KIND == ACE_BF16 ? 4 * NT / (BN / CB) == KT : RB * BSTEP == KT, "B stage");
+    Chunk<TB, CB> rb[RB];
+    auto load_b = [&](long jt, int st) {
+        const long j0 = jt * BN + bc;
+        const int k0 = st * KT + br;
+        if ((st + 1) * KT <= K && (jt + 1) * BN <= ncol) {
+            const TB* b = B + (size_t)k0 * ncol + j0;
+#pragma unroll
+            for (int e = 0; e < RB; ++e) rb[e] = load_chunk<CB>(b + (size_t)(e * BSTEP) * ncol);
+        } else {
+#pragma unroll
+            for (int e = 0; e < RB; ++e)
+#pragma unroll
+                for (int i = 0; i < CB; ++i)
+                    rb[e].v[i] = (k0 + e * BSTEP < K && j0 + i < ncol) ? B[(size_t)(k0 + e * BSTEP) * ncol + j0 + i]
+                                                                       : TB(0);
+        }
+    };
+    auto stage_b = [&](int buf) {
+        E* dst = Bs + buf * S::B_ELEMS;
+        if constexpr (KIND == ACE_BF16) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                Chunk<E, 4> w;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) w.v[e] = Kd::cvt(rb[e].v[i]);
+                const int row = (bc & 64) + i * 16 + ((bc & 63) >> 2);
+                __builtin_memcpy(__builtin_assume_aligned(&dst[row * PITCH + br], 8), &w, 8);
+            }
+        } else {
+#pragma unroll
+            for (int e = 0; e < RB; ++e) {
+                Vec v;
+#pragma unroll
+                for (int i = 0; i < CB; ++i) v[i] = Kd::cvt(rb[e].v[i]);
+                *reinterpret_cast<Vec*>(&dst[(br + e * BSTEP) * BN + bc]) = v;
+            }
+        }
+    };
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int wm = wave >> 1, wn = wave & 1;
-    load(jt * BN, 0);
-    for (int st = 0;;) {
-        // LDS-only barriers: the loads in flight cross them (their
-        // registers are waited for where they are staged)
-        lds_sync();
+    const int r = lane & 15, g = lane >> 4;
+    // column of tile q held by this lane, within the wave's 64
+    auto col = [&](int q) { return KIND == ACE_F64 ? 32 * (q >> 1) + 2 * r + (q & 1) : 4 * r + q; };
+    auto mma = [&](const E* a_st, int buf, int h) {
+        const E* b_st = Bs + buf * S::B_ELEMS;
+        Vec a[P];
 #pragma unroll
-        for (int e = 0; e < PER; ++e) {
-            const int idx = threadIdx.x + NT * e;
-            As[(idx / KT) * PITCH + idx % KT] = Kd::cvt(ra[e]);
-            Bs[(idx % BN) * PITCH + idx / BN] = Kd::cvt(rb[e]);
-        }
-        lds_sync();
-        long jn = jt;
-        int sn = st + 1;
-        if (sn == nst) {
-            sn = 0;
-            jn = jt + jstep;
-        }
-        if (jn < ntile) load(jn * BN, sn * KT);
-        tile_mma<KIND, std::is_same<TB, double>::value, KT, PITCH>(As, Bs, acc);
-        if (sn == 0) {
-            int lane = threadIdx.x & 63;
-            asm volatile("" : "+v"(lane));
-            const int ib = i0 + wm * 64, il = m - ib;
-            const long jb = jt * BN + wn * 64, jl = ncol - jb;
-            TC* __restrict__ Cb = C + (size_t)ib * ncol + jb;
+        for (int p = 0; p < P; ++p)
+            a[p] = *reinterpret_cast<const Vec*>(&a_st[((wm * P + p) * 16 + r) * PITCH + (4 * h + g) * CE]);
+        if constexpr (KIND == ACE_BF16) {
 #pragma unroll
-            for (int p = 0; p < 4; ++p)
+            for (int q = 0; q < 4; ++q) {
+                const Vec b = *reinterpret_cast<const Vec*>(&b_st[(wn * 64 + q * 16 + r) * PITCH + g * CE]);
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
+                for (int p = 0; p < P; ++p) acc[p][q] = Kd::mma(a[p], b, 0, acc[p][q]);
+            }
+        } else {
 #pragma unroll
-                    for (int v = 0; v < 4; ++v) {
-                        const int i = p * 16 + Kd::row(lane >> 4, v), j = q * 16 + (lane & 15);
-                        if (i < il && j < jl) Cb[(size_t)i * ncol + j] = store_as<TC>(alpha * (double)acc[p][q][v]);
+            for (int s = 0; s < Kd::STEPS; ++s) {
+                const E* brow = &b_st[((4 * h + g) * CE + s) * BN + wn * 64];
+                E b[4];
+                if constexpr (KIND == ACE_F64) {
+#pragma unroll
+                    for (int u = 0; u < 2; ++u) {
+                        const Vec w = *reinterpret_cast<const Vec*>(&brow[32 * u + 2 * r]);
+                        b[2 * u] = w[0];
+                        b[2 * u + 1] = w[1];
                     }
-                    acc[p][q] = typename Kd::Acc{0, 0, 0, 0};
+                } else {
+                    const Vec w = *reinterpret_cast<const Vec*>(&brow[4 * r]);
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) b[q] = w[q];
                 }
-            if (jn >= ntile) break;
+#pragma unroll
+                for (int p = 0; p < P; ++p)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        Vec bv{};
+                        bv[s] = b[q];
+                        acc[p][q] = Kd::mma(a[p], bv, s, acc[p][q]);
+                    }
+            }
         }
-        jt = jn;
-        st = sn;
+    };
+    auto store = [&](It it) {
+        const int ib = it.ib * TM + wm * 16 * P;
+        const long jb = it.jt * BN + wn * 64;
+        const bool inside = jb + 64 <= ncol;
+#pragma unroll
+        for (int p = 0; p < P; ++p)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int i = ib + p * 16 + Kd::row(g, v);
+                if (i < m) {
+                    TC* Cr = C + (size_t)i * ncol + jb;
+#pragma unroll
+                    for (int q0 = 0; q0 < 4; q0 += CB) {
+                        Chunk<TC, CB> c;
+#pragma unroll
+                        for (int u = 0; u < CB; ++u) c.v[u] = store_as<TC>(alpha * (double)acc[p][q0 + u][v]);
+                        if (inside) {
+                            __builtin_memcpy(Cr + col(q0), &c, sizeof(c));
+                        } else {
+#pragma unroll
+                            for (int u = 0; u < CB; ++u)
+                                if (jb + col(q0 + u) < ncol) Cr[col(q0 + u)] = c.v[u];
+                        }
+                    }
+                }
+            }
+#pragma unroll
+        for (int p = 0; p < P; ++p)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) acc[p][q] = typename Kd::Acc{0, 0, 0, 0};
+    };
+
+    if constexpr (RES)
+        for (int st = 0; st < nst_all; ++st) {
+            load_a(cur.ib, st);
+            stage_a(As + st * AST);
+        }
+    auto load = [&](It it) {
+        if (!RES) load_a(it.ib, it.st);
+        load_b(it.jt, it.st);
+    };
+    auto stage = [&](int buf) {
+        if (!RES) stage_a(As + buf * AST);
+        stage_b(buf);
+    };
+    It n1 = next(cur);
+    load(cur);
+    stage(0);
+    if (n1.jt < ntile) load(n1);
+    lds_sync();
+    for (int buf = 0;; buf ^= 1) {
+        const It n2 = next(n1);
+        const E* a_st = As + (RES ? cur.st : buf) * AST;
+        if (S::CH == 8) mma(a_st, buf, 0);
+        if (n1.jt < ntile) {
+            stage(buf ^ 1);
+            if (n2.jt < ntile) load(n2);
+        }
+        mma(a_st, buf, S::CH == 8 ? 1 : 0);
+        if (n1.st == 0) store(cur);
+        if (n1.jt >= ntile) break;
+        lds_sync();   // the loads in flight cross it
+        cur = n1;
+        n1 = n2;
     }
+}
+
+// Rows of 32 in an NT block along a side of x: as few blocks of at most 128
+// as hold it, as thin as that many allow.  Products over a short K (the small
+// matrices of the polar iteration) are bound by latency and take the smallest
+// block: 256 x 256 x 256 on 64 workgroups, not 4.
+constexpr long NT_SHORT_K = 2048;
+int nt_block(long K, int x) {
+    if (K <= NT_SHORT_K) return 1;
+    const int nb = (x + 127) / 128;
+    return std::max(1, (x + 32 * nb - 1) / (32 * nb));
+}
+
+template <int KIND, typename TA, typename TB, int P, int Q>
+void nt_launch(unsigned nb, hipStream_t s, const TA* A, const TB* B, int m, int n, long K, long kslice, int splits,
+               double* part) {
+    hipLaunchKernelGGL((k_nt_mfma<KIND, TA, TB, P, Q>), dim3(nb), dim3(NT), 0, s, A, B, m, n, K, kslice, splits, part);
+}
+template <int KIND, typename TA, typename TB, int P>
+void nt_launch_p(int Q, unsigned nb, hipStream_t s, const TA* A, const TB* B, int m, int n, long K, long kslice,
+                 int splits, double* part) {
+    switch (Q) {
+        case 1: return nt_launch<KIND, TA, TB, P, 1>(nb, s, A, B, m, n, K, kslice, splits, part);
+        case 2: return nt_launch<KIND, TA, TB, P, 2>(nb, s, A, B, m, n, K, kslice, splits, part);
+        case 3: return nt_launch<KIND, TA, TB, P, 3>(nb, s, A, B, m, n, K, kslice, splits, part);
+        default: return nt_launch<KIND, TA, TB, P, 4>(nb, s, A, B, m, n, K, kslice, splits, part);
+    }
+}
+
+// LDS of an NN workgroup; resident A up to half a CU's 160 KB
+constexpr size_t NN_LDS_HALF = 80 * 1024;
+template <int KIND>
+size_t nn_lds(int P, int a_stages) {
+    using S = NN<KIND>;
+    return sizeof(typename Kind<KIND>::E) * ((size_t)2 * S::B_ELEMS + (size_t)a_stages * 32 * P * S::PITCH);
+}
+
+template <int KIND, typename TB, typename TC, int P, bool RES, bool LOWER>
+hipError_t nn_launch(const double* A, long sai, long sak, const TB* B, int m, int K, long ncol, double alpha, TC* C,
+                     size_t lds, hipStream_t s) {
+    // resident workgroups per CU by registers and the CU count, queried once
+    // per process (a thread-safe static initialization)
+    struct Fill {
+        hipError_t err;
+        int occ, n_cu;
+    };
+    static const Fill fill = [] {
+        int dev = 0, o = 0, c = 0;
+        hipError_t e = hipGetDevice(&dev);
+        if (e == hipSuccess) e = hipDeviceGetAttribute(&c, hipDeviceAttributeMultiprocessorCount, dev);
+        if (e == hipSuccess)
+            e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&o, k_nn_mfma<KIND, TB, TC, P, RES, LOWER>, NT, 0);
+        if (e == hipSuccess && (o < 1 || c < 1)) e = hipErrorInvalidValue;
+        return Fill{e, o, c};
+    }();
+    if (fill.err != hipSuccess) return fill.err;
+    const int occ = std::max(1, std::min(fill.occ, (int)(2 * NN_LDS_HALF / lds)));
+    const int per = (m + 32 * P - 1) / (32 * P);
+    const long ntile = (ncol + BN - 1) / BN;
+    // as many slots as stay resident (at least one), no more than the tiles need
+    long slots = (long)fill.n_cu * occ / ((long)ACE_XCD * per);
+    slots = std::max(1L, std::min(slots, (ntile + ACE_XCD - 1) / ACE_XCD));
+    const long nb = slots * ACE_XCD * per;
+    if (nb > 0x7fffffffL) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((k_nn_mfma<KIND, TB, TC, P, RES, LOWER>), dim3((unsigned)nb), dim3(NT), lds, s, A, sai, sak, B,
+                       m, K, ncol, alpha, C, (int)slots);
+    return hipGetLastError();
+}
+template <int KIND, typename TB, typename TC, int P>
+hipError_t nn_launch_p(const double* A, long sai, long sak, const TB* B, int m, int K, long ncol, double alpha, TC* C,
+                       bool lower, hipStream_t s) {
+    const int nst = K > 0 ? (K + NN<KIND>::KT - 1) / NN<KIND>::KT : 1;
+    const size_t res = nn_lds<KIND>(P, nst);
+    if (res <= NN_LDS_HALF)
+        return nn_launch<KIND, TB, TC, P, true, false>(A, sai, sak, B, m, K, ncol, alpha, C, res, s);
+    const size_t lds = nn_lds<KIND>(P, 2);
+    // L^-1 multiplies W, which is FP64
+    constexpr bool W64 = std::is_same<TB, double>::value;
+    if (W64 && lower && m > 32 * P)
+        return nn_launch<KIND, TB, TC, P, false, W64>(A, sai, sak, B, m, K, ncol, alpha, C, lds, s);
+    return nn_launch<KIND, TB, TC, P, false, false>(A, sai, sak, B, m, K, ncol, alpha, C, lds, s);
 }
 
 }  // namespace
 
+// Blocks wanted: two rounds of two workgroups per CU for the large tiles, four
+// for the small ones, which are bound by loads in flight; a slice is at least
+// four block sides long, so that writing the partials stays small beside
+// reading the operands.
 int ace_mfma_splits(long K, int m, int n, int max_splits) {
-    const long tiles = (long)((m + BM - 1) / BM) * ((n + BN - 1) / BN);
-    long s = (1024 + tiles - 1) / tiles;
-    const long maxs = (K + 2047) / 2048;
+    const int tm = 32 * nt_block(K, m), tn = 32 * nt_block(K, n);
+    const long tiles = (long)((m + tm - 1) / tm) * ((n + tn - 1) / tn);
+    const long want = tm * tn <= 64 * 64 ? 2048 : 1024;
+    long s = (want + tiles - 1) / tiles;
+    const long min_slice = std::max(256, 4 * std::max(tm, tn));
+    const long maxs = K <= NT_SHORT_K ? 1 : (K + min_slice - 1) / min_slice;
     if (s > maxs) s = maxs;
     if (max_splits > 0 && s > max_splits) s = max_splits;
     if (s < 1) s = 1;
@@ -379,56 +650,40 @@ int ace_mfma_splits(long K, int m, int n, int max_splits) {
 template <int KIND, typename TA, typename TB>
 hipError_t ace_mm_nt(const TA* A, const TB* B, int m, int n, long K, double alpha, double* part, double* C,
                      hipStream_t s, int max_splits) {
-    if ((long)BM * K >= 0x7fffffffL) return hipErrorInvalidValue;   // 32-bit element offsets of a stage
+    if (128 * K >= 0x7fffffffL) return hipErrorInvalidValue;
     const int splits = ace_mfma_splits(K, m, n, max_splits);
+    const int P = nt_block(K, m), Q = nt_block(K, n);
+    constexpr int KT = 8 * Kind<KIND>::CE;
     long kslice = (K + splits - 1) / splits;
-    kslice = (kslice + Kind<KIND>::KT - 1) / Kind<KIND>::KT * Kind<KIND>::KT;
-    const long nb = xcd_grid(splits, ((n + BN - 1) / BN) * ((m + BM - 1) / BM));
+    kslice = (kslice + KT - 1) / KT * KT;
+    const long nb = xcd_grid(splits, ((n + 32 * Q - 1) / (32 * Q)) * ((m + 32 * P - 1) / (32 * P)));
     if (nb > 0x7fffffffL) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((k_nt_mfma<KIND, TA, TB>), dim3((unsigned)nb), dim3(NT), 0, s, A, B, m, n, K, kslice, splits,
-                       part);
+    switch (P) {
+        case 1: nt_launch_p<KIND, TA, TB, 1>(Q, (unsigned)nb, s, A, B, m, n, K, kslice, splits, part); break;
+        case 2: nt_launch_p<KIND, TA, TB, 2>(Q, (unsigned)nb, s, A, B, m, n, K, kslice, splits, part); break;
+        case 3: nt_launch_p<KIND, TA, TB, 3>(Q, (unsigned)nb, s, A, B, m, n, K, kslice, splits, part); break;
+        default: nt_launch_p<KIND, TA, TB, 4>(Q, (unsigned)nb, s, A, B, m, n, K, kslice, splits, part); break;
+    }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const int mn = m * n;
-    hipLaunchKernelGGL(k_slice_sum, dim3((mn + 255) / 256), dim3(256), 0, s, part, splits, mn, alpha, C);
+    hipLaunchKernelGGL(k_slice_sum, dim3((mn + SS_E - 1) / SS_E), dim3(SS_E * SS_G), 0, s, part, splits, mn, alpha, C);
     return hipGetLastError();
 }
 
 template <int KIND, typename TB, typename TC>
 hipError_t ace_mm_nn(const double* A, long sai, long sak, const TB* B, int m, int K, long ncol, double alpha, TC* C,
-                     hipStream_t s) {
+                     hipStream_t s, bool lower) {
     if (m <= 0 || ncol <= 0) return hipSuccess;
-    // resident workgroups per CU of this instantiation and the CU count,
-    // queried once per process (a thread-safe static initialization)
-    struct Fill {
-        hipError_t err;
-        int occ, n_cu;
-    };
-    static const Fill fill = [] {
-        int dev = 0, o = 0, c = 0;
-        hipError_t e = hipGetDevice(&dev);
-        if (e == hipSuccess) e = hipDeviceGetAttribute(&c, hipDeviceAttributeMultiprocessorCount, dev);
-        if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&o, k_nn_mfma<KIND, TB, TC>, NT, 0);
-        if (e == hipSuccess && (o < 1 || c < 1)) e = hipErrorInvalidValue;
-        return Fill{e, o, c};
-    }();
-    if (fill.err != hipSuccess) return fill.err;
-    const int occ = fill.occ, n_cu = fill.n_cu;
-    const int per = (m + BM - 1) / BM;
-    const long ntile = (ncol + BN - 1) / BN;
-    // as many slots as stay resident (at least one), no more than the tiles need
-    long slots = (long)n_cu * occ / ((long)ACE_XCD * per);
-    slots = std::max(1L, std::min(slots, (ntile + ACE_XCD - 1) / ACE_XCD));
-    const long nb = slots * ACE_XCD * per;
-    if (nb > 0x7fffffffL) return hipErrorInvalidValue;
-    // a thread's 32-bit offsets: A rows below NT / KT, k below KT; B rows 0, 1
-    constexpr int KT = nn_kt<KIND>();
-    if (sai < 0 || sak < 0 || (long)(NT / KT) * sai + (long)KT * sak >= 0x7fffffffL ||
-        2 * ncol + BN >= 0x7fffffffL)
+    if (sai < 0 || sak < 0 || 8 * sai + 32 * sak >= 0x7fffffffL || 2 * ncol + BN >= 0x7fffffffL)
         return hipErrorInvalidValue;
-    hipLaunchKernelGGL((k_nn_mfma<KIND, TB, TC>), dim3((unsigned)nb), dim3(NT), 0, s, A, sai, sak, B, m, K, ncol, alpha,
-                       C, (int)slots);
-    return hipGetLastError();
+    const int nb = (m + 127) / 128;
+    switch ((m + 32 * nb - 1) / (32 * nb)) {
+        case 1: return nn_launch_p<KIND, TB, TC, 1>(A, sai, sak, B, m, K, ncol, alpha, C, lower, s);
+        case 2: return nn_launch_p<KIND, TB, TC, 2>(A, sai, sak, B, m, K, ncol, alpha, C, lower, s);
+        case 3: return nn_launch_p<KIND, TB, TC, 3>(A, sai, sak, B, m, K, ncol, alpha, C, lower, s);
+        default: return nn_launch_p<KIND, TB, TC, 4>(A, sai, sak, B, m, K, ncol, alpha, C, lower, s);
+    }
 }
 
 #define NT_INST(KIND, TA, TB) \
@@ -436,14 +691,14 @@ hipError_t ace_mm_nn(const double* A, long sai, long sak, const TB* B, int m, in
                                                 hipStream_t, int);
 #define NN_INST(KIND, TB, TC)                                                                                      \
     template hipError_t ace_mm_nn<KIND, TB, TC>(const double*, long, long, const TB*, int, int, long, double, TC*, \
-                                                hipStream_t);
-// M and the energy (FP64 operands; xi converted exactly), dV xi^T psi per ace_dtype
+                                                hipStream_t, bool);
+// M and the energy (FP64 operands; xi converted exactly), dV psi xi^T per ace_dtype
 NT_INST(ACE_F64, double, double)
 NT_INST(ACE_F64, double, float)
 NT_INST(ACE_F64, double, uint16_t)
 NT_INST(ACE_F32, float, float)
 NT_INST(ACE_BF16, uint16_t, uint16_t)
-// xi = L^-1 W and K psi = -C^T xi per ace_dtype
+// xi = L^-1 W and K psi = -C xi per ace_dtype
 NN_INST(ACE_F64, double, double)
 NN_INST(ACE_F32, double, float)
 NN_INST(ACE_F32, float, float)

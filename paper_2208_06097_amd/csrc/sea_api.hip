@@ -1162,16 +1162,16 @@ sea_status sea_ace_build(sea_ctx* ctx, int64_t n_grid, int n_occ, double dV, con
     } else {
         SEA_HIP_CHECK(ctx, ace_trtri(L_dev, n_occ, Li, s));
     }
-    // xi (orbital-major) = L^{-1} W
+    // xi (orbital-major) = L^{-1} W; L^{-1} is lower triangular, the eigen map is not
     if (ctx->opts.ace_dtype == SEA_F64)
         SEA_HIP_CHECK(ctx, (ace_mm_nn<ACE_F64, double, double>(Li, n_occ, 1, W_dev, n_occ, n_occ, n_grid, 1.0,
-                                                               (double*)xi_dev, s)));
+                                                               (double*)xi_dev, s, !eigen)));
     else if (ctx->opts.ace_dtype == SEA_F32)
         SEA_HIP_CHECK(ctx, (ace_mm_nn<ACE_F32, double, float>(Li, n_occ, 1, W_dev, n_occ, n_occ, n_grid, 1.0,
-                                                              (float*)xi_dev, s)));
+                                                              (float*)xi_dev, s, !eigen)));
     else
         SEA_HIP_CHECK(ctx, (ace_mm_nn<ACE_BF16, double, uint16_t>(Li, n_occ, 1, W_dev, n_occ, n_occ, n_grid, 1.0,
-                                                                  (uint16_t*)xi_dev, s)));
+                                                                  (uint16_t*)xi_dev, s, !eigen)));
     if (eigen && ctx->opts.ace_decomp == SEA_DECOMP_AUTO) {
         fail(ctx, SEA_W_EIGEN_FALLBACK, "Mbar not positive definite (pivot %d): eigen decomposition used", hflag);
         return SEA_W_EIGEN_FALLBACK;
@@ -1193,22 +1193,21 @@ sea_status sea_ace_apply(sea_ctx* ctx, int64_t n_grid, int n_occ, double dV, con
     double* Cm = (double*)(base + Ly.cmat);
     ctx->ev_used[SEA_STAGE_ACE_APPLY] = false;
     StageTimer t(ctx, SEA_STAGE_ACE_APPLY, s);
-    // C (n_occ x n_vec) = dV xi psi^T ; out (n_vec x n_grid) = -C^T xi
+    // C (n_vec x n_occ) = dV psi xi^T ; out (n_vec x n_grid) = -C xi
     if (ctx->opts.ace_dtype == SEA_F64) {
-        SEA_HIP_CHECK(ctx, (ace_mm_nt<ACE_F64, double, double>((const double*)xi_dev, (const double*)psi_dev, n_occ,
-                                                               n_vec, n_grid, dV, part, Cm, s)));
-        SEA_HIP_CHECK(ctx, (ace_mm_nn<ACE_F64, double, double>(Cm, 1, n_vec, (const double*)xi_dev, n_vec, n_occ,
+        SEA_HIP_CHECK(ctx, (ace_mm_nt<ACE_F64, double, double>((const double*)psi_dev, (const double*)xi_dev, n_vec, n_occ,
+                                                               n_grid, dV, part, Cm, s)));
+        SEA_HIP_CHECK(ctx, (ace_mm_nn<ACE_F64, double, double>(Cm, n_occ, 1, (const double*)xi_dev, n_vec, n_occ,
                                                                n_grid, -1.0, (double*)out_dev, s)));
     } else if (ctx->opts.ace_dtype == SEA_F32) {
-        SEA_HIP_CHECK(ctx, (ace_mm_nt<ACE_F32, float, float>((const float*)xi_dev, (const float*)psi_dev, n_occ,
-                                                             n_vec, n_grid, dV, part, Cm, s)));
-        SEA_HIP_CHECK(ctx, (ace_mm_nn<ACE_F32, float, float>(Cm, 1, n_vec, (const float*)xi_dev, n_vec, n_occ,
+        SEA_HIP_CHECK(ctx, (ace_mm_nt<ACE_F32, float, float>((const float*)psi_dev, (const float*)xi_dev, n_vec,
+                                                             n_occ, n_grid, dV, part, Cm, s)));
+        SEA_HIP_CHECK(ctx, (ace_mm_nn<ACE_F32, float, float>(Cm, n_occ, 1, (const float*)xi_dev, n_vec, n_occ,
                                                              n_grid, -1.0, (float*)out_dev, s)));
     } else {
-        SEA_HIP_CHECK(ctx, (ace_mm_nt<ACE_BF16, uint16_t, uint16_t>((const uint16_t*)xi_dev,
-                                                                    (const uint16_t*)psi_dev, n_occ, n_vec, n_grid,
-                                                                    dV, part, Cm, s)));
-        SEA_HIP_CHECK(ctx, (ace_mm_nn<ACE_BF16, uint16_t, float>(Cm, 1, n_vec, (const uint16_t*)xi_dev, n_vec,
+        SEA_HIP_CHECK(ctx, (ace_mm_nt<ACE_BF16, uint16_t, uint16_t>((const uint16_t*)psi_dev, (const uint16_t*)xi_dev, n_vec,
+                                                                    n_occ, n_grid, dV, part, Cm, s)));
+        SEA_HIP_CHECK(ctx, (ace_mm_nn<ACE_BF16, uint16_t, float>(Cm, n_occ, 1, (const uint16_t*)xi_dev, n_vec,
                                                                  n_occ, n_grid, -1.0, (float*)out_dev, s)));
     }
     return SEA_OK;

@@ -59,7 +59,7 @@ extern "C" sea_status sea_ace_apply_noalloc(sea_ctx* ctx, int64_t n_grid, int n_
     if (n_vec < 1) return fail(ctx, SEA_E_ARG, "n_vec < 1");
     if (!(dV > 0.0) || !std::isfinite(dV)) return fail(ctx, SEA_E_ARG, "dV must be positive and finite");
     if (!xi_dev || !psi_dev || !out_dev) return fail(ctx, SEA_E_ARG, "NULL array argument");
-    // the small product C (n_occ x n_vec) and at least one K slice of partials
+    // the small product C (n_vec x n_occ) and at least one K slice of partials
     const size_t mn = (size_t)n_occ * (size_t)n_vec * sizeof(double);
     const size_t c_bytes = align256(mn);
     if (c_bytes >= kScratchBytes || (kScratchBytes - c_bytes) / mn < 1)
@@ -76,24 +76,24 @@ extern "C" sea_status sea_ace_apply_noalloc(sea_ctx* ctx, int64_t n_grid, int n_
     double* part = (double*)(base + c_bytes);
     hipStream_t s = (hipStream_t)ctx->opts.hip_stream;
     hipError_t e;
-    // C (n_occ x n_vec) = dV xi psi^T ; out (n_vec x n_grid) = -C^T xi
+    // C (n_vec x n_occ) = dV psi xi^T ; out (n_vec x n_grid) = -C xi
     if (ctx->opts.ace_dtype == SEA_F64) {
-        e = ace_mm_nt<ACE_F64, double, double>((const double*)xi_dev, (const double*)psi_dev, n_occ, n_vec, n_grid, dV,
+        e = ace_mm_nt<ACE_F64, double, double>((const double*)psi_dev, (const double*)xi_dev, n_vec, n_occ, n_grid, dV,
                                                part, Cm, s, max_splits);
         if (e == hipSuccess)
-            e = ace_mm_nn<ACE_F64, double, double>(Cm, 1, n_vec, (const double*)xi_dev, n_vec, n_occ, n_grid, -1.0,
+            e = ace_mm_nn<ACE_F64, double, double>(Cm, n_occ, 1, (const double*)xi_dev, n_vec, n_occ, n_grid, -1.0,
                                                    (double*)out_dev, s);
     } else if (ctx->opts.ace_dtype == SEA_F32) {
-        e = ace_mm_nt<ACE_F32, float, float>((const float*)xi_dev, (const float*)psi_dev, n_occ, n_vec, n_grid, dV,
+        e = ace_mm_nt<ACE_F32, float, float>((const float*)psi_dev, (const float*)xi_dev, n_vec, n_occ, n_grid, dV,
                                              part, Cm, s, max_splits);
         if (e == hipSuccess)
-            e = ace_mm_nn<ACE_F32, float, float>(Cm, 1, n_vec, (const float*)xi_dev, n_vec, n_occ, n_grid, -1.0,
+            e = ace_mm_nn<ACE_F32, float, float>(Cm, n_occ, 1, (const float*)xi_dev, n_vec, n_occ, n_grid, -1.0,
                                                  (float*)out_dev, s);
     } else {
-        e = ace_mm_nt<ACE_BF16, uint16_t, uint16_t>((const uint16_t*)xi_dev, (const uint16_t*)psi_dev, n_occ, n_vec,
+        e = ace_mm_nt<ACE_BF16, uint16_t, uint16_t>((const uint16_t*)psi_dev, (const uint16_t*)xi_dev, n_vec, n_occ,
                                                     n_grid, dV, part, Cm, s, max_splits);
         if (e == hipSuccess)
-            e = ace_mm_nn<ACE_BF16, uint16_t, float>(Cm, 1, n_vec, (const uint16_t*)xi_dev, n_vec, n_occ, n_grid, -1.0,
+            e = ace_mm_nn<ACE_BF16, uint16_t, float>(Cm, n_occ, 1, (const uint16_t*)xi_dev, n_vec, n_occ, n_grid, -1.0,
                                                      (float*)out_dev, s);
     }
     if (e != hipSuccess) return fail(ctx, SEA_E_HIP, "HIP error: %s", hipGetErrorString(e));

@@ -298,7 +298,8 @@ ExxLayout exx_layout(const sea_ctx* ctx, const CellSet& S, bool with_v, bool eag
     L.rnorm = (spectral || tiled64) ? take(np * RZ_TILES * 2 * sizeof(double)) : 0;
     L.cg_r = tiled64 ? take(np * stride * sizeof(double)) : 0;
     L.cg_p = tiled64 ? take(2 * np * stride * sizeof(double)) : 0;
-    L.cg_part = tiled64 ? take(np * RZ_TILES * 4 * sizeof(double)) : 0;
+    L.cg_ap = tiled64 && cg64_small_extents(pairs, n_pairs).n ? take(np * stride * sizeof(double)) : 0;
+    L.cg_part = tiled64 ? take(np * CG64_PART * sizeof(double)) : 0;
     L.cg_rho = tiled64 ? take(np * 2 * sizeof(double)) : 0;
     L.cg_done = tiled64 ? take(np * sizeof(int)) : 0;
     L.cg_active = tiled64 ? take(((size_t)ctx->opts.max_iter + 1) * sizeof(int)) : 0;
@@ -577,6 +578,7 @@ static ExxArgs exx_args(sea_ctx* ctx, const CellSet& S, const ExxLayout& Ly, cha
     a.ep_stride = Ly.ep_stride;
     a.cg_r = Ly.cg_r ? (double*)(base + Ly.cg_r) : nullptr;
     a.cg_p = Ly.cg_p ? (double*)(base + Ly.cg_p) : nullptr;
+    a.cg_ap = Ly.cg_ap ? (double*)(base + Ly.cg_ap) : nullptr;
     a.cg_part = Ly.cg_part ? (double*)(base + Ly.cg_part) : nullptr;
     a.cg_rho = Ly.cg_rho ? (double*)(base + Ly.cg_rho) : nullptr;
     a.cg_done = Ly.cg_done ? (int*)(base + Ly.cg_done) : nullptr;
@@ -591,17 +593,22 @@ static ExxArgs exx_args(sea_ctx* ctx, const CellSet& S, const ExxLayout& Ly, cha
 // has stopped (checked from the per-iteration counters every few
 // iterations, which synchronizes), then the true residual's norms into
 // rel_res.
-static sea_status cg64_run(sea_ctx* ctx, const ExxArgs& a0, double* rnorm, hipStream_t s) {
+static sea_status cg64_run(sea_ctx* ctx, const CellSet& S, const ExxArgs& a0, double* rnorm, hipStream_t s) {
     ExxArgs a = a0;
     a.rnorm = nullptr;
     SEA_HIP_CHECK(ctx, launch_fill_int(a.cg_active, (size_t)a.max_iter + 1, s));
-    SEA_HIP_CHECK(ctx, launch_cg64_init(a, s));
+    const Cg64Small small = cg64_small_extents(S.pairs.data(), a.n_pairs);
+    const bool large = small.n < a.n_pairs;
+    if (small.n) SEA_HIP_CHECK(ctx, launch_cg64_small(a, small, -1, s));
+    if (large) SEA_HIP_CHECK(ctx, launch_cg64_init(a, s));
     constexpr int every = 16;
     for (int k = 0;; ++k) {
         a.cg_it = k;
-        SEA_HIP_CHECK(ctx, launch_cg64_sweep(a, 0, s));
+        if (small.n) SEA_HIP_CHECK(ctx, launch_cg64_small(a, small, 0, s));
+        if (large) SEA_HIP_CHECK(ctx, launch_cg64_sweep(a, 0, s));
         if (k >= a.max_iter) break;
-        SEA_HIP_CHECK(ctx, launch_cg64_sweep(a, 1, s));
+        if (small.n) SEA_HIP_CHECK(ctx, launch_cg64_small(a, small, 1, s));
+        if (large) SEA_HIP_CHECK(ctx, launch_cg64_sweep(a, 1, s));
         if (k % every == every - 1) {
             int active = 0;
             SEA_HIP_CHECK(ctx, hipMemcpyAsync(&active, a.cg_active + k, sizeof(int), hipMemcpyDeviceToHost, s));
@@ -776,7 +783,7 @@ static sea_status exx_enqueue(sea_ctx* ctx, const CellSet& S, const ExxLayout& L
                 timer_off(SEA_STAGE_FINISH);
             }
         } else if (tiled64) {
-            sea_status st = cg64_run(ctx, a, (double*)(base + Ly.rnorm), s);
+            sea_status st = cg64_run(ctx, S, a, (double*)(base + Ly.rnorm), s);
             if (st != SEA_OK) return st;
             timer_off(SEA_STAGE_CG);
             if (!f.action) {

@@ -73,7 +73,7 @@ struct StageTimer {
 // Byte layout of the exx workspace (offsets from the workspace base).
 struct ExxLayout {
     size_t pairs, pair_cell, order, dbox, cells, partial, mom, b, v, bres, slots, stats, csr_off, csr_ent, scal, counter;
-    size_t nnx, nny, nnact, dst_tmp, dst_tab, dst_mu, rnorm, racah_tab, mpoly, epart, cg_r, cg_p, cg_part,
+    size_t nnx, nny, nnact, dst_tmp, dst_tab, dst_mu, rnorm, racah_tab, mpoly, epart, cg_r, cg_p, cg_ap, cg_part,
         cg_rho, cg_done, cg_active, refine, sc_work, total;
     int nmax;
     int ep_stride;        // pair-energy partial slots per pair (scatter)
@@ -142,7 +142,8 @@ struct ExxArgs {
     // FP64 row-tile CG (one launch per sweep over all pairs)
     double* cg_r;         // n_pairs x stride: residual
     double* cg_p;         // 2 x n_pairs x stride: search direction, by iteration parity
-    double* cg_part;      // n_pairs x RZ_TILES x 8 partial sums per row tile (k_cg.hip)
+    double* cg_ap;        // n_pairs x stride: A p of the small domains
+    double* cg_part;      // n_pairs x CG64_PART partial sums (k_cg.hip)
     double* cg_rho;       // n_pairs x 2: |r|^2 of the last two iterations
     int* cg_done;         // n_pairs: the pair has stopped; null outside the row-tile CG
     int* cg_active;       // max_iter + 1 counters: pairs still iterating at each iteration
@@ -278,6 +279,23 @@ hipError_t launch_residual_zm(const ExxArgs& a, hipStream_t s, bool write = true
 hipError_t launch_cg64_init(const ExxArgs& a, hipStream_t s);
 hipError_t launch_cg64_sweep(const ExxArgs& a, int sweep, hipStream_t s);
 hipError_t launch_cg64_exit(const ExxArgs& a, hipStream_t s);
+// Small domains of the FP64 CG, cut along z as well (k_cg.hip).  The line lies
+// with the domain alone, so that a pair's result does not depend on its batch,
+// and where a full chip of pairs stops gaining: 300 pairs of 32^3 80.9 -> 41.6
+// ms, of 40^3 144 -> 96, of 48^3 200 -> 167, but of 56^3 275 -> 310 (HBM then
+// carries the two more words); 8 pairs gain 3 to 4 times at every size.
+constexpr int CG64_PART = 256;            // partial sums of a pair
+constexpr int CG64_SMALL_PTS = 131072, CG64_SMALL_NZ = 128;
+__host__ __device__ inline bool cg64_small(const sea_pair& P) {
+    return (long)P.n[0] * P.n[1] * P.n[2] <= CG64_SMALL_PTS && P.n[2] <= CG64_SMALL_NZ;
+}
+struct Cg64Small {
+    int n, packed;                        // how many, and of those with two rows to a wavefront
+    int tiles, chunks, blocks;            // their largest extents in workgroups
+};
+Cg64Small cg64_small_extents(const sea_pair* pairs, int n_pairs);
+// sweep -1: the start, 0: A, 1: B
+hipError_t launch_cg64_small(const ExxArgs& a, const Cg64Small& e, int sweep, hipStream_t s);
 // Refinement of the spectral start's potentials (cubic grids, every pair taken
 // by the transform).  launch_refine_flags after the norms pass sets each
 // pair's iters, converged and rel_res and lists the pairs that miss the target

@@ -177,7 +177,12 @@ __global__ __launch_bounds__(NT, nt_minb(P, Q)) void k_nt_mfma(const TA* __restr
     const int tn = (n + TN - 1) / TN, tm = (m + TM - 1) / TM;
     long slice;
     int tile;
-    xcd_block(tn * tm, slice, tile);
+    if (splits < ACE_XCD) {   // (too few slices to give each XCD some: the tiles go round)
+        slice = blockIdx.x / (tn * tm);
+        tile = blockIdx.x % (tn * tm);
+    } else {
+        xcd_block(tn * tm, slice, tile);
+    }
     if (slice >= splits) return;   // padding of the last XCD round (an empty slice still writes its zeros)
     const long kb = slice * kslice;
     const int j0 = (tile % tn) * TN, i0 = (tile / tn) * TM;
@@ -547,15 +552,24 @@ __global__ __launch_bounds__(NT, nn_minb(P)) void k_nn_mfma(const double* __rest
     }
 }
 
-// Rows of 32 in an NT block along a side of x: as few blocks of at most 128
-// as hold it, as thin as that many allow.  Products over a short K (the small
-// matrices of the polar iteration) are bound by latency and take the smallest
-// block: 256 x 256 x 256 on 64 workgroups, not 4.
+// Rows (and columns) of 32 in an NT block: as few blocks of at most 128 as hold
+// the side, as thin as that many allow.  Products over a short K are not split
+// along it and take smaller blocks until there is one for each CU, or the
+// smallest (256 x 256 x 256: 64 workgroups, not 4, 45 -> 11 us).
 constexpr long NT_SHORT_K = 2048;
-int nt_block(long K, int x) {
-    if (K <= NT_SHORT_K) return 1;
+int nt_side(int x) {
     const int nb = (x + 127) / 128;
     return std::max(1, (x + 32 * nb - 1) / (32 * nb));
+}
+void nt_block(long K, int m, int n, int& P, int& Q) {
+    P = nt_side(m);
+    Q = nt_side(n);
+    auto blocks = [&] { return (long)((m + 32 * P - 1) / (32 * P)) * ((n + 32 * Q - 1) / (32 * Q)); };
+    if (K <= NT_SHORT_K)
+        while (blocks() < 256 && (P > 1 || Q > 1)) {
+            P = std::max(1, P / 2);
+            Q = std::max(1, Q / 2);
+        }
 }
 
 template <int KIND, typename TA, typename TB, int P, int Q>
@@ -635,7 +649,9 @@ hipError_t nn_launch_p(const double* A, long sai, long sak, const TB* B, int m, 
 // four block sides long, so that writing the partials stays small beside
 // reading the operands.
 int ace_mfma_splits(long K, int m, int n, int max_splits) {
-    const int tm = 32 * nt_block(K, m), tn = 32 * nt_block(K, n);
+    int P, Q;
+    nt_block(K, m, n, P, Q);
+    const int tm = 32 * P, tn = 32 * Q;
     const long tiles = (long)((m + tm - 1) / tm) * ((n + tn - 1) / tn);
     const long want = tm * tn <= 64 * 64 ? 2048 : 1024;
     long s = (want + tiles - 1) / tiles;
@@ -652,11 +668,13 @@ hipError_t ace_mm_nt(const TA* A, const TB* B, int m, int n, long K, double alph
                      hipStream_t s, int max_splits) {
     if (128 * K >= 0x7fffffffL) return hipErrorInvalidValue;
     const int splits = ace_mfma_splits(K, m, n, max_splits);
-    const int P = nt_block(K, m), Q = nt_block(K, n);
+    int P, Q;
+    nt_block(K, m, n, P, Q);
     constexpr int KT = 8 * Kind<KIND>::CE;
     long kslice = (K + splits - 1) / splits;
     kslice = (kslice + KT - 1) / KT * KT;
-    const long nb = xcd_grid(splits, ((n + 32 * Q - 1) / (32 * Q)) * ((m + 32 * P - 1) / (32 * P)));
+    const int tiles = ((n + 32 * Q - 1) / (32 * Q)) * ((m + 32 * P - 1) / (32 * P));
+    const long nb = splits < ACE_XCD ? (long)splits * tiles : xcd_grid(splits, tiles);
     if (nb > 0x7fffffffL) return hipErrorInvalidValue;
     switch (P) {
         case 1: nt_launch_p<KIND, TA, TB, 1>(Q, (unsigned)nb, s, A, B, m, n, K, kslice, splits, part); break;
@@ -677,8 +695,10 @@ hipError_t ace_mm_nn(const double* A, long sai, long sak, const TB* B, int m, in
     if (m <= 0 || ncol <= 0) return hipSuccess;
     if (sai < 0 || sak < 0 || 8 * sai + 32 * sak >= 0x7fffffffL || 2 * ncol + BN >= 0x7fffffffL)
         return hipErrorInvalidValue;
+    // blocks as in the NT product; the smallest where the columns are few (256 x
+    // 256 x 256: 16 workgroups, not 4)
     const int nb = (m + 127) / 128;
-    switch ((m + 32 * nb - 1) / (32 * nb)) {
+    switch (ncol <= NT_SHORT_K && m <= NT_SHORT_K ? 1 : (m + 32 * nb - 1) / (32 * nb)) {
         case 1: return nn_launch_p<KIND, TB, TC, 1>(A, sai, sak, B, m, K, ncol, alpha, C, lower, s);
         case 2: return nn_launch_p<KIND, TB, TC, 2>(A, sai, sak, B, m, K, ncol, alpha, C, lower, s);
         case 3: return nn_launch_p<KIND, TB, TC, 3>(A, sai, sak, B, m, K, ncol, alpha, C, lower, s);

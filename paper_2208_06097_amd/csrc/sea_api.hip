@@ -1301,7 +1301,7 @@ ScdmFull scdm_full_layout(long Ng, int n) {
     L.P = take(nn);
     L.Ya = take(nn);
     L.Yb = take(nn);
-    L.err = take(64);
+    L.err = take(SC_NS_ERR * sizeof(double));
     L.part = take((size_t)ace_mfma_splits(n, n, n) * nn);
     L.total = off;
     return L;
@@ -1362,7 +1362,7 @@ extern "C" sea_status sea_scdm(sea_ctx* ctx, int64_t n_grid, int n_occ, const vo
         SEA_HIP_CHECK(ctx, scdm_init(phi_dev, f32, Ng, n, ws, L.piv, s));
         int k0 = 0;
         for (;;) {
-            SEA_HIP_CHECK(ctx, scdm_round(phi_dev, f32, Ng, n, rounds == 0, ws, L.piv, s));
+            SEA_HIP_CHECK(ctx, scdm_round(phi_dev, f32, Ng, n, k0, ws, L.piv, s));
             SEA_HIP_CHECK(ctx, scdm_read_state(ws, L.piv, &k, &fl, s));
             ++rounds;
             if (fl) break;
@@ -1396,9 +1396,10 @@ extern "C" sea_status sea_scdm(sea_ctx* ctx, int64_t n_grid, int n_occ, const vo
             SEA_HIP_CHECK(ctx, (ace_mm_nn<ACE_F64, double, double>(P, n, 1, cur, n, n, n, 1.0, nxt, s)));
             std::swap(cur, nxt);
             if (it % 4 == 3) {
-                double e = 0.0;
-                SEA_HIP_CHECK(ctx, hipMemcpyAsync(&e, errd, sizeof(double), hipMemcpyDeviceToHost, s));
+                double part_e[SC_NS_ERR], e = 0.0;
+                SEA_HIP_CHECK(ctx, hipMemcpyAsync(part_e, errd, sizeof(part_e), hipMemcpyDeviceToHost, s));
                 SEA_HIP_CHECK(ctx, hipStreamSynchronize(s));
+                for (double q : part_e) e += q;
                 conv = e <= 1e-24;   // |X^T X - I|_F <= 1e-12 before the last step
             }
         }

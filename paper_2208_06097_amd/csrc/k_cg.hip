@@ -50,6 +50,7 @@ __constant__ double kCw[7] = {-5369.0 / 1800.0, 12.0 / 7.0,      -15.0 / 56.0,  
 constexpr int LW = 64;                 // LDS row length (x)
 constexpr int LH = 64 + 2 * SEA_HALO;  // LDS rows per plane (y with halo)
 constexpr int PL = 64 * 64;            // slot-array plane pitch (elements)
+constexpr int RZ_XCD = 8;              // workgroup k runs on XCD k mod 8
 
 // Cubic grid: -Lap_h f = w0 f + sum_k wk (six neighbours at distance k).
 template <typename T>
@@ -520,7 +521,458 @@ __global__ __launch_bounds__(NT) void k_cg_zm(ExxArgs a) {
         const int qi = pid_sh;
         if (qi >= a.n_pairs) break;
         const int pid = a.order ? a.order[qi] : qi;  // largest domains first
+        if (a.team && cg_team_takes(a.pairs[pid])) continue;
         solve_pair<T, NT, COLS, PREFETCH, DEPTH, BUF, XC>(a, pid, lds, red, cc, rr, pp, r64);
+    }
+}
+
+// ---------------------------------------------------------------------------
+// FP32-state CG on a team of workgroups.  One workgroup per pair streams 8
+// words a point and iteration through memory (the arrays of 256 pairs, 0.8 GB,
+// fit no cache), forms A p twice and leaves most of the chip idle in the last
+// round of a pair list.  Here TM_G workgroups own TM_ZP planes each of one
+// domain and keep r and A p in registers and p in LDS; c alone is in memory
+// (read and written once an iteration) and p's planes go through it to the
+// neighbours.  Same recurrences, point for point, as the z-march above with
+// reliable updates; only the FP64 sums are added in another order.
+// Measured per iteration of a 63^3 domain: 35 to 45 us on 8 CUs (32 teams at
+// once), against 300 us and more on one; 288 such pairs 289 -> 153 ms, 8 of them
+// 107 -> 12 ms.  About 17 us of it are the vector ALUs, the rest the three
+// meetings and a third of r and A p, which the compiler spills.
+//
+// What a workgroup writes for others (p's planes, c, flags, partial sums) goes
+// past the caches that are not shared, in both directions (device scope).  Two
+// kinds of meeting: a flag with the number of the meeting, stored when all of the
+// workgroup's writes are complete, which the neighbours (p's planes) or all (c
+// before a residual update) wait for; and a sum, whose parts are their own flags
+// (an empty slot is all zero bits, a zero part is stored as -0), one trip through
+// memory.  The c update fills the wait for the sums.
+//
+// A workgroup fills a CU (LDS) and a team's are numbered together on one XCD (8
+// of its 32 CUs), so all of a team run at once as soon as that many are free,
+// whatever other streams hold: four such kernels at once (the hardware queues)
+// cannot all hold incomplete teams.  A workgroup that waits for a member not yet
+// started waits for CUs that other work gives back.  Every wait is bounded all
+// the same: past TM_SPIN polls (about a minute) the pair ends as failed.
+constexpr int TM_G = 8, TM_ZP = 8, TM_NT = 1024;
+constexpr int TM_TY = TM_NT / 64, TM_C = 64 / TM_TY;   // rows of threads; columns of a thread
+constexpr unsigned TM_SPIN = 1u << 26;
+static_assert(TM_G * TM_ZP >= CG_TEAM_MAX && TM_ZP >= SEA_HALO, "planes of the largest domain; halos from the neighbours");
+struct TeamCtl {
+    unsigned flag[TM_G];        // meetings reached by each workgroup
+    int pid[2];                 // queue index of the team's pair, by parity
+    int pad[6];
+    double part[4][TM_G];       // parts of four successive sums
+};
+static_assert(sizeof(TeamCtl) <= CG_TEAM_CTL && (CG_TEAM_CTL & 7) == 0, "control block");
+template <typename T>
+__device__ __forceinline__ T ld_dev(const T* p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <typename T>
+__device__ __forceinline__ void st_dev(T* p, T v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// One of the team's arrays of 64 x 64 planes in memory, the lane's column in a
+// VGPR and the (uniform) plane and row offset in a scalar register; device
+// scope, past the caches that CUs and XCDs keep for themselves.
+struct TeamIO {
+    static constexpr int DEVICE = 16;   // cache policy: sc1
+    __amdgpu_buffer_rsrc_t rs;
+    int voff;
+    __device__ TeamIO(float* base, int n_elems, int col0)
+        : rs(__builtin_amdgcn_make_buffer_rsrc(base, 0, n_elems * (int)sizeof(float), 0x00020000)),
+          voff(col0 * (int)sizeof(float)) {}
+    __device__ __forceinline__ float ld(int off) const {
+        return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, voff, off * (int)sizeof(float), DEVICE));
+    }
+    __device__ __forceinline__ void st(int off, float v) const {
+        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), rs, voff, off * (int)sizeof(float), DEVICE);
+    }
+    // the lane's own element, not an offset from its column
+    __device__ __forceinline__ float at(int elem) const {
+        return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, elem * (int)sizeof(float), 0, DEVICE));
+    }
+};
+
+struct Team {
+    TeamCtl* ctl;
+    int g;                       // this workgroup's number in the team
+    unsigned seq = 0;            // meetings so far
+    int n_sum = 0;               // sums so far
+    double* red;                 // LDS: one per wavefront
+    double* tot;                 // LDS: the last sum
+    int* fail;                   // LDS
+
+    // All writes of this workgroup are complete and its flag says so.
+    __device__ __forceinline__ void publish() {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        ++seq;
+        if (threadIdx.x == 0) st_dev(&ctl->flag[g], seq);
+    }
+    // Waits until workgroups lo..hi have published as often as this one;
+    // false once the wait has run out.
+    __device__ __forceinline__ bool wait(int lo, int hi) {
+        const int t = lo + (int)threadIdx.x;
+        if (threadIdx.x < TM_G && t <= hi) {
+            unsigned n = 0;
+            while ((int)(ld_dev(&ctl->flag[t]) - seq) < 0) {
+                __builtin_amdgcn_s_sleep(1);
+                if (++n > TM_SPIN) {
+                    *fail = 1;
+                    break;
+                }
+            }
+        }
+        __syncthreads();
+        return *fail == 0;
+    }
+    __device__ __forceinline__ bool sync() {
+        publish();
+        return wait(0, TM_G - 1);
+    }
+    // The team's sum of every thread's t, in a fixed order.  begin stores this
+    // workgroup's part, end waits for all.  A slot is cleared two sums before it
+    // is used again: its last readers have by then added to the sum between.
+    __device__ __forceinline__ void begin(double t) {
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) t += __shfl_xor(t, off, 64);
+        if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = t;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            t = 0.0;
+            for (int w = 0; w < TM_NT / 64; ++w) t += red[w];
+            if (t == 0.0) t = -0.0;
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the slot's clearing, two sums ago
+            st_dev(&ctl->part[n_sum & 3][g], t);
+            st_dev(&ctl->part[(n_sum + 2) & 3][g], 0.0);
+        }
+    }
+    __device__ __forceinline__ bool end(double& total) {
+        if (threadIdx.x < 64) {
+            const int lane = threadIdx.x;
+            double t = 0.0;
+            if (lane < TM_G) {
+                unsigned n = 0;
+                while (__double_as_longlong(t = ld_dev(&ctl->part[n_sum & 3][lane])) == 0) {
+                    __builtin_amdgcn_s_sleep(1);
+                    if (++n > TM_SPIN) {
+                        *fail = 1;
+                        break;
+                    }
+                }
+            }
+#pragma unroll
+            for (int off = TM_G / 2; off > 0; off >>= 1) t += __shfl_xor(t, off, 64);
+            if (lane == 0) *tot = t;
+        }
+        ++n_sum;
+        __syncthreads();
+        total = *tot;
+        return *fail == 0;
+    }
+    __device__ __forceinline__ bool sum(double t, double& total) {
+        begin(t);
+        return end(total);
+    }
+};
+
+// One pair.  Thread (tx, ty) owns the points (tx, ty + TM_TY c, TM_ZP g + z).
+// pl: LDS planes of p with SEA_HALO zero rows on either side; cc, ph: the
+// team's c and exported p (planes of 64 x 64), r64: the FP64 residual.
+__device__ __forceinline__ bool team_solve(const ExxArgs& a, int pid, Team& tm, float* pl, const TeamIO& cc,
+                                           const TeamIO& ph, double* r64) {
+    const DevCell& C = a.cells[a.pair_cell[pid]];
+    const double ih2 = 1.0 / (C.h[0] * C.h[0]);
+    SW<float> w = make_sw<float>(ih2);
+#pragma unroll
+    for (int k = 0; k < 7; ++k) w.w[k] = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(w.w[k])));
+    const sea_pair P = a.pairs[pid];
+    const int nx = P.n[0], ny = P.n[1], nz = P.n[2];
+    const double* __restrict__ b = a.b + (size_t)pid * a.stride;
+    double* __restrict__ x = a.v + (size_t)pid * a.stride;
+    int tid = threadIdx.x;
+    const int z0 = TM_ZP * tm.g, nown = min(max(nz - z0, 0), TM_ZP);   // this workgroup's planes: z0 + [0, nown)
+    const double tol2 = Delta<float>::target * Delta<float>::target * a.rel_tol * a.rel_tol;
+    const bool lead = tm.g == 0 && threadIdx.x == 0;
+    auto msk = [&](int c) { return ((tid & 63) < nx && (tid >> 6) + TM_TY * c < ny) ? 1.0f : 0.0f; };
+    auto off = [&](int c, int z) { return (z0 + z) * PL + c * TM_TY * 64; };   // and the lane's column
+    // Uniform values that each unrolled part takes anew: kept across the
+    // iterations, the offsets and conditions of all points (and, through their
+    // spills, vector registers) would be held throughout.
+    // A value that is computed where it stands (the compiler would otherwise
+    // load everything of a sweep first and do the sums in the reduction).
+    auto here = [](auto& v) { asm volatile("" : "+v"(v)); };
+    auto fresh = [](int v) {
+        asm volatile("" : "+s"(v));
+        return v;
+    };
+    float* const own = pl + threadIdx.x + SEA_HALO * LW;   // + z LH LW + TM_TY c LW
+    float r[TM_C][TM_ZP], ap[TM_C][TM_ZP];
+
+    // r64 -= A c and x += c in FP64 (c of the whole domain in memory); |r64|^2
+    auto refresh = [&](double& out) -> bool {
+        asm volatile("" : "+v"(tid));
+        if (!tm.sync()) return false;   // every workgroup's c
+        const SW<double> wd = make_sw<double>(ih2);
+        double uacc = 0.0;
+#pragma unroll
+        for (int c = 0; c < TM_C; ++c) {
+            const int y = (tid >> 6) + TM_TY * c;
+#pragma unroll 1
+            for (int z = 0; z < nown; ++z) {
+                const int q = off(c, z) + tid;
+                const float ctr = cc.at(q);
+                double s = wd.w[0] * (double)ctr;
+                float u = ctr, d = ctr;
+#pragma unroll
+                for (int k = 1; k <= SEA_HALO; ++k) {
+                    u = wshl1(u);
+                    d = wshr1(d);
+                    // rows and planes outside: read at the point itself, taken as zero
+                    const bool yu = y + k < 64, yd = y - k >= 0, zu = z0 + z + k < nz, zd = z0 + z - k >= 0;
+                    const float yp = cc.at(q + (yu ? k * 64 : 0)), ym = cc.at(q - (yd ? k * 64 : 0));
+                    const float zp = cc.at(q + (zu ? k * PL : 0)), zm = cc.at(q - (zd ? k * PL : 0));
+                    s += wd.w[k] * (((double)u + (double)d) + ((double)(yu ? yp : 0.0f) + (double)(yd ? ym : 0.0f)) +
+                                    ((double)(zu ? zp : 0.0f) + (double)(zd ? zm : 0.0f)));
+                }
+                const double rn = (double)msk(c) * (r64[tid + off(c, z)] - s);
+                r64[tid + off(c, z)] = rn;
+                uacc += rn * rn;
+                if (msk(c) != 0.0f) x[((z0 + z) * ny + y) * nx + (tid & 63)] += (double)ctr;
+            }
+        }
+        return tm.sum(uacc, out);
+    };
+    // inner state from r64: r = (float) r64, c = 0; |r|^2
+    auto reset = [&](bool zero_p, double& out) -> bool {
+        asm volatile("" : "+v"(tid));
+        double uacc = 0.0;
+#pragma unroll
+        for (int c = 0; c < TM_C; ++c) {
+            const int o = fresh(off(c, 0));
+#pragma unroll
+            for (int z = 0; z < TM_ZP; ++z) {
+                r[c][z] = (float)r64[tid + o + z * PL];
+                cc.st(o + z * PL, 0.0f);
+                uacc += (double)r[c][z] * (double)r[c][z];
+                here(r[c][z]);
+                here(uacc);
+                if (zero_p) own[z * (LH * LW) + TM_TY * c * LW] = 0.0f;
+            }
+        }
+        return tm.sum(uacc, out);
+    };
+
+    const bool sres = a.x_nonzero && a.start_res, fold = a.x_nonzero && !a.start_res;
+    if (sres && a.rnorm) {
+        double b2, q2;
+        if (start_meets_target(a, pid, tol2, b2, q2)) {
+            if (lead) {
+                a.stats[pid].iters = 0;
+                a.stats[pid].converged = 1;
+                a.stats[pid].rel_res = b2 > 0.0 ? sqrt(q2 / b2) : 0.0;
+                hist_put(a, pid, 0, q2, b2);
+            }
+            return true;
+        }
+    }
+    const double* __restrict__ br = sres ? a.bres + (size_t)pid * a.stride : nullptr;
+    double bb = 0.0, r2 = 0.0;
+    {
+        double bacc = 0.0, racc = 0.0;
+#pragma unroll
+        for (int c = 0; c < TM_C; ++c) {
+#pragma unroll 1
+            for (int z = 0; z < TM_ZP; ++z) {
+                double rv = 0.0;
+                float c0 = 0.0f;
+                if (z < nown && msk(c) != 0.0f) {
+                    const int id = ((z0 + z) * ny + (tid >> 6) + TM_TY * c) * nx + (tid & 63);
+                    const double bv = b[id];
+                    bacc += bv * bv;
+                    rv = sres ? br[id] : bv;
+                    if (fold) c0 = (float)x[id];
+                    if (!sres) x[id] = 0.0;
+                }
+                r64[tid + off(c, z)] = rv;
+                if (fold) cc.st(off(c, z), c0);
+                racc += rv * rv;
+            }
+        }
+        if (!tm.sum(bacc, bb) || !tm.sum(racc, r2)) return false;
+    }
+    if (fold && !refresh(r2)) return false;
+
+    int it = 0, conv = 0;
+    double rho = 0.0, rupd = r2;
+    float beta = 0.0f;
+    if (lead) hist_put(a, pid, 0, r2, bb);
+    if (!(r2 == r2) || !(bb == bb)) conv = -1;
+    else if (r2 <= tol2 * bb) conv = 1;
+    else if (a.max_iter <= 0) conv = 0;
+    else if (!reset(true, rho)) return false;
+    while (conv == 0 && rho > 0.0) {
+        // p = r + beta p, its planes out to the neighbours
+#pragma unroll
+        for (int c = 0; c < TM_C; ++c) {
+            const int o = fresh(off(c, 0));
+#pragma unroll
+            for (int z = 0; z < TM_ZP; ++z) {
+                float* q = own + z * (LH * LW) + TM_TY * c * LW;
+                const float pn = r[c][z] + beta * *q;
+                *q = pn;
+                ph.st(o + z * PL, pn);
+            }
+        }
+        tm.publish();
+        if (!tm.wait(max(tm.g - 1, 0), min(tm.g + 1, TM_G - 1))) return false;
+        // A p and <p, A p>, a column at a time, the next column's halo planes on
+        // the way; planes outside the team's are read at an own plane and taken
+        // as zero (planes past the domain within them are zero)
+        float hl[SEA_HALO], hu[SEA_HALO];
+        auto halo = [&](int c) {
+            const int o = fresh(off(c, 0));
+#pragma unroll
+            for (int k = 0; k < SEA_HALO; ++k) {
+                hl[k] = ph.ld(o + (tm.g > 0 ? (k - SEA_HALO) * PL : 0));
+                hu[k] = ph.ld(o + (tm.g < TM_G - 1 ? (TM_ZP + k) * PL : 0));
+            }
+        };
+        halo(0);
+        double dacc = 0.0;
+#pragma unroll
+        for (int c = 0; c < TM_C; ++c) {
+            __builtin_amdgcn_sched_barrier(0);
+            float q[TM_ZP + 2 * SEA_HALO];
+#pragma unroll
+            for (int k = 0; k < SEA_HALO; ++k) {
+                q[k] = tm.g > 0 ? hl[k] : 0.0f;
+                q[SEA_HALO + TM_ZP + k] = tm.g < TM_G - 1 ? hu[k] : 0.0f;
+            }
+            if (c + 1 < TM_C) halo(c + 1);
+#pragma unroll
+            for (int z = 0; z < TM_ZP; ++z) q[SEA_HALO + z] = own[z * (LH * LW) + TM_TY * c * LW];
+#pragma unroll
+            for (int z = 0; z < TM_ZP; ++z) {
+                __builtin_amdgcn_sched_barrier(0);
+                const float* row = own + z * (LH * LW) + TM_TY * c * LW;
+                const float ctr = q[SEA_HALO + z];
+                float s = w.w[0] * ctr;
+                float u = ctr, d = ctr;
+#pragma unroll
+                for (int k = 1; k <= SEA_HALO; ++k) {
+                    u = wshl1(u);
+                    d = wshr1(d);
+                    s += w.w[k] *
+                         ((u + d) + (row[k * LW] + row[-k * LW]) + (q[SEA_HALO + z + k] + q[SEA_HALO + z - k]));
+                }
+                ap[c][z] = s;
+                dacc += (double)ctr * (double)s;
+                here(ap[c][z]);
+                here(dacc);
+            }
+        }
+        tm.begin(dacc);
+        float cv[TM_C][TM_ZP];
+#pragma unroll
+        for (int c = 0; c < TM_C; ++c) {
+            const int o = fresh(off(c, 0));
+#pragma unroll
+            for (int z = 0; z < TM_ZP; ++z) cv[c][z] = cc.ld(o + z * PL);
+        }
+        double pAp;
+        if (!tm.end(pAp)) return false;
+        const float al = (float)(rho / pAp);
+        asm volatile("" : "+v"(tid));
+        // r -= alpha A p, <r, r>; c += alpha p
+        double racc = 0.0;
+#pragma unroll
+        for (int c = 0; c < TM_C; ++c) {
+            const int no = fresh(nown);
+            const float m = msk(c);
+#pragma unroll
+            for (int z = 0; z < TM_ZP; ++z) {
+                const float rn = (z < no ? m : 0.0f) * (r[c][z] - al * ap[c][z]);
+                r[c][z] = rn;
+                racc += (double)rn * (double)rn;
+                here(r[c][z]);
+                here(racc);
+            }
+        }
+        tm.begin(racc);
+#pragma unroll
+        for (int c = 0; c < TM_C; ++c) {
+            const int o = fresh(off(c, 0));
+#pragma unroll
+            for (int z = 0; z < TM_ZP; ++z) cc.st(o + z * PL, cv[c][z] + al * own[z * (LH * LW) + TM_TY * c * LW]);
+        }
+        double rn2;
+        if (!tm.end(rn2)) return false;
+        ++it;
+        if (lead) hist_put(a, pid, it, rn2, bb);
+        const bool nan = !(rn2 == rn2);
+        if (!nan && rn2 > tol2 * bb && rn2 > Delta<float>::v2 * rupd && it < a.max_iter) {
+            beta = (float)(rn2 / rho);
+            rho = rn2;
+            continue;
+        }
+        // reliable update in FP64: r64 -= A c, x += c
+        if (!refresh(r2)) return false;
+        if (!(r2 == r2)) { conv = -1; break; }
+        if (r2 <= tol2 * bb) { conv = 1; break; }
+        if (it >= a.max_iter) break;
+        // continue the same Krylov process from the replaced residual
+        double r2t;
+        if (!reset(false, r2t)) return false;
+        beta = (float)(r2t / rho);
+        rho = r2t;
+        rupd = r2;
+    }
+    if (lead) {
+        a.stats[pid].iters = it;
+        a.stats[pid].converged = conv;
+        a.stats[pid].rel_res = bb > 0.0 ? sqrt(r2 / bb) : 0.0;
+    }
+    return true;
+}
+
+// Workgroup k: XCD k mod 8; of that XCD's sequence, eight at a time are a team.
+__global__ __launch_bounds__(TM_NT) void k_cg_team(ExxArgs a, char* ctl, int n_teams) {
+    extern __shared__ unsigned char smem[];
+    float* pl = reinterpret_cast<float*>(smem);
+    __shared__ double red[TM_NT / 64];
+    __shared__ double tot;
+    __shared__ int fail;
+    const int xcd = blockIdx.x % RZ_XCD, seq = blockIdx.x / RZ_XCD;
+    const int team = (seq / TM_G) * RZ_XCD + xcd;
+    if (team >= n_teams) return;
+    Team tm{reinterpret_cast<TeamCtl*>(ctl + (size_t)team * CG_TEAM_CTL), seq % TM_G};
+    tm.red = red;
+    tm.tot = &tot;
+    tm.fail = &fail;
+    if (threadIdx.x == 0) fail = 0;
+    for (int i = threadIdx.x; i < TM_ZP * LW * LH; i += TM_NT) pl[i] = 0.0f;
+    // the team's slot: c, the exported p (floats), r64, 64 planes each (CG_TEAM_SLOT)
+    constexpr int planes = TM_G * TM_ZP * PL;
+    float* fs = reinterpret_cast<float*>(a.slots + (size_t)team * 4 * a.slot_stride);
+    const TeamIO cc(fs, planes, threadIdx.x), ph(fs + planes, planes, threadIdx.x);
+    double* r64 = a.slots + (size_t)team * 4 * a.slot_stride + planes;
+    int* queue = reinterpret_cast<int*>(ctl + (size_t)n_teams * CG_TEAM_CTL);
+    for (int turn = 0;; turn ^= 1) {
+        if (tm.g == 0 && threadIdx.x == 0)
+            st_dev(&tm.ctl->pid[turn], atomicAdd(queue, 1));
+        if (!tm.sync()) break;
+        const int qi = ld_dev(&tm.ctl->pid[turn]);
+        if (qi >= a.n_pairs) break;
+        const int pid = a.order ? a.order[qi] : qi;   // largest domains first
+        if (!cg_team_takes(a.pairs[pid])) continue;
+        if (!team_solve(a, pid, tm, pl, cc, ph, r64)) {
+            if (threadIdx.x == 0) a.stats[pid].converged = -1;
+            break;
+        }
     }
 }
 
@@ -599,6 +1051,9 @@ bool cg_zm_fits(const sea_pair* pairs, int n_pairs, const double* h) {
     return true;
 }
 
+size_t cg_team_lds_bytes() { return (size_t)TM_ZP * LW * LH * sizeof(float); }
+int cg_teams(int n_cu) { return n_cu / TM_G; }
+
 size_t cg_zm_lds_bytes(int state_f32) { return (size_t)2 * LW * LH * (state_f32 ? sizeof(float) : sizeof(double)); }
 
 // b - A x0 for a start guess x0 (FP64), one workgroup per pair.
@@ -630,7 +1085,6 @@ __global__ __launch_bounds__(FIN_BS) void k_start_residual(ExxArgs a) {
 constexpr int RZ_NT = 1024;
 constexpr int RZ_ROWS = 16;   // rows owned per workgroup: one per wavefront
 constexpr int RZ_WR = RZ_ROWS + 2 * SEA_HALO;   // rows of the window
-constexpr int RZ_XCD = 8;
 #ifndef SEA_RZ_PRE
 #define SEA_RZ_PRE 2
 #endif
@@ -1418,5 +1872,17 @@ hipError_t launch_cg_zm(const ExxArgs& a, int variant, hipStream_t s) {
     hipError_t e = hipFuncSetAttribute((const void*)v.fn, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(v.fn, dim3(a.n_slots), dim3(v.nt), lds, s, a);
+    return hipGetLastError();
+}
+
+hipError_t launch_cg_team(const ExxArgs& a, int n_eligible, char* ctl, int n_cu, hipStream_t s) {
+    const int lds = (int)cg_team_lds_bytes();
+    const int teams = std::min(std::min(cg_teams(n_cu), n_eligible), a.n_slots);
+    hipError_t e = hipFuncSetAttribute((const void*)k_cg_team, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    if (e != hipSuccess) return e;
+    e = launch_fill_int((int*)ctl, ((size_t)teams * CG_TEAM_CTL + sizeof(int)) / sizeof(int), s);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_cg_team, dim3((teams + RZ_XCD - 1) / RZ_XCD * RZ_XCD * TM_G), dim3(TM_NT), lds, s, a, ctl,
+                       teams);
     return hipGetLastError();
 }

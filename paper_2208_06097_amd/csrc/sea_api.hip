@@ -304,6 +304,10 @@ ExxLayout exx_layout(const sea_ctx* ctx, const CellSet& S, bool with_v, bool eag
     L.cg_done = tiled64 ? take(np * sizeof(int)) : 0;
     L.cg_active = tiled64 ? take(((size_t)ctx->opts.max_iter + 1) * sizeof(int)) : 0;
     L.refine = refine ? take((REFINE_MAX + 1) * (np + 1) * sizeof(int)) : 0;   // counts, then lists
+    if (ctx->opts.stencil_dtype == SEA_F32 && !refine) {
+        L.team = take(cg_teams(ctx->n_cu) * CG_TEAM_CTL + sizeof(int));
+        L.slot_stride = std::max(L.slot_stride, CG_TEAM_SLOT);
+    }
     L.epart = take(np * (size_t)L.ep_stride * sizeof(double));
     L.slots = take((size_t)L.n_slots * 4 * L.slot_stride * sizeof(double));
     L.stats = take(np * sizeof(DevStat));
@@ -775,7 +779,14 @@ static sea_status exx_enqueue(sea_ctx* ctx, const CellSet& S, const ExxLayout& L
             // norms decide first, and bres is only there for the pairs they fail)
             az.start_res = ctx->opts.start == SEA_START_SPECTRAL ? 1 : 0;
             az.rnorm = (az.start_res && residual_zm_lds_bytes() <= ctx->max_lds) ? (double*)(base + Ly.rnorm) : nullptr;
-            SEA_HIP_CHECK(ctx, launch_cg_zm(az, var, s));
+            // without a chosen variant, teams of workgroups take the domains that fit them
+            int n_team = 0;
+            if (ctx->opts.cg_variant < 0 && ctx->cg_tuned < 0 && cg_teams(ctx->n_cu) > 0 &&
+                cg_team_lds_bytes() + 1024 <= ctx->max_lds)
+                for (const auto& p : S.pairs) n_team += cg_team_takes(p);
+            az.team = n_team > 0;
+            if (n_team) SEA_HIP_CHECK(ctx, launch_cg_team(az, n_team, base + Ly.team, ctx->n_cu, s));
+            if (n_team < n_pairs) SEA_HIP_CHECK(ctx, launch_cg_zm(az, var, s));
             timer_off(SEA_STAGE_CG);
             if (!f.action) {
                 timer_on(SEA_STAGE_FINISH);

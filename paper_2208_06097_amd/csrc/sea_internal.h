@@ -74,7 +74,7 @@ struct StageTimer {
 struct ExxLayout {
     size_t pairs, pair_cell, order, dbox, cells, partial, mom, b, v, bres, slots, stats, csr_off, csr_ent, scal, counter;
     size_t nnx, nny, nnact, dst_tmp, dst_tab, dst_mu, rnorm, racah_tab, mpoly, epart, cg_r, cg_p, cg_ap, cg_part,
-        cg_rho, cg_done, cg_active, refine, sc_work, total;
+        cg_rho, cg_done, cg_active, refine, sc_work, team, total;
     int nmax;
     int ep_stride;        // pair-energy partial slots per pair (scatter)
     int n_chunks;
@@ -129,6 +129,7 @@ struct ExxArgs {
     double xc_beta_min;   // paired-update CG: smallest beta for recovering a pending step
     int max_iter;
     int lmax;
+    int team;             // FP32 z-march: leave the pairs that the teams take
     int* queue_ctr;       // persistent-kernel pair counter (zeroed before the CG launch)
     const int* order;     // CG queue order: pair ids by decreasing domain size (nullable)
     const int* dbox;      // per pair 12 ints: boxes where W_i and W_j take the pair
@@ -355,6 +356,22 @@ __device__ __forceinline__ void lds_sync() { asm volatile("s_waitcnt lgkmcnt(0)\
 // z-marching CG (k_cg.hip): needs every pair with n[0], n[1] <= 64.
 bool cg_zm_fits(const sea_pair* pairs, int n_pairs, const double* h);
 size_t cg_zm_lds_bytes(int state_f32);
+// FP32 CG by teams of workgroups (k_cg.hip): domains of up to 64 points an axis,
+// from the size on where a team is the faster form for long pair lists too (the
+// line lies with the domain alone, so that a pair's result does not depend on its
+// batch): 1000 pairs of 40^3 307 ms by the z-march and about 340 by teams, of 50^3
+// 455 and 420, 300 pairs of 63^3 288 and 158.
+constexpr int CG_TEAM_MAX = 64, CG_TEAM_MIN_PTS = 90000;
+constexpr size_t CG_TEAM_CTL = 2048;            // bytes of a team's control block
+constexpr size_t CG_TEAM_SLOT = 32 * 64 * 64;   // least slot_stride: c, p (FP32) and r64 of 64 planes in four of them
+__host__ __device__ inline bool cg_team_takes(const sea_pair& P) {
+    return P.n[0] <= CG_TEAM_MAX && P.n[1] <= CG_TEAM_MAX && P.n[2] <= CG_TEAM_MAX &&
+           P.n[0] * P.n[1] * P.n[2] >= CG_TEAM_MIN_PTS;
+}
+size_t cg_team_lds_bytes();
+int cg_teams(int n_cu);   // teams that run at once
+// ctl: cg_teams(n_cu) control blocks and the queue's counter (cleared here)
+hipError_t launch_cg_team(const ExxArgs& a, int n_eligible, char* ctl, int n_cu, hipStream_t s);
 // part: eps_marginals_part_doubles(N, n_occ) of scratch
 size_t eps_marginals_part_doubles(const int* N, int n_occ);
 hipError_t launch_eps_marginals(const void* phi, int f32, const int* N, int n_occ, int nmax, double* m, double* part,

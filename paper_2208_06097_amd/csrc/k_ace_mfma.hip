@@ -161,6 +161,10 @@ __device__ __forceinline__ typename Kind<KIND>::Vec to_vec(const Chunk<T, Kind<K
 // (9 KB per 32 rows) holds, up to four.  An FP64 block of 128 x 128 has 128
 // accumulator registers a lane and fits twice.
 constexpr int nt_minb(int P, int Q) { return P + Q <= 4 ? 4 : P + Q <= 5 ? 3 : 2; }
+// Stages in flight in registers beside the two in LDS.  Large BF16 blocks wait for
+// their loads (59% of the wavefronts' time with one); a large FP64 or FP32 block
+// has no registers left for a second and small blocks gain nothing.
+constexpr int nt_ahead(int kind, int P, int Q) { return kind == ACE_BF16 && P * Q > 4 ? 2 : 1; }
 
 template <int KIND, typename TA, typename TB, int P, int Q>
 __global__ __launch_bounds__(NT, nt_minb(P, Q)) void k_nt_mfma(const TA* __restrict__ A, const TB* __restrict__ B,
@@ -201,33 +205,34 @@ __global__ __launch_bounds__(NT, nt_minb(P, Q)) void k_nt_mfma(const TA* __restr
     for (int e = 0; e < P; ++e) pa[e] = A + (size_t)min(i0 + cr + 32 * e, m - 1) * K + ck;
 #pragma unroll
     for (int e = 0; e < Q; ++e) pb[e] = B + (size_t)min(j0 + cr + 32 * e, n - 1) * K + ck;
-    Chunk<TA, CE> ra[P];
-    Chunk<TB, CE> rb[Q];
-    auto load = [&](long k0) {
+    constexpr int AH = nt_ahead(KIND, P, Q);
+    Chunk<TA, CE> ra[AH][P];
+    Chunk<TB, CE> rb[AH][Q];
+    auto load = [&](int slot, long k0) {
         if (k0 + KT <= ke) {
 #pragma unroll
-            for (int e = 0; e < P; ++e) ra[e] = load_chunk<CE>(pa[e] + k0);
+            for (int e = 0; e < P; ++e) ra[slot][e] = load_chunk<CE>(pa[e] + k0);
 #pragma unroll
-            for (int e = 0; e < Q; ++e) rb[e] = load_chunk<CE>(pb[e] + k0);
+            for (int e = 0; e < Q; ++e) rb[slot][e] = load_chunk<CE>(pb[e] + k0);
         } else {
             const int kl = (int)(ke - k0) - ck;   // values of this thread's chunk inside
 #pragma unroll
             for (int e = 0; e < P; ++e)
 #pragma unroll
-                for (int i = 0; i < CE; ++i) ra[e].v[i] = i < kl ? pa[e][k0 + i] : TA(0);
+                for (int i = 0; i < CE; ++i) ra[slot][e].v[i] = i < kl ? pa[e][k0 + i] : TA(0);
 #pragma unroll
             for (int e = 0; e < Q; ++e)
 #pragma unroll
-                for (int i = 0; i < CE; ++i) rb[e].v[i] = i < kl ? pb[e][k0 + i] : TB(0);
+                for (int i = 0; i < CE; ++i) rb[slot][e].v[i] = i < kl ? pb[e][k0 + i] : TB(0);
         }
     };
-    auto stage = [&](int buf) {
+    auto stage = [&](int slot, int buf) {
 #pragma unroll
         for (int e = 0; e < P; ++e)
-            *reinterpret_cast<Vec*>(&As[buf][(cr + 32 * e) * PITCH + ck]) = to_vec<KIND, TA>(ra[e]);
+            *reinterpret_cast<Vec*>(&As[buf][(cr + 32 * e) * PITCH + ck]) = to_vec<KIND, TA>(ra[slot][e]);
 #pragma unroll
         for (int e = 0; e < Q; ++e)
-            *reinterpret_cast<Vec*>(&Bs[buf][(cr + 32 * e) * PITCH + ck]) = to_vec<KIND, TB>(rb[e]);
+            *reinterpret_cast<Vec*>(&Bs[buf][(cr + 32 * e) * PITCH + ck]) = to_vec<KIND, TB>(rb[slot][e]);
     };
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int wm = wave >> 1, wn = wave & 1;
@@ -247,19 +252,43 @@ __global__ __launch_bounds__(NT, nt_minb(P, Q)) void k_nt_mfma(const TA* __restr
 #pragma unroll
                 for (int q = 0; q < Q; ++q) acc[p][q] = Kd::mma(a[p], b[q], s, acc[p][q]);
     };
-    if (kb < ke) {
-        load(kb);
-        stage(0);
-        if (kb + KT < ke) load(kb + KT);
+    if constexpr (AH == 1) {
+        if (kb < ke) {
+            load(0, kb);
+            stage(0, 0);
+            if (kb + KT < ke) load(0, kb + KT);
+            lds_sync();
+            int buf = 0;
+            for (long k0 = kb; k0 < ke; k0 += KT) {
+                mma(buf, 0);
+                if (k0 + KT < ke) stage(0, buf ^ 1);
+                if (k0 + 2 * KT < ke) load(0, k0 + 2 * KT);
+                mma(buf, 1);
+                lds_sync();   // the loads in flight cross it
+                buf ^= 1;
+            }
+        }
+    } else if (kb < ke) {
+        load(0, kb);
+        stage(0, 0);
+#pragma unroll
+        for (int u = 0; u < AH; ++u)
+            if (kb + (u + 1) * KT < ke) load(u, kb + (u + 1) * KT);
         lds_sync();
+        // stage i: slot (i - 1) % AH holds stage i once stage i - 1 is multiplied
         int buf = 0;
-        for (long k0 = kb; k0 < ke; k0 += KT) {
-            mma(buf, 0);
-            if (k0 + KT < ke) stage(buf ^ 1);
-            if (k0 + 2 * KT < ke) load(k0 + 2 * KT);
-            mma(buf, 1);
-            lds_sync();   // the loads in flight cross it
-            buf ^= 1;
+        for (long k0 = kb; k0 < ke; k0 += AH * KT) {
+#pragma unroll
+            for (int u = 0; u < AH; ++u) {
+                const long k = k0 + u * KT;
+                if (u > 0 && k >= ke) break;
+                mma(buf, 0);
+                if (k + KT < ke) stage(u, buf ^ 1);
+                if (k + (AH + 1) * KT < ke) load(u, k + (AH + 1) * KT);
+                mma(buf, 1);
+                lds_sync();   // the loads in flight cross it
+                buf ^= 1;
+            }
         }
     }
     double* Pt = part + (size_t)slice * m * n;
@@ -334,6 +363,10 @@ struct NN {
     static constexpr int ROWS = NT / CH;                      // A rows of one pass of the threads
 };
 constexpr int nn_minb(int P) { return P <= 2 ? 3 : 2; }
+// Stages of B in flight in registers: BF16 operands with the coefficients resident
+// are bound by them (FP64 and FP32 gain nothing).
+template <int KIND, typename TB>
+constexpr int nn_ahead(bool res) { return res && KIND == ACE_BF16 && sizeof(TB) == 2 ? 4 : 1; }
 
 template <int KIND, typename TB, typename TC, int P, bool RES, bool LOWER>
 __global__ __launch_bounds__(NT, nn_minb(P)) void k_nn_mfma(const double* __restrict__ A, long sai, long sak,
@@ -401,31 +434,33 @@ __global__ __launch_bounds__(NT, nn_minb(P)) void k_nn_mfma(const double* __rest
     const int br = KIND == ACE_BF16 ? 4 * (threadIdx.x / (BN / CB)) : threadIdx.x / (BN / CB);
     constexpr int BSTEP = KIND == ACE_BF16 ? 1 : NT / (BN / CB);
     static_assert(KIND == ACE_BF16 ? 4 * NT / (BN / CB) == KT : RB * BSTEP == KT, "B stage");
-    Chunk<TB, CB> rb[RB];
-    auto load_b = [&](long jt, int st) {
+    constexpr int AH = nn_ahead<KIND, TB>(RES);
+    Chunk<TB, CB> rb[AH][RB];
+    auto load_b = [&](int slot, long jt, int st) {
         const long j0 = jt * BN + bc;
         const int k0 = st * KT + br;
         if ((st + 1) * KT <= K && (jt + 1) * BN <= ncol) {
             const TB* b = B + (size_t)k0 * ncol + j0;
 #pragma unroll
-            for (int e = 0; e < RB; ++e) rb[e] = load_chunk<CB>(b + (size_t)(e * BSTEP) * ncol);
+            for (int e = 0; e < RB; ++e) rb[slot][e] = load_chunk<CB>(b + (size_t)(e * BSTEP) * ncol);
         } else {
 #pragma unroll
             for (int e = 0; e < RB; ++e)
 #pragma unroll
                 for (int i = 0; i < CB; ++i)
-                    rb[e].v[i] = (k0 + e * BSTEP < K && j0 + i < ncol) ? B[(size_t)(k0 + e * BSTEP) * ncol + j0 + i]
-                                                                       : TB(0);
+                    rb[slot][e].v[i] = (k0 + e * BSTEP < K && j0 + i < ncol)
+                                           ? B[(size_t)(k0 + e * BSTEP) * ncol + j0 + i]
+                                           : TB(0);
         }
     };
-    auto stage_b = [&](int buf) {
+    auto stage_b = [&](int slot, int buf) {
         E* dst = Bs + buf * S::B_ELEMS;
         if constexpr (KIND == ACE_BF16) {
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 Chunk<E, 4> w;
 #pragma unroll
-                for (int e = 0; e < 4; ++e) w.v[e] = Kd::cvt(rb[e].v[i]);
+                for (int e = 0; e < 4; ++e) w.v[e] = Kd::cvt(rb[slot][e].v[i]);
                 const int row = (bc & 64) + i * 16 + ((bc & 63) >> 2);
                 __builtin_memcpy(__builtin_assume_aligned(&dst[row * PITCH + br], 8), &w, 8);
             }
@@ -434,7 +469,7 @@ __global__ __launch_bounds__(NT, nn_minb(P)) void k_nn_mfma(const double* __rest
             for (int e = 0; e < RB; ++e) {
                 Vec v;
 #pragma unroll
-                for (int i = 0; i < CB; ++i) v[i] = Kd::cvt(rb[e].v[i]);
+                for (int i = 0; i < CB; ++i) v[i] = Kd::cvt(rb[slot][e].v[i]);
                 *reinterpret_cast<Vec*>(&dst[(br + e * BSTEP) * BN + bc]) = v;
             }
         }
@@ -522,33 +557,59 @@ __global__ __launch_bounds__(NT, nn_minb(P)) void k_nn_mfma(const double* __rest
             load_a(cur.ib, st);
             stage_a(As + st * AST);
         }
-    auto load = [&](It it) {
+    auto load = [&](int slot, It it) {
         if (!RES) load_a(it.ib, it.st);
-        load_b(it.jt, it.st);
+        load_b(slot, it.jt, it.st);
     };
-    auto stage = [&](int buf) {
+    auto stage = [&](int slot, int buf) {
         if (!RES) stage_a(As + buf * AST);
-        stage_b(buf);
+        stage_b(slot, buf);
     };
+    load(0, cur);
+    stage(0, 0);
     It n1 = next(cur);
-    load(cur);
-    stage(0);
-    if (n1.jt < ntile) load(n1);
-    lds_sync();
-    for (int buf = 0;; buf ^= 1) {
-        const It n2 = next(n1);
-        const E* a_st = As + (RES ? cur.st : buf) * AST;
-        if (S::CH == 8) mma(a_st, buf, 0);
-        if (n1.jt < ntile) {
-            stage(buf ^ 1);
-            if (n2.jt < ntile) load(n2);
+    if constexpr (AH == 1) {
+        if (n1.jt < ntile) load(0, n1);
+        lds_sync();
+        for (int buf = 0;; buf ^= 1) {
+            const It n2 = next(n1);
+            const E* a_st = As + (RES ? cur.st : buf) * AST;
+            if (S::CH == 8) mma(a_st, buf, 0);
+            if (n1.jt < ntile) {
+                stage(0, buf ^ 1);
+                if (n2.jt < ntile) load(0, n2);
+            }
+            mma(a_st, buf, S::CH == 8 ? 1 : 0);
+            if (n1.st == 0) store(cur);
+            if (n1.jt >= ntile) return;
+            lds_sync();   // the loads in flight cross it
+            cur = n1;
+            n1 = n2;
         }
-        mma(a_st, buf, S::CH == 8 ? 1 : 0);
-        if (n1.st == 0) store(cur);
-        if (n1.jt >= ntile) break;
-        lds_sync();   // the loads in flight cross it
-        cur = n1;
-        n1 = n2;
+    }
+    It ahead = n1;   // the next stage to load
+#pragma unroll
+    for (int u = 0; u < AH; ++u) {
+        if (ahead.jt < ntile) load(u, ahead);
+        ahead = next(ahead);
+    }
+    lds_sync();
+    for (int buf = 0;;) {
+#pragma unroll
+        for (int u = 0; u < AH; ++u) {   // slot u holds n1
+            const E* a_st = As + (RES ? cur.st : buf) * AST;
+            if (S::CH == 8) mma(a_st, buf, 0);
+            if (n1.jt < ntile) stage(u, buf ^ 1);
+            if (ahead.jt < ntile) load(u, ahead);
+            mma(a_st, buf, S::CH == 8 ? 1 : 0);
+            if (n1.st == 0) store(cur);
+            if (n1.jt >= ntile) return;
+            lds_sync();   // the loads in flight cross it
+            cur = n1;
+            n1 = next(n1);
+            ahead = next(ahead);
+            buf ^= 1;
+        }
     }
 }
 

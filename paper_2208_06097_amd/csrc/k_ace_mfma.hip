@@ -31,7 +31,7 @@
 // reading their operands and large ones by the matrix cores.  Measured, against
 // 128 x 128 blocks throughout with element-wise staging between two barriers:
 // FP64 32 x 32 x 216000 320 -> 22 us (5.0 TB/s), 256 x 256 x 1728000 4.19 ->
-// 3.87 ms (58 TFLOP/s); FP32 NN 256 x 256 x 1728000 2.66 -> 2.21 ms, its
+// 3.45 ms (66 TFLOP/s); FP32 NN 256 x 256 x 1728000 2.66 -> 2.21 ms, its
 // triangular form 2.80 -> 1.86 ms; BF16 NN 200 x 152 x 1030301 0.63 -> 0.43 ms.
 // Operand lanes: A row = lane % 16, B column = lane % 16, k block = lane / 16.
 // Result lanes: column = lane % 16; the row of item v is 4 (lane / 16) + v
@@ -208,12 +208,15 @@ __global__ __launch_bounds__(NT, nt_minb(P, Q)) void k_nt_mfma(const TA* __restr
     constexpr int AH = nt_ahead(KIND, P, Q);
     Chunk<TA, CE> ra[AH][P];
     Chunk<TB, CE> rb[AH][Q];
+    auto load_whole = [&](long k0, int slot = 0) {
+#pragma unroll
+        for (int e = 0; e < P; ++e) ra[slot][e] = load_chunk<CE>(pa[e] + k0);
+#pragma unroll
+        for (int e = 0; e < Q; ++e) rb[slot][e] = load_chunk<CE>(pb[e] + k0);
+    };
     auto load = [&](int slot, long k0) {
         if (k0 + KT <= ke) {
-#pragma unroll
-            for (int e = 0; e < P; ++e) ra[slot][e] = load_chunk<CE>(pa[e] + k0);
-#pragma unroll
-            for (int e = 0; e < Q; ++e) rb[slot][e] = load_chunk<CE>(pb[e] + k0);
+            load_whole(k0, slot);
         } else {
             const int kl = (int)(ke - k0) - ck;   // values of this thread's chunk inside
 #pragma unroll
@@ -259,12 +262,35 @@ __global__ __launch_bounds__(NT, nt_minb(P, Q)) void k_nt_mfma(const TA* __restr
             if (kb + KT < ke) load(0, kb + KT);
             lds_sync();
             int buf = 0;
-            for (long k0 = kb; k0 < ke; k0 += KT) {
+            long k0 = kb;
+            // whole stages with two more behind them: no branches, and the LDS
+            // writes and loads dealt out between the matrix instructions (in one
+            // run they hold up the next operands' reads: FP64 256 x 256 x 1728000
+            // 3.87 -> 3.45 ms, 66 TFLOP/s)
+            for (; k0 + 3 * KT <= ke; k0 += KT) {
+                mma(buf, 0);
+                stage(0, buf ^ 1);
+                load_whole(k0 + 2 * KT);
+                mma(buf, 1);
+                constexpr int MM = P * Q * Kd::STEPS;   // of one half
+                __builtin_amdgcn_sched_group_barrier(0x100, P + Q, 0);   // first half's operands
+#pragma unroll
+                for (int e = 0; e < P + Q; ++e) {
+                    __builtin_amdgcn_sched_group_barrier(0x008, MM / (P + Q), 0);
+                    __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);
+                    __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+                }
+                __builtin_amdgcn_sched_group_barrier(0x100, P + Q, 0);
+                __builtin_amdgcn_sched_group_barrier(0x008, 2 * MM, 0);
+                lds_sync();   // the loads in flight cross it
+                buf ^= 1;
+            }
+            for (; k0 < ke; k0 += KT) {
                 mma(buf, 0);
                 if (k0 + KT < ke) stage(0, buf ^ 1);
                 if (k0 + 2 * KT < ke) load(0, k0 + 2 * KT);
                 mma(buf, 1);
-                lds_sync();   // the loads in flight cross it
+                lds_sync();
                 buf ^= 1;
             }
         }

@@ -380,6 +380,9 @@ __device__ __forceinline__ uint16_t store_as<uint16_t>(double v) { return f_to_b
 // LOWER: A(i, k) = 0 for k > i, and a row block stops at its last row's k;
 // a workgroup then takes the next row block with each tile, so that all do
 // the same work.
+//
+// FP32 256 x 256 x 1728000 2.66 -> 1.95 ms, FP64 4.46 -> 4.1 ms with the staging
+// dealt out inside the tiles.
 template <int KIND>
 struct NN {
     using Kd = Kind<KIND>;
@@ -433,14 +436,21 @@ __global__ __launch_bounds__(NT, nn_minb(P)) void k_nn_mfma(const double* __rest
     // repeat the last one, k past K are zeros
     const int ar = threadIdx.x / S::CH, ak = CE * (threadIdx.x % S::CH);
     Chunk<double, CE> ra[PA];
-    auto load_a = [&](int ib, int st) {
-        const int k0 = st * KT + ak;
+    auto a_at = [&](int ib, int st, int e) {
+        return A + (long)min(ib * TM + ar + S::ROWS * e, m - 1) * sai + (long)(st * KT + ak) * sak;
+    };
+    auto load_a_whole = [&](int ib, int st) {
 #pragma unroll
-        for (int e = 0; e < PA; ++e) {
-            const double* a = A + (long)min(ib * TM + ar + S::ROWS * e, m - 1) * sai + (long)k0 * sak;
-            if (sak == 1 && (st + 1) * KT <= K) {
-                ra[e] = load_chunk<CE>(a);
-            } else {
+        for (int e = 0; e < PA; ++e) ra[e] = load_chunk<CE>(a_at(ib, st, e));
+    };
+    auto load_a = [&](int ib, int st) {
+        if (sak == 1 && (st + 1) * KT <= K) {
+            load_a_whole(ib, st);
+        } else {
+            const int k0 = st * KT + ak;
+#pragma unroll
+            for (int e = 0; e < PA; ++e) {
+                const double* a = a_at(ib, st, e);
 #pragma unroll
                 for (int i = 0; i < CE; ++i) ra[e].v[i] = k0 + i < K ? a[i * sak] : 0.0;
             }
@@ -462,13 +472,16 @@ __global__ __launch_bounds__(NT, nn_minb(P)) void k_nn_mfma(const double* __rest
     static_assert(KIND == ACE_BF16 ? 4 * NT / (BN / CB) == KT : RB * BSTEP == KT, "B stage");
     constexpr int AH = nn_ahead<KIND, TB>(RES);
     Chunk<TB, CB> rb[AH][RB];
+    auto load_b_whole = [&](int slot, long jt, int st) {
+        const TB* b = B + (size_t)(st * KT + br) * ncol + jt * BN + bc;
+#pragma unroll
+        for (int e = 0; e < RB; ++e) rb[slot][e] = load_chunk<CB>(b + (size_t)(e * BSTEP) * ncol);
+    };
     auto load_b = [&](int slot, long jt, int st) {
         const long j0 = jt * BN + bc;
         const int k0 = st * KT + br;
         if ((st + 1) * KT <= K && (jt + 1) * BN <= ncol) {
-            const TB* b = B + (size_t)k0 * ncol + j0;
-#pragma unroll
-            for (int e = 0; e < RB; ++e) rb[slot][e] = load_chunk<CB>(b + (size_t)(e * BSTEP) * ncol);
+            load_b_whole(slot, jt, st);
         } else {
 #pragma unroll
             for (int e = 0; e < RB; ++e)
@@ -597,7 +610,37 @@ __global__ __launch_bounds__(NT, nn_minb(P)) void k_nn_mfma(const double* __rest
     if constexpr (AH == 1) {
         if (n1.jt < ntile) load(0, n1);
         lds_sync();
-        for (int buf = 0;; buf ^= 1) {
+        int buf = 0;
+        for (;;) {
+            // whole stages inside a column tile with two more behind them: no
+            // branches, and the LDS writes and loads dealt out between the matrix
+            // instructions (as in the NT product)
+            if constexpr (!RES && S::CH == 8) {
+                const bool tile_whole = sak == 1 && (cur.jt + 1) * BN <= ncol;
+                while (tile_whole && cur.st + 2 < stages(cur.ib) && (cur.st + 3) * KT <= K) {
+                    const E* a_st = As + buf * AST;
+                    mma(a_st, buf, 0);
+                    stage(0, buf ^ 1);
+                    load_a_whole(cur.ib, cur.st + 2);
+                    load_b_whole(0, cur.jt, cur.st + 2);
+                    mma(a_st, buf, 1);
+                    constexpr int MM = P * 4 * Kd::STEPS, NW = PA + RB;   // of one half; LDS writes
+                    constexpr int LD = KIND == ACE_F32 ? 2 : 1;           // loads per write
+                    __builtin_amdgcn_sched_group_barrier(0x100, P + 4, 0);   // first half's operands
+#pragma unroll
+                    for (int e = 0; e < NW; ++e) {
+                        __builtin_amdgcn_sched_group_barrier(0x008, MM / NW, 0);
+                        __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);
+                        __builtin_amdgcn_sched_group_barrier(0x020, LD, 0);
+                    }
+                    __builtin_amdgcn_sched_group_barrier(0x100, P + 4, 0);
+                    __builtin_amdgcn_sched_group_barrier(0x008, 2 * MM, 0);
+                    lds_sync();   // the loads in flight cross it
+                    ++cur.st;
+                    buf ^= 1;
+                }
+                n1 = next(cur);
+            }
             const It n2 = next(n1);
             const E* a_st = As + (RES ? cur.st : buf) * AST;
             if (S::CH == 8) mma(a_st, buf, 0);
@@ -611,6 +654,7 @@ __global__ __launch_bounds__(NT, nn_minb(P)) void k_nn_mfma(const double* __rest
             lds_sync();   // the loads in flight cross it
             cur = n1;
             n1 = n2;
+            buf ^= 1;
         }
     }
     It ahead = n1;   // the next stage to load

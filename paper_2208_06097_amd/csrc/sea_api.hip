@@ -1367,6 +1367,7 @@ extern "C" sea_status sea_scdm(sea_ctx* ctx, int64_t n_grid, int n_occ, const vo
     ctx->ev_used[SEA_STAGE_SCDM] = false;
     ctx->ev_used[SEA_STAGE_ROTATE] = false;
     int k = 0, fl = 0, rounds = 0;
+    const double* ut = nullptr;   // U^T (in the workspace)
     {
         StageTimer t(ctx, SEA_STAGE_SCDM, s);
         // Eq. 1: pivots, one pass over Phi^T per round
@@ -1417,11 +1418,12 @@ extern "C" sea_status sea_scdm(sea_ctx* ctx, int64_t n_grid, int n_occ, const vo
         if (!conv)
             return fail(ctx, SEA_E_RANK, "B = (Phi^T)_{:,C} too ill-conditioned: its polar factor did not converge");
         SEA_HIP_CHECK(ctx, ace_transpose(cur, n, U_dev, s));
+        ut = cur;
     }
     if (phi_loc_dev) {
         StageTimer t(ctx, SEA_STAGE_ROTATE, s);
-        // Eq. 6: phi_loc_k = sum_j phi_j U_jk
-        SEA_HIP_CHECK(ctx, rotate_rows(U_dev, 1, n, phi_dtype, n, Ng, phi_dev, phi_loc_dev, s));
+        // Eq. 6: phi_loc_k = sum_j phi_j U_jk, by the rows of U^T
+        SEA_HIP_CHECK(ctx, rotate_rows(ut, n, 1, phi_dtype, n, Ng, phi_dev, phi_loc_dev, s));
     }
     if (piv_host)
         SEA_HIP_CHECK(ctx, hipMemcpyAsync(piv_host, ws + L.piv.piv, (size_t)n * sizeof(int), hipMemcpyDeviceToHost, s));

@@ -92,7 +92,12 @@ typedef struct {
     sea_start start;        /* CG initial guess                                */
     int32_t cg_variant;     /* F32 state: z-march kernel variant; -1 = the     */
                             /* context's autotuned choice, else the default;  */
-                            /* 0..sea_cg_variant_count()-1 = that variant     */
+                            /* 0..sea_cg_variant_count()-1 = that variant.    */
+                            /* With -1, domains of 90000 points and more (up  */
+                            /* to 64 an axis) are solved by teams of          */
+                            /* workgroups, in the arithmetic of the variants  */
+                            /* without -xc, unless the tuned choice is an     */
+                            /* -xc variant                                    */
     int32_t profile;        /* non-zero: time each stage with HIP events       */
     sea_dtype nn_weight_dtype; /* learned start: network weights F32 or BF16   */
     void *hip_stream;       /* hipStream_t; NULL = default stream              */
@@ -312,8 +317,9 @@ sea_status sea_scatter_autotune(sea_ctx *ctx, int n_cells, const sea_cell *cells
  * |r_t| / |b| at hist_dev[k * (len + 1) + t] (FP64, device memory owned by
  * the caller, n_pairs * (len + 1) doubles, n_pairs of the call): t = 0 is
  * the start's true FP64 residual, t >= 1 the CG's recursive residual after
- * t iterations (FP32 z-march, FP64 row tiles and their preconditioned form;
- * the generic FP64 kernel records its exit only).  Entries after
+ * t iterations (FP32 z-march and teams, FP64 row tiles and small domains;
+ * the generic FP64 kernel records its exit only) or, with the spectral
+ * start's exact corrections, the true residual after t of them.  Entries after
  * a pair's last iteration are NaN.  hist_dev NULL or len < 0 turns the
  * recording off.  The buffer must hold the next calls' pairs; it is not
  * checked.  SEA_E_ARG for a negative len with a non-NULL buffer. */

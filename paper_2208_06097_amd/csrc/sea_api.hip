@@ -779,9 +779,11 @@ static sea_status exx_enqueue(sea_ctx* ctx, const CellSet& S, const ExxLayout& L
             // norms decide first, and bres is only there for the pairs they fail)
             az.start_res = ctx->opts.start == SEA_START_SPECTRAL ? 1 : 0;
             az.rnorm = (az.start_res && residual_zm_lds_bytes() <= ctx->max_lds) ? (double*)(base + Ly.rnorm) : nullptr;
-            // without a chosen variant, teams of workgroups take the domains that fit them
+            // teams of workgroups take the domains that fit them, unless the caller has
+            // fixed a variant or the autotuner chose one with paired iterate updates
+            // (which round c differently)
             int n_team = 0;
-            if (ctx->opts.cg_variant < 0 && ctx->cg_tuned < 0 && cg_teams(ctx->n_cu) > 0 &&
+            if (ctx->opts.cg_variant < 0 && !cg_variant_paired(ctx->cg_tuned) && cg_teams(ctx->n_cu) > 0 &&
                 cg_team_lds_bytes() + 1024 <= ctx->max_lds)
                 for (const auto& p : S.pairs) n_team += cg_team_takes(p);
             az.team = n_team > 0;

@@ -380,6 +380,7 @@ hipError_t launch_eps_overlap(const void* phi, int f32, const int* N, double dV,
                               double* S, hipStream_t s);
 int cg_variant_count();
 const char* cg_variant_name(int v);
+bool cg_variant_paired(int v);   // paired iterate updates (-xc)
 hipError_t launch_cg_zm(const ExxArgs& a, int variant, hipStream_t s);
 hipError_t launch_cg_finish(const ExxArgs& a, hipStream_t s);
 // the scatter's compiled schedules (workgroup orders), the autotuner's choices

@@ -304,7 +304,9 @@ ExxLayout exx_layout(const sea_ctx* ctx, const CellSet& S, bool with_v, bool eag
     L.cg_done = tiled64 ? take(np * sizeof(int)) : 0;
     L.cg_active = tiled64 ? take(((size_t)ctx->opts.max_iter + 1) * sizeof(int)) : 0;
     L.refine = refine ? take((REFINE_MAX + 1) * (np + 1) * sizeof(int)) : 0;   // counts, then lists
-    if (ctx->opts.stencil_dtype == SEA_F32 && !refine) {
+    bool teams = false;
+    for (int k = 0; k < n_pairs; ++k) teams = teams || cg_team_takes(pairs[k]);
+    if (teams && ctx->opts.stencil_dtype == SEA_F32 && !refine) {
         L.team = take(cg_teams(ctx->n_cu) * CG_TEAM_CTL + sizeof(int));
         L.slot_stride = std::max(L.slot_stride, CG_TEAM_SLOT);
     }

@@ -536,9 +536,9 @@ __global__ __launch_bounds__(NT) void k_cg_zm(ExxArgs a) {
 // (read and written once an iteration) and p's planes go through it to the
 // neighbours.  Same recurrences, point for point, as the z-march above with
 // reliable updates; only the FP64 sums are added in another order.
-// Measured per iteration of a 63^3 domain: 35 to 45 us on 8 CUs (32 teams at
-// once), against 300 us and more on one; 288 such pairs 289 -> 153 ms, 8 of them
-// 107 -> 12 ms.  About 17 us of it are the vector ALUs, the rest the three
+// Measured per iteration of a 63^3 domain: 36 us on 8 CUs, 47 with all 32 teams
+// at work, against 300 us and more on one; 288 such pairs 289 -> 159 ms, 8 of
+// them 107 -> 13 ms.  About 17 us of it are the vector ALUs, the rest the three
 // meetings and a third of r and A p, which the compiler spills.
 //
 // What a workgroup writes for others (p's planes, c, flags, partial sums) goes
@@ -858,7 +858,6 @@ __device__ __forceinline__ bool team_solve(const ExxArgs& a, int pid, Team& tm, 
             for (int z = 0; z < TM_ZP; ++z) q[SEA_HALO + z] = own[z * (LH * LW) + TM_TY * c * LW];
 #pragma unroll
             for (int z = 0; z < TM_ZP; ++z) {
-                __builtin_amdgcn_sched_barrier(0);
                 const float* row = own + z * (LH * LW) + TM_TY * c * LW;
                 const float ctr = q[SEA_HALO + z];
                 float s = w.w[0] * ctr;

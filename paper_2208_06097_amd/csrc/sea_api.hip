@@ -652,6 +652,19 @@ static sea_status refine_run(sea_ctx* ctx, const ExxArgs& a0, double* rnorm, dou
     return SEA_OK;
 }
 
+// Whether stream s may use every CU (teams wait for each other: a stream
+// restricted to a few CUs keeps the one-workgroup form).
+static bool whole_device(hipStream_t s, int n_cu) {
+    uint32_t mask[32] = {};
+    if (hipExtStreamGetCUMask(s, 32, mask) != hipSuccess) {
+        (void)hipGetLastError();
+        return true;
+    }
+    int bits = 0;
+    for (uint32_t w : mask) bits += __builtin_popcount(w);
+    return bits == 0 || bits >= n_cu;
+}
+
 // The whole kernel sequence of one call, on stream s (capturable).
 static sea_status exx_enqueue(sea_ctx* ctx, const CellSet& S, const ExxLayout& Ly, char* base, const ExxArgs& a,
                               const ExxFlags& f, hipStream_t s) {
@@ -786,7 +799,7 @@ static sea_status exx_enqueue(sea_ctx* ctx, const CellSet& S, const ExxLayout& L
             // (which round c differently)
             int n_team = 0;
             if (ctx->opts.cg_variant < 0 && !cg_variant_paired(ctx->cg_tuned) && cg_teams(ctx->n_cu) > 0 &&
-                cg_team_lds_bytes() + 1024 <= ctx->max_lds)
+                cg_team_lds_bytes() + 1024 <= ctx->max_lds && (!nocap || whole_device(s, ctx->n_cu)))
                 for (const auto& p : S.pairs) n_team += cg_team_takes(p);
             az.team = n_team > 0;
             if (n_team) SEA_HIP_CHECK(ctx, launch_cg_team(az, n_team, base + Ly.team, ctx->n_cu, s));

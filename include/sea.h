@@ -97,7 +97,11 @@ typedef struct {
                             /* to 64 an axis) are solved by teams of          */
                             /* workgroups, in the arithmetic of the variants  */
                             /* without -xc, unless the tuned choice is an     */
-                            /* -xc variant                                    */
+                            /* -xc variant.  Teams are made of workgroups     */
+                            /* that run at the same time; pairs for which     */
+                            /* none come together within 20 ms (a stream      */
+                            /* restricted to a few CUs, CUs held by other     */
+                            /* work) are solved by the variant                */
     int32_t profile;        /* non-zero: time each stage with HIP events       */
     sea_dtype nn_weight_dtype; /* learned start: network weights F32 or BF16   */
     void *hip_stream;       /* hipStream_t; NULL = default stream              */

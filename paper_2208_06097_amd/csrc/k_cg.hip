@@ -41,6 +41,7 @@
 #include <cstring>
 #include <type_traits>
 
+#include "cg_team_join.h"
 #include "sea_internal.h"
 
 namespace {
@@ -517,12 +518,17 @@ __global__ __launch_bounds__(NT) void k_cg_zm(ExxArgs a) {
     double* r64 = reinterpret_cast<double*>(slot + 3 * a.slot_stride * sizeof(double));
     for (;;) {
         __syncthreads();
-        if (threadIdx.x == 0) pid_sh = atomicAdd(a.queue_ctr, 1);
+        if (threadIdx.x == 0) {   // the next pair, of those that no team has taken
+            int qi, pid = -1;
+            while ((qi = atomicAdd(a.queue_ctr, 1)) < a.n_pairs) {
+                pid = a.order ? a.order[qi] : qi;  // largest domains first
+                if (!a.team || !cg_team_takes(a.pairs[pid]) || a.stats[pid].converged == CG_TEAM_LEFT) break;
+            }
+            pid_sh = qi < a.n_pairs ? pid : -1;
+        }
         __syncthreads();
-        const int qi = pid_sh;
-        if (qi >= a.n_pairs) break;
-        const int pid = a.order ? a.order[qi] : qi;  // largest domains first
-        if (a.team && cg_team_takes(a.pairs[pid])) continue;
+        const int pid = pid_sh;
+        if (pid < 0) break;
         solve_pair<T, NT, COLS, PREFETCH, DEPTH, BUF, XC>(a, pid, lds, red, cc, rr, pp, r64);
     }
 }
@@ -549,15 +555,18 @@ __global__ __launch_bounds__(NT) void k_cg_zm(ExxArgs a) {
 // (an empty slot is all zero bits, a zero part is stored as -0), one trip through
 // memory.  The c update fills the wait for the sums.
 //
-// A workgroup fills a CU (LDS) and a team's are numbered together on one XCD (8
-// of its 32 CUs), so all of a team run at once as soon as that many are free,
-// whatever other streams hold: four such kernels at once (the hardware queues)
-// cannot all hold incomplete teams.  A workgroup that waits for a member not yet
-// started waits for CUs that other work gives back.  Every wait is bounded all
-// the same: past TM_SPIN polls (about a minute) the pair ends as failed.
+// A workgroup fills a CU (LDS), and only workgroups that already run form a team
+// (cg_team_join.h), of one XCD (8 of its 32 CUs) on a device with nothing else to
+// do: whatever else holds CUs, a team that has begun can end.  Pairs that no team
+// takes, because none came together within TM_JOIN_MS, go to the z-march, which is
+// launched after the teams.  The limit is some kernels of other streams long; a
+// stream restricted to fewer than 8 CUs of an XCD pays it once a call.
+// Waits inside a team are bounded all the same: past TM_SPIN polls (about a minute)
+// the pair ends as failed.
 constexpr int TM_G = 8, TM_ZP = 8, TM_NT = 1024;
 constexpr int TM_TY = TM_NT / 64, TM_C = 64 / TM_TY;   // rows of threads; columns of a thread
 constexpr unsigned TM_SPIN = 1u << 26;
+constexpr int TM_JOIN_MS = 20;
 static_assert(TM_G * TM_ZP >= CG_TEAM_MAX && TM_ZP >= SEA_HALO, "planes of the largest domain; halos from the neighbours");
 struct TeamCtl {
     unsigned flag[TM_G];        // meetings reached by each workgroup
@@ -566,6 +575,9 @@ struct TeamCtl {
     double part[4][TM_G];       // parts of four successive sums
 };
 static_assert(sizeof(TeamCtl) <= CG_TEAM_CTL && (CG_TEAM_CTL & 7) == 0, "control block");
+// After the teams' control blocks: the queue's counter and the classes' words, a
+// line each.
+static_assert((1 + RZ_XCD) * 64 <= CG_TEAM_TAIL, "control block's tail");
 template <typename T>
 __device__ __forceinline__ T ld_dev(const T* p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -574,6 +586,18 @@ template <typename T>
 __device__ __forceinline__ void st_dev(T* p, T v) {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
+
+// A class's word in memory (team_join); patience also ends with the queue.
+struct TeamWord {
+    unsigned* word;
+    const int* queue;
+    int n_pairs;
+    long long t0, limit;   // wall clock ticks
+    __device__ unsigned load() const { return ld_dev(word); }
+    __device__ unsigned cas(unsigned expected, unsigned desired) const { return atomicCAS(word, expected, desired); }
+    __device__ bool expired() const { return wall_clock64() - t0 >= limit || ld_dev(queue) >= n_pairs; }
+    __device__ void pause() const { __builtin_amdgcn_s_sleep(8); }
+};
 
 // One of the team's arrays of 64 x 64 planes in memory, the lane's column in a
 // VGPR and the (uniform) plane and row offset in a scalar register; device
@@ -939,31 +963,52 @@ __device__ __forceinline__ bool team_solve(const ExxArgs& a, int pid, Team& tm, 
     return true;
 }
 
-// Workgroup k: XCD k mod 8; of that XCD's sequence, eight at a time are a team.
-__global__ __launch_bounds__(TM_NT) void k_cg_team(ExxArgs a, char* ctl, int n_teams) {
+// Clears the control blocks and marks the pairs that teams may take: none of them
+// is solved yet.
+__global__ __launch_bounds__(256) void k_team_start(ExxArgs a, int* __restrict__ ctl, int n_ctl) {
+    const int t0 = blockIdx.x * 256 + threadIdx.x, nt = gridDim.x * 256;
+    for (int t = t0; t < n_ctl; t += nt) ctl[t] = 0;
+    for (int t = t0; t < a.n_pairs; t += nt)
+        if (cg_team_takes(a.pairs[t])) {
+            a.stats[t].iters = 0;
+            a.stats[t].converged = CG_TEAM_LEFT;
+            a.stats[t].rel_res = __builtin_nan("");
+        }
+}
+
+// Class of workgroup k: k mod 8, the XCD it runs on; eight that arrive one after
+// the other there are a team.
+__global__ __launch_bounds__(TM_NT) void k_cg_team(ExxArgs a, char* ctl, int n_teams, long long limit) {
     extern __shared__ unsigned char smem[];
     float* pl = reinterpret_cast<float*>(smem);
     __shared__ double red[TM_NT / 64];
     __shared__ double tot;
-    __shared__ int fail;
-    const int xcd = blockIdx.x % RZ_XCD, seq = blockIdx.x / RZ_XCD;
-    const int team = (seq / TM_G) * RZ_XCD + xcd;
-    if (team >= n_teams) return;
-    Team tm{reinterpret_cast<TeamCtl*>(ctl + (size_t)team * CG_TEAM_CTL), seq % TM_G};
+    __shared__ int fail, place_sh;
+    char* tail = ctl + (size_t)n_teams * CG_TEAM_CTL;
+    int* queue = reinterpret_cast<int*>(tail);
+    const int cls = blockIdx.x % RZ_XCD;
+    if (threadIdx.x == 0) {
+        TeamWord word{reinterpret_cast<unsigned*>(tail + 64 * (1 + cls)), queue, a.n_pairs, wall_clock64(), limit};
+        place_sh = team_join(word, TM_G, (n_teams - cls + RZ_XCD - 1) / RZ_XCD * TM_G);
+        fail = 0;
+    }
+    __syncthreads();
+    const int place = place_sh;
+    if (place < 0) return;
+    const int team = place / TM_G * RZ_XCD + cls;
+    Team tm{reinterpret_cast<TeamCtl*>(ctl + (size_t)team * CG_TEAM_CTL), place % TM_G};
     tm.red = red;
     tm.tot = &tot;
     tm.fail = &fail;
-    if (threadIdx.x == 0) fail = 0;
+    const bool lead = tm.g == 0 && threadIdx.x == 0;
     for (int i = threadIdx.x; i < TM_ZP * LW * LH; i += TM_NT) pl[i] = 0.0f;
     // the team's slot: c, the exported p (floats), r64, 64 planes each (CG_TEAM_SLOT)
     constexpr int planes = TM_G * TM_ZP * PL;
     float* fs = reinterpret_cast<float*>(a.slots + (size_t)team * 4 * a.slot_stride);
     const TeamIO cc(fs, planes, threadIdx.x), ph(fs + planes, planes, threadIdx.x);
     double* r64 = a.slots + (size_t)team * 4 * a.slot_stride + planes;
-    int* queue = reinterpret_cast<int*>(ctl + (size_t)n_teams * CG_TEAM_CTL);
     for (int turn = 0;; turn ^= 1) {
-        if (tm.g == 0 && threadIdx.x == 0)
-            st_dev(&tm.ctl->pid[turn], atomicAdd(queue, 1));
+        if (lead) st_dev(&tm.ctl->pid[turn], atomicAdd(queue, 1));
         if (!tm.sync()) break;
         const int qi = ld_dev(&tm.ctl->pid[turn]);
         if (qi >= a.n_pairs) break;
@@ -1884,10 +1929,13 @@ hipError_t launch_cg_team(const ExxArgs& a, int n_eligible, char* ctl, int n_cu,
     const int lds = (int)cg_team_lds_bytes();
     const int teams = std::min(std::min(cg_teams(n_cu), n_eligible), a.n_slots);
     hipError_t e = hipFuncSetAttribute((const void*)k_cg_team, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    int dev = 0, khz = 0;   // of the wall clock
+    if (e == hipSuccess) e = hipGetDevice(&dev);
+    if (e == hipSuccess) e = hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, dev);
     if (e != hipSuccess) return e;
-    e = launch_fill_int((int*)ctl, ((size_t)teams * CG_TEAM_CTL + sizeof(int)) / sizeof(int), s);
-    if (e != hipSuccess) return e;
+    const int n_ctl = (int)((teams * CG_TEAM_CTL + CG_TEAM_TAIL) / sizeof(int));
+    hipLaunchKernelGGL(k_team_start, dim3(64), dim3(256), 0, s, a, (int*)ctl, n_ctl);
     hipLaunchKernelGGL(k_cg_team, dim3((teams + RZ_XCD - 1) / RZ_XCD * RZ_XCD * TM_G), dim3(TM_NT), lds, s, a, ctl,
-                       teams);
+                       teams, (long long)khz * TM_JOIN_MS);
     return hipGetLastError();
 }

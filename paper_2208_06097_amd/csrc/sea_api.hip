@@ -307,7 +307,7 @@ ExxLayout exx_layout(const sea_ctx* ctx, const CellSet& S, bool with_v, bool eag
     bool teams = false;
     for (int k = 0; k < n_pairs; ++k) teams = teams || cg_team_takes(pairs[k]);
     if (teams && ctx->opts.stencil_dtype == SEA_F32 && !refine) {
-        L.team = take(cg_teams(ctx->n_cu) * CG_TEAM_CTL + sizeof(int));
+        L.team = take(cg_teams(ctx->n_cu) * CG_TEAM_CTL + CG_TEAM_TAIL);
         L.slot_stride = std::max(L.slot_stride, CG_TEAM_SLOT);
     }
     L.epart = take(np * (size_t)L.ep_stride * sizeof(double));
@@ -652,8 +652,9 @@ static sea_status refine_run(sea_ctx* ctx, const ExxArgs& a0, double* rnorm, dou
     return SEA_OK;
 }
 
-// Whether stream s may use every CU (teams wait for each other: a stream
-// restricted to a few CUs keeps the one-workgroup form).
+// Whether stream s may use every CU.  On a stream restricted to a few CUs teams
+// may not come together, and the time they wait for that is saved (a captured
+// sequence can be replayed on any stream and finds out there).
 static bool whole_device(hipStream_t s, int n_cu) {
     uint32_t mask[32] = {};
     if (hipExtStreamGetCUMask(s, 32, mask) != hipSuccess) {
@@ -803,7 +804,7 @@ static sea_status exx_enqueue(sea_ctx* ctx, const CellSet& S, const ExxLayout& L
                 for (const auto& p : S.pairs) n_team += cg_team_takes(p);
             az.team = n_team > 0;
             if (n_team) SEA_HIP_CHECK(ctx, launch_cg_team(az, n_team, base + Ly.team, ctx->n_cu, s));
-            if (n_team < n_pairs) SEA_HIP_CHECK(ctx, launch_cg_zm(az, var, s));
+            SEA_HIP_CHECK(ctx, launch_cg_zm(az, var, s));   // the rest, and what no team took
             timer_off(SEA_STAGE_CG);
             if (!f.action) {
                 timer_on(SEA_STAGE_FINISH);

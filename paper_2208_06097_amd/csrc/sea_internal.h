@@ -129,7 +129,7 @@ struct ExxArgs {
     double xc_beta_min;   // paired-update CG: smallest beta for recovering a pending step
     int max_iter;
     int lmax;
-    int team;             // FP32 z-march: leave the pairs that the teams take
+    int team;             // FP32 z-march: leave the pairs that teams have taken
     int* queue_ctr;       // persistent-kernel pair counter (zeroed before the CG launch)
     const int* order;     // CG queue order: pair ids by decreasing domain size (nullable)
     const int* dbox;      // per pair 12 ints: boxes where W_i and W_j take the pair
@@ -363,6 +363,8 @@ size_t cg_zm_lds_bytes(int state_f32);
 // 455 and 420, 300 pairs of 63^3 288 and 158.
 constexpr int CG_TEAM_MAX = 64, CG_TEAM_MIN_PTS = 90000;
 constexpr size_t CG_TEAM_CTL = 2048;            // bytes of a team's control block
+constexpr size_t CG_TEAM_TAIL = 640;            // and of what follows the last one
+constexpr int CG_TEAM_LEFT = -2;                // DevStat::converged of a pair that no team has taken
 constexpr size_t CG_TEAM_SLOT = 32 * 64 * 64;   // least slot_stride: c, p (FP32) and r64 of 64 planes in four of them
 __host__ __device__ inline bool cg_team_takes(const sea_pair& P) {
     return P.n[0] <= CG_TEAM_MAX && P.n[1] <= CG_TEAM_MAX && P.n[2] <= CG_TEAM_MAX &&
@@ -370,7 +372,8 @@ __host__ __device__ inline bool cg_team_takes(const sea_pair& P) {
 }
 size_t cg_team_lds_bytes();
 int cg_teams(int n_cu);   // teams that run at once
-// ctl: cg_teams(n_cu) control blocks and the queue's counter (cleared here)
+// ctl: cg_teams(n_cu) control blocks and their tail (cleared here).  Pairs that no
+// team took are left for launch_cg_zm with a.team set.
 hipError_t launch_cg_team(const ExxArgs& a, int n_eligible, char* ctl, int n_cu, hipStream_t s);
 // part: eps_marginals_part_doubles(N, n_occ) of scratch
 size_t eps_marginals_part_doubles(const int* N, int n_occ);

@@ -562,7 +562,7 @@ __global__ __launch_bounds__(NT) void k_cg_zm(ExxArgs a) {
 // launched after the teams.  The limit is some kernels of other streams long; a
 // stream restricted to fewer than 8 CUs of an XCD pays it once a call.
 // Waits inside a team are bounded all the same: past TM_SPIN polls (about a minute)
-// the pair ends as failed.
+// the pair ends as failed, whichever member's wait it was.
 constexpr int TM_G = 8, TM_ZP = 8, TM_NT = 1024;
 constexpr int TM_TY = TM_NT / 64, TM_C = 64 / TM_TY;   // rows of threads; columns of a thread
 constexpr unsigned TM_SPIN = 1u << 26;
@@ -704,11 +704,18 @@ struct Team {
     }
 };
 
-// One pair.  Thread (tx, ty) owns the points (tx, ty + TM_TY c, TM_ZP g + z).
+// What a pair's solve came to (DevStat's fields).
+struct TeamEnd {
+    int iters, converged;
+    double rel_res;
+};
+
+// One pair; false once a wait has run out.  Thread (tx, ty) owns the points
+// (tx, ty + TM_TY c, TM_ZP g + z).
 // pl: LDS planes of p with SEA_HALO zero rows on either side; cc, ph: the
 // team's c and exported p (planes of 64 x 64), r64: the FP64 residual.
 __device__ __forceinline__ bool team_solve(const ExxArgs& a, int pid, Team& tm, float* pl, const TeamIO& cc,
-                                           const TeamIO& ph, double* r64) {
+                                           const TeamIO& ph, double* r64, TeamEnd& end) {
     const DevCell& C = a.cells[a.pair_cell[pid]];
     const double ih2 = 1.0 / (C.h[0] * C.h[0]);
     SW<float> w = make_sw<float>(ih2);
@@ -795,12 +802,8 @@ __device__ __forceinline__ bool team_solve(const ExxArgs& a, int pid, Team& tm, 
     if (sres && a.rnorm) {
         double b2, q2;
         if (start_meets_target(a, pid, tol2, b2, q2)) {
-            if (lead) {
-                a.stats[pid].iters = 0;
-                a.stats[pid].converged = 1;
-                a.stats[pid].rel_res = b2 > 0.0 ? sqrt(q2 / b2) : 0.0;
-                hist_put(a, pid, 0, q2, b2);
-            }
+            end = TeamEnd{0, 1, b2 > 0.0 ? sqrt(q2 / b2) : 0.0};
+            if (lead) hist_put(a, pid, 0, q2, b2);
             return true;
         }
     }
@@ -955,11 +958,7 @@ __device__ __forceinline__ bool team_solve(const ExxArgs& a, int pid, Team& tm, 
         rho = r2t;
         rupd = r2;
     }
-    if (lead) {
-        a.stats[pid].iters = it;
-        a.stats[pid].converged = conv;
-        a.stats[pid].rel_res = bb > 0.0 ? sqrt(r2 / bb) : 0.0;
-    }
+    end = TeamEnd{it, conv, bb > 0.0 ? sqrt(r2 / bb) : 0.0};
     return true;
 }
 
@@ -1014,10 +1013,18 @@ __global__ __launch_bounds__(TM_NT) void k_cg_team(ExxArgs a, char* ctl, int n_t
         if (qi >= a.n_pairs) break;
         const int pid = a.order ? a.order[qi] : qi;   // largest domains first
         if (!cg_team_takes(a.pairs[pid])) continue;
-        if (!team_solve(a, pid, tm, pl, cc, ph, r64)) {
-            if (threadIdx.x == 0) a.stats[pid].converged = -1;
-            break;
+        // solved when all of the team say so: a member whose last wait ran out does
+        // not come to this meeting, and its planes may be unfinished
+        TeamEnd end;
+        const bool ok = team_solve(a, pid, tm, pl, cc, ph, r64, end) && tm.sync();
+        if (lead) {
+            a.stats[pid].converged = ok ? end.converged : -1;
+            if (ok) {
+                a.stats[pid].iters = end.iters;
+                a.stats[pid].rel_res = end.rel_res;
+            }
         }
+        if (!ok) break;
     }
 }
 

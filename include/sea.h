@@ -95,7 +95,9 @@ typedef struct {
                             /* 0..sea_cg_variant_count()-1 = that variant.    */
                             /* With -1, domains of 90000 points and more (up  */
                             /* to 64 an axis) are solved by teams of          */
-                            /* workgroups, in the arithmetic of the variants  */
+                            /* workgroups where that is faster, which their   */
+                            /* planes (53 and more always) and the number of  */
+                            /* pairs say, in the arithmetic of the variants   */
                             /* without -xc, unless the tuned choice is an     */
                             /* -xc variant.  Teams are made of workgroups     */
                             /* that run at the same time; pairs for which     */

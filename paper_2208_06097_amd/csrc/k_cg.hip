@@ -522,7 +522,7 @@ __global__ __launch_bounds__(NT) void k_cg_zm(ExxArgs a) {
             int qi, pid = -1;
             while ((qi = atomicAdd(a.queue_ctr, 1)) < a.n_pairs) {
                 pid = a.order ? a.order[qi] : qi;  // largest domains first
-                if (!a.team || !cg_team_takes(a.pairs[pid]) || a.stats[pid].converged == CG_TEAM_LEFT) break;
+                if (!a.team || !cg_team_takes(a.pairs[pid], a.team) || a.stats[pid].converged == CG_TEAM_LEFT) break;
             }
             pid_sh = qi < a.n_pairs ? pid : -1;
         }
@@ -968,7 +968,7 @@ __global__ __launch_bounds__(256) void k_team_start(ExxArgs a, int* __restrict__
     const int t0 = blockIdx.x * 256 + threadIdx.x, nt = gridDim.x * 256;
     for (int t = t0; t < n_ctl; t += nt) ctl[t] = 0;
     for (int t = t0; t < a.n_pairs; t += nt)
-        if (cg_team_takes(a.pairs[t])) {
+        if (cg_team_takes(a.pairs[t], a.team)) {
             a.stats[t].iters = 0;
             a.stats[t].converged = CG_TEAM_LEFT;
             a.stats[t].rel_res = __builtin_nan("");
@@ -1012,7 +1012,7 @@ __global__ __launch_bounds__(TM_NT) void k_cg_team(ExxArgs a, char* ctl, int n_t
         const int qi = ld_dev(&tm.ctl->pid[turn]);
         if (qi >= a.n_pairs) break;
         const int pid = a.order ? a.order[qi] : qi;   // largest domains first
-        if (!cg_team_takes(a.pairs[pid])) continue;
+        if (!cg_team_takes(a.pairs[pid], a.team)) continue;
         // solved when all of the team say so: a member whose last wait ran out does
         // not come to this meeting, and its planes may be unfinished
         TeamEnd end;

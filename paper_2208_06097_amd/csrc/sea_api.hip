@@ -305,7 +305,7 @@ ExxLayout exx_layout(const sea_ctx* ctx, const CellSet& S, bool with_v, bool eag
     L.cg_active = tiled64 ? take(((size_t)ctx->opts.max_iter + 1) * sizeof(int)) : 0;
     L.refine = refine ? take((REFINE_MAX + 1) * (np + 1) * sizeof(int)) : 0;   // counts, then lists
     bool teams = false;
-    for (int k = 0; k < n_pairs; ++k) teams = teams || cg_team_takes(pairs[k]);
+    for (int k = 0; k < n_pairs; ++k) teams = teams || cg_team_takes(pairs[k], cg_team_min_nz(n_pairs, ctx->n_cu));
     if (teams && ctx->opts.stencil_dtype == SEA_F32 && !refine) {
         L.team = take(cg_teams(ctx->n_cu) * CG_TEAM_CTL + CG_TEAM_TAIL);
         L.slot_stride = std::max(L.slot_stride, CG_TEAM_SLOT);
@@ -798,11 +798,12 @@ static sea_status exx_enqueue(sea_ctx* ctx, const CellSet& S, const ExxLayout& L
             // teams of workgroups take the domains that fit them, unless the caller has
             // fixed a variant or the autotuner chose one with paired iterate updates
             // (which round c differently)
+            const int min_nz = cg_team_min_nz(n_pairs, ctx->n_cu);
             int n_team = 0;
             if (ctx->opts.cg_variant < 0 && !cg_variant_paired(ctx->cg_tuned) && cg_teams(ctx->n_cu) > 0 &&
                 cg_team_lds_bytes() + 1024 <= ctx->max_lds && (!nocap || whole_device(s, ctx->n_cu)))
-                for (const auto& p : S.pairs) n_team += cg_team_takes(p);
-            az.team = n_team > 0;
+                for (const auto& p : S.pairs) n_team += cg_team_takes(p, min_nz);
+            az.team = n_team > 0 ? min_nz : 0;
             if (n_team) SEA_HIP_CHECK(ctx, launch_cg_team(az, n_team, base + Ly.team, ctx->n_cu, s));
             SEA_HIP_CHECK(ctx, launch_cg_zm(az, var, s));   // the rest, and what no team took
             timer_off(SEA_STAGE_CG);

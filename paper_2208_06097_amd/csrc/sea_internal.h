@@ -129,7 +129,8 @@ struct ExxArgs {
     double xc_beta_min;   // paired-update CG: smallest beta for recovering a pending step
     int max_iter;
     int lmax;
-    int team;             // FP32 z-march: leave the pairs that teams have taken
+    int team;             // FP32 z-march: leave the pairs that teams have taken, of those with
+                          // this many planes (0: no teams)
     int* queue_ctr;       // persistent-kernel pair counter (zeroed before the CG launch)
     const int* order;     // CG queue order: pair ids by decreasing domain size (nullable)
     const int* dbox;      // per pair 12 ints: boxes where W_i and W_j take the pair
@@ -356,19 +357,30 @@ __device__ __forceinline__ void lds_sync() { asm volatile("s_waitcnt lgkmcnt(0)\
 // z-marching CG (k_cg.hip): needs every pair with n[0], n[1] <= 64.
 bool cg_zm_fits(const sea_pair* pairs, int n_pairs, const double* h);
 size_t cg_zm_lds_bytes(int state_f32);
-// FP32 CG by teams of workgroups (k_cg.hip): domains of up to 64 points an axis,
-// from the size on where a team is the faster form for long pair lists too (the
-// line lies with the domain alone, so that a pair's result does not depend on its
-// batch): 1000 pairs of 40^3 307 ms by the z-march and about 340 by teams, of 50^3
-// 455 and 420, 300 pairs of 63^3 288 and 158.
+// FP32 CG by teams of workgroups (k_cg.hip): domains of up to 64 points an axis and
+// of at least min_nz planes (cg_team_min_nz).
 constexpr int CG_TEAM_MAX = 64, CG_TEAM_MIN_PTS = 90000;
 constexpr size_t CG_TEAM_CTL = 2048;            // bytes of a team's control block
 constexpr size_t CG_TEAM_TAIL = 640;            // and of what follows the last one
 constexpr int CG_TEAM_LEFT = -2;                // DevStat::converged of a pair that no team has taken
 constexpr size_t CG_TEAM_SLOT = 32 * 64 * 64;   // least slot_stride: c, p (FP32) and r64 of 64 planes in four of them
-__host__ __device__ inline bool cg_team_takes(const sea_pair& P) {
-    return P.n[0] <= CG_TEAM_MAX && P.n[1] <= CG_TEAM_MAX && P.n[2] <= CG_TEAM_MAX &&
+__host__ __device__ inline bool cg_team_takes(const sea_pair& P, int min_nz) {
+    return P.n[0] <= CG_TEAM_MAX && P.n[1] <= CG_TEAM_MAX && P.n[2] <= CG_TEAM_MAX && P.n[2] >= min_nz &&
            P.n[0] * P.n[1] * P.n[2] >= CG_TEAM_MIN_PTS;
+}
+// The planes from which a team is the faster form in a call of n_pairs pairs.  A
+// team's iteration costs the same for every domain; the z-march's follows the
+// planes, with a part for each round of a pair per CU and a part for each pair.
+// Fitted to 40 iterations of 32 to 1600 pairs of 48 to 64 points in x and y and 22
+// to 64 planes: z-march nz (0.19 rounds + 0.0007 n) ms, teams 0.07 n; the line keeps to
+// the z-march's side.  Teams over z-march: 64 pairs of 22 planes 0.69, of 64
+// planes 0.34; 256 of 48 1.09, of 54 0.99, of 64 0.88; 288 of 31 0.99, of 48 0.77;
+// 1000 of 48 1.05, of 54 0.98, of 64 0.87.  From 53 planes on the domain alone
+// decides; below, a pair's FP64 sums, and so the last digits of its result, can
+// depend on the length of its list.
+inline int cg_team_min_nz(int n_pairs, int n_cu) {
+    const long n = n_pairs, rounds = (n + n_cu - 1) / n_cu;
+    return n > 0 ? (int)(1000 * n / (9 * n_cu * rounds + 10 * n)) + 1 : 1;
 }
 size_t cg_team_lds_bytes();
 int cg_teams(int n_cu);   // teams that run at once

@@ -181,7 +181,10 @@ def kernel_rooflines(form, stages, pairs, npts, stats, cell, n_pairs, tune, wbyt
     else:
         k = "k_cg_zm" if FORMS[form]["stencil"] == "f32" else "k_cg64"
         cgb = float(np.sum(stats["iters"].astype(np.float64) * 6.0 * npts * wbytes))
-        name = (f"k_cg_zm<float, {tune['variant'] if tune else ''}>" if k == "k_cg_zm" else
+        # teams of workgroups take the domains where they are the faster form,
+        # unless a variant is fixed (a tuned choice has its times)
+        teams = "k_cg_team and " if tune and tune["ms"] else ""
+        name = (f"{teams}k_cg_zm<float, {tune['variant'] if tune else ''}>" if k == "k_cg_zm" else
                 "k_cg64_init/k_cg64_sweep<0,1> (row tiles, two sweeps per iteration)")
         out[k] = _kernel(name, stages["cg"], 1, cgb, f"6 words x {int(wbytes)} B per interior point per CG iteration",
                          tr(k, cg_iters_total=int(stats["iters"].sum())))
@@ -197,7 +200,7 @@ def cg_roofline(form, cg_ms, stats, npts):
     if b == 0.0 or cg_ms <= 0.0:
         return None
     gbs = b / (cg_ms * 1e-3) / 1e9
-    return {"kernel": "k_cg_zm<float>" if w == 4.0 else "k_cg64 (row tiles)", "ms": cg_ms, "bytes": b,
+    return {"kernel": "k_cg_team and k_cg_zm<float>" if w == 4.0 else "k_cg64 (row tiles)", "ms": cg_ms, "bytes": b,
             "achieved_gbs": gbs, "frac": gbs / HBM_PEAK_GBS}
 
 

@@ -38,7 +38,6 @@
 // norms and dot products accumulate in FP64.  A separate kernel recomputes
 // the true residual b - A x in FP64 at exit and the pair energy.
 #include <algorithm>
-#include <cstring>
 #include <type_traits>
 
 #include "cg_team_join.h"
@@ -1916,11 +1915,6 @@ constexpr int kNumCgVariants = sizeof(kCgVariants) / sizeof(kCgVariants[0]);
 int cg_variant_count() { return kNumCgVariants; }
 
 const char* cg_variant_name(int v) { return (v >= 0 && v < kNumCgVariants) ? kCgVariants[v].name : nullptr; }
-
-bool cg_variant_paired(int v) {
-    const char* n = cg_variant_name(v);
-    return n && strstr(n, "-xc");
-}
 
 hipError_t launch_cg_zm(const ExxArgs& a, int variant, hipStream_t s) {
     if (variant < 0 || variant >= kNumCgVariants) return hipErrorInvalidValue;

@@ -305,7 +305,7 @@ ExxLayout exx_layout(const sea_ctx* ctx, const CellSet& S, bool with_v, bool eag
     L.cg_active = tiled64 ? take(((size_t)ctx->opts.max_iter + 1) * sizeof(int)) : 0;
     L.refine = refine ? take((REFINE_MAX + 1) * (np + 1) * sizeof(int)) : 0;   // counts, then lists
     bool teams = false;
-    for (int k = 0; k < n_pairs; ++k) teams = teams || cg_team_takes(pairs[k], cg_team_min_nz(n_pairs, ctx->n_cu));
+    for (int k = 0; k < n_pairs; ++k) teams = teams || cg_team_takes(pairs[k], cg_team_min_nz(n_pairs, ctx->n_cu, 1.0));
     if (teams && ctx->opts.stencil_dtype == SEA_F32 && !refine) {
         L.team = take(cg_teams(ctx->n_cu) * CG_TEAM_CTL + CG_TEAM_TAIL);
         L.slot_stride = std::max(L.slot_stride, CG_TEAM_SLOT);
@@ -796,12 +796,12 @@ static sea_status exx_enqueue(sea_ctx* ctx, const CellSet& S, const ExxLayout& L
             az.start_res = ctx->opts.start == SEA_START_SPECTRAL ? 1 : 0;
             az.rnorm = (az.start_res && residual_zm_lds_bytes() <= ctx->max_lds) ? (double*)(base + Ly.rnorm) : nullptr;
             // teams of workgroups take the domains that fit them, unless the caller has
-            // fixed a variant or the autotuner chose one with paired iterate updates
-            // (which round c differently)
-            const int min_nz = cg_team_min_nz(n_pairs, ctx->n_cu);
+            // fixed a variant; an autotuned one moves the line to where they are faster
+            // than it
+            const int min_nz = cg_team_min_nz(n_pairs, ctx->n_cu, ctx->cg_cost);
             int n_team = 0;
-            if (ctx->opts.cg_variant < 0 && !cg_variant_paired(ctx->cg_tuned) && cg_teams(ctx->n_cu) > 0 &&
-                cg_team_lds_bytes() + 1024 <= ctx->max_lds && (!nocap || whole_device(s, ctx->n_cu)))
+            if (ctx->opts.cg_variant < 0 && cg_teams(ctx->n_cu) > 0 && cg_team_lds_bytes() + 1024 <= ctx->max_lds &&
+                (!nocap || whole_device(s, ctx->n_cu)))
                 for (const auto& p : S.pairs) n_team += cg_team_takes(p, min_nz);
             az.team = n_team > 0 ? min_nz : 0;
             if (n_team) SEA_HIP_CHECK(ctx, launch_cg_team(az, n_team, base + Ly.team, ctx->n_cu, s));
@@ -1841,7 +1841,7 @@ extern "C" sea_status sea_exx_autotune(sea_ctx* ctx, int n_cells, const sea_cell
     }
     const int nv = cg_variant_count();
     int arg = 0;
-    float tbest = 0.0f;
+    float tbest = 0.0f, t0 = 0.0f;
     hipError_t err = hipSuccess;
     for (int v = 0; v < nv && err == hipSuccess; ++v) {
         float ms = 0.0f;
@@ -1854,6 +1854,7 @@ extern "C" sea_status sea_exx_autotune(sea_ctx* ctx, int n_cells, const sea_cell
             if (err == hipSuccess) err = hipEventElapsedTime(&ms, e0, e1);
         }
         if (ms_host) ms_host[v] = ms;
+        if (v == 0) t0 = ms;
         if (v == 0 || ms < tbest) {
             tbest = ms;
             arg = v;
@@ -1863,7 +1864,18 @@ extern "C" sea_status sea_exx_autotune(sea_ctx* ctx, int n_cells, const sea_cell
     (void)hipEventDestroy(e1);
     if (err != hipSuccess) return fail(ctx, SEA_E_HIP, "autotune: %s", hipGetErrorString(err));
     ctx->cg_tuned = arg;
+    ctx->cg_cost = tbest > 0.0f ? (double)tbest / t0 : 1.0;
     if (best) *best = arg;
+    return SEA_OK;
+}
+
+extern "C" sea_status sea_set_cg_choice(sea_ctx* ctx, int variant, double cost) {
+    if (!ctx) return SEA_E_ARG;
+    if (variant < 0 || variant >= cg_variant_count())
+        return fail(ctx, SEA_E_ARG, "CG variant %d out of range (%d variants)", variant, cg_variant_count());
+    if (!(cost > 0.0 && cost <= 1.0)) return fail(ctx, SEA_E_ARG, "cost must be in (0, 1]");
+    ctx->cg_tuned = variant;
+    ctx->cg_cost = cost;
     return SEA_OK;
 }
 

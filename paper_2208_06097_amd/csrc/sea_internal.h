@@ -38,6 +38,7 @@ struct sea_ctx {
     bool ev_ready = false;
     const void* nn_state = nullptr;   // attached network (learned start)
     int cg_tuned = -1;                // z-march variant chosen by sea_exx_autotune
+    double cg_cost = 1.0;             // its time there, the default variant's being 1
     void* noalloc_scratch = nullptr;  // device address of this device's static scratch array
     // sine-transform kernel variants (spectral start): the autotuner's choice
     // and a fixed choice (-1: none; the fixed one wins)
@@ -376,11 +377,13 @@ __host__ __device__ inline bool cg_team_takes(const sea_pair& P, int min_nz) {
 // the z-march's side.  Teams over z-march: 64 pairs of 22 planes 0.69, of 64
 // planes 0.34; 256 of 48 1.09, of 54 0.99, of 64 0.88; 288 of 31 0.99, of 48 0.77;
 // 1000 of 48 1.05, of 54 0.98, of 64 0.87.  From 53 planes on the domain alone
-// decides; below, a pair's FP64 sums, and so the last digits of its result, can
+// decides (cost 1); below, a pair's FP64 sums, and so the last digits of its result, can
 // depend on the length of its list.
-inline int cg_team_min_nz(int n_pairs, int n_cu) {
+// cost: time of the z-march variant in use, the default one's being 1 (the fit's).
+inline int cg_team_min_nz(int n_pairs, int n_cu, double cost) {
     const long n = n_pairs, rounds = (n + n_cu - 1) / n_cu;
-    return n > 0 ? (int)(1000 * n / (9 * n_cu * rounds + 10 * n)) + 1 : 1;
+    const double nz = n > 0 ? 1000.0 * n / (cost * (9.0 * n_cu * rounds + 10.0 * n)) : 0.0;
+    return nz < CG_TEAM_MAX ? (int)nz + 1 : CG_TEAM_MAX + 1;
 }
 size_t cg_team_lds_bytes();
 int cg_teams(int n_cu);   // teams that run at once
@@ -395,7 +398,6 @@ hipError_t launch_eps_overlap(const void* phi, int f32, const int* N, double dV,
                               double* S, hipStream_t s);
 int cg_variant_count();
 const char* cg_variant_name(int v);
-bool cg_variant_paired(int v);   // paired iterate updates (-xc)
 hipError_t launch_cg_zm(const ExxArgs& a, int variant, hipStream_t s);
 hipError_t launch_cg_finish(const ExxArgs& a, hipStream_t s);
 // the scatter's compiled schedules (workgroup orders), the autotuner's choices

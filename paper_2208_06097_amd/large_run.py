@@ -46,7 +46,7 @@ def main():
     W = torch.empty((cell.n_occ,) + (cell.N,) * 3, dtype=torch.float64, device="cuda")
     forms = {"zero-f32": sea.SEA_START_ZERO, "multipole-f32": sea.SEA_START_MULTIPOLE,
              "learned-f32": sea.SEA_START_LEARNED, "spectral-f32": sea.SEA_START_SPECTRAL}
-    ws, variant, out = None, None, {}
+    ws, tuned, out = None, None, {}
     for name in ("spectral-f32", "learned-f32", "multipole-f32", "zero-f32"):   # largest workspace first
         ctx = sea.Context(rel_tol=args.tol, stencil_dtype=sea.SEA_F32, start=forms[name], profile=True)
         if name == "learned-f32":
@@ -55,10 +55,10 @@ def main():
         if ws is None:
             ws = ctx.workspace(ctx.exx_workspace_bytes(cell.N, cell.L, cell.n_occ, pairs))
             log(f"workspace {ws.numel() / 2**30:.1f} GiB")
-        if variant is None:
-            variant = ctx.autotune([(phi, cell.N, cell.L, pairs)], sample_pairs=2048, iters=20, ws=ws)["variant"]
+        if tuned is None:
+            tuned = ctx.autotune([(phi, cell.N, cell.L, pairs)], sample_pairs=2048, iters=20, ws=ws)
         else:
-            ctx.set_opts(cg_variant=ctx.cg_variants().index(variant))
+            ctx.cg_choice(tuned["variant"], tuned["ms"])
         _, E, stats, status = ctx.exx_action(phi, cell.N, cell.L, pairs, ws=ws, W=W)
         ms = ctx.stage_times()
         vxx = sum(ms[k] for k in ("gather", "boundary", "guess", "cg", "finish", "scatter", "energy"))
@@ -74,7 +74,7 @@ def main():
     z, l = out["zero-f32"], out["learned-f32"]
     res = {"workload": "256-molecule water-like cell, L=37.3 bohr, 190^3 grid, 1024 orbitals, 63^3 pair domains, "
                        "FP32 CG state + FP64 reliable updates to a relative true residual",
-           "seed": args.seed, "n_pairs": len(pairs), "rel_tol": args.tol, "cg_variant": variant, "forms": out,
+           "seed": args.seed, "n_pairs": len(pairs), "rel_tol": args.tol, "cg_variant": tuned["variant"], "forms": out,
            "learned_vs_zero": {"iters_saved_frac": 1 - l["iters_mean"] / z["iters_mean"],
                                "time_saved_frac": 1 - l["vxx_ms"] / z["vxx_ms"]},
            "spectral_vs_zero": {"time_saved_frac": 1 - out["spectral-f32"]["vxx_ms"] / z["vxx_ms"]},

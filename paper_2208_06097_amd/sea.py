@@ -31,7 +31,7 @@ EXPORTS = [
     "sea_nn_workspace_bytes", "sea_nn_forward", "sea_nn_train_step", "sea_nn_attach",
     "sea_exx_nn_samples", "sea_exx_batched_workspace_bytes", "sea_exx_action_batched",
     "sea_exx_plan_create", "sea_exx_plan_launch", "sea_exx_plan_results", "sea_exx_plan_destroy",
-    "sea_cg_variant_count", "sea_cg_variant_name", "sea_exx_autotune",
+    "sea_cg_variant_count", "sea_cg_variant_name", "sea_exx_autotune", "sea_set_cg_choice",
     "sea_nn_infer_workspace_bytes", "sea_nn_infer", "sea_eps_workspace_bytes", "sea_build_pairs_eps",
     "sea_successive_idempotency", "sea_scdm_workspace_bytes", "sea_scdm", "sea_rotate",
     "sea_ace_apply_noalloc", "sea_spectral_variant_count", "sea_spectral_variant_name",
@@ -159,6 +159,7 @@ def load() -> C.CDLL:
     lib.sea_cg_variant_name.argtypes = [i]
     lib.sea_cg_variant_name.restype = C.c_char_p
     lib.sea_exx_autotune.argtypes = [vp, i, vp, vp, sz, i, i, vp, P(i)]
+    lib.sea_set_cg_choice.argtypes = [vp, i, C.c_double]
     lib.sea_spectral_variant_count.argtypes = []
     lib.sea_spectral_variant_count.restype = i
     lib.sea_spectral_variant_name.argtypes = [i]
@@ -393,7 +394,8 @@ class Context:
         """Pick the FP32-state CG kernel variant for this workload.
 
         Times every variant on a strided sample of the cells' pairs (same
-        work for each) and keeps the fastest for this context.  With
+        work for each) and keeps the fastest for this context; its time also
+        says from which domains on teams of workgroups are faster still.  With
         ``cache`` (a JSON path), a stored choice for the same device, variant
         set and domain shapes is reused without timing, and new results are
         stored.  Returns {"variant": name, "ms": {name: ms} or None, "cached": bool}."""
@@ -409,7 +411,7 @@ class Context:
                 store = json.load(f)
             hit = store.get(key)
             if hit and hit.get("variant") in names:
-                self.set_opts(cg_variant=names.index(hit["variant"]))
+                self.cg_choice(hit["variant"], hit.get("ms"))
                 return {"variant": hit["variant"], "ms": hit.get("ms"), "cached": True}
         arr, _, keep = self._cells(cells, need_W=False)
         if ws is None:
@@ -425,6 +427,14 @@ class Context:
             with open(cache, "w") as f:
                 json.dump(store, f, indent=1)
         return out
+
+    def cg_choice(self, variant, ms=None):
+        """Set what an earlier ``autotune`` chose: the variant's name and the
+        times {name: ms} that it returned."""
+        names = self.cg_variants()
+        cost = min(1.0, ms[variant] / ms[names[0]]) if ms else 1.0
+        self.set_opts(cg_variant=-1)
+        self._check(self.lib.sea_set_cg_choice(self.h, names.index(variant), cost))
 
     def spectral_variants(self):
         """(plane variant names, z-line variant names) of the sine-transform passes."""

@@ -442,7 +442,6 @@ __global__ __launch_bounds__(SC_PICK) void k_scdm_step(int n, int step, ScdmStat
     __shared__ double sv[W];
     __shared__ long long sj[W];
     __shared__ int slot_sh, go_sh;
-    if (st->stop) return;
     const bool rec = blockIdx.x == 0 && threadIdx.x == 0;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int k0 = st->k0, k = k0 + step;
@@ -450,10 +449,13 @@ __global__ __launch_bounds__(SC_PICK) void k_scdm_step(int n, int step, ScdmStat
         if (rec) st->stop = 1;
         return;
     }
+    // One thread reads st->stop for its block: block 0 of this launch may set it
+    // meanwhile, and all of a block have to see the same (a block that sees the old
+    // value comes to the same end by itself)
     if (step == 0) {
         if (threadIdx.x == 0) {
             slot_sh = st->gslot;
-            go_sh = 1;
+            go_sh = !st->stop;
         }
     } else {
         double v = -2.0;
@@ -469,7 +471,7 @@ __global__ __launch_bounds__(SC_PICK) void k_scdm_step(int n, int step, ScdmStat
         block_argmax<SC_PICK>(bv, bj, sv, sj);
         if (threadIdx.x == 0) {
             const double tau = __longlong_as_double((long long)st->tau_bits);
-            go_sh = bv > tau && bv > 0.0;
+            go_sh = !st->stop && bv > tau && bv > 0.0;
             sj[0] = bj;
             if (!go_sh && rec) st->stop = 1;
         }

@@ -4,6 +4,7 @@
 #pragma once
 
 #include <algorithm>
+#include <cfloat>
 #include <cmath>
 #include <cstdlib>
 #include <vector>
@@ -54,10 +55,12 @@ inline int host_build_pairs(const int32_t* n, const double* L, int n_occ, const 
 // are direct sums, in the order the runs are listed.  Prefix sums say which
 // runs need one: the largest mass of a length grows with the length, so a
 // bisection finds the lengths whose masses all lie below the target by more
-// than the prefix sums' rounding (N 2^-53 of the total; the margin is
-// 1e-12), and at the lengths from there only starts within the margin are
-// summed.  (Summing every start of every length took 28 ms for the axes of
-// 256 orbitals of 120 points; this takes 0.6 ms.)
+// than rounding can explain, and at the lengths from there only starts within
+// that margin are summed.  A prefix sum is at most twice the total T, so each
+// addition that two of them differ by is off by 2 u T at most (u = 2^-53), and
+// each of the direct sum by u T: (3 N + 1) u T between the two; the margin is
+// 8 N u T.  (Summing every start of every length took 28 ms for the axes of 256
+// orbitals of 120 points; this takes 0.6 ms.)
 inline void eps_run(const double* m, int N, double eps, int* lo, int* len) {
     double T = 0.0;
     for (int k = 0; k < N; ++k) T += m[k];
@@ -66,7 +69,7 @@ inline void eps_run(const double* m, int N, double eps, int* lo, int* len) {
     for (int k = 0; k < 2 * N; ++k) cum[k + 1] = cum[k] + m[k % N];
     // no margin to speak of in a sum that is not finite: every run is summed
     const bool fin = std::isfinite(cum[2 * (size_t)N]);
-    const double low = target - 1e-12 * std::fabs(T);
+    const double low = target - 4.0 * N * DBL_EPSILON * std::fabs(T);
     auto below = [&](int ln) {   // every run of this length misses the target
         for (int s0 = 0; s0 < N; ++s0)
             if (cum[s0 + ln] - cum[s0] >= low) return false;

@@ -181,9 +181,7 @@ def kernel_rooflines(form, stages, pairs, npts, stats, cell, n_pairs, tune, wbyt
     else:
         k = "k_cg_zm" if FORMS[form]["stencil"] == "f32" else "k_cg64"
         cgb = float(np.sum(stats["iters"].astype(np.float64) * 6.0 * npts * wbytes))
-        # teams of workgroups take the domains where they are the faster form,
-        # unless a variant is fixed (a tuned choice has its times)
-        teams = "k_cg_team and " if tune and tune["ms"] else ""
+        teams = "k_cg_team and " if tune and tune.get("teams") else ""
         name = (f"{teams}k_cg_zm<float, {tune['variant'] if tune else ''}>" if k == "k_cg_zm" else
                 "k_cg64_init/k_cg64_sweep<0,1> (row tiles, two sweeps per iteration)")
         out[k] = _kernel(name, stages["cg"], 1, cgb, f"6 words x {int(wbytes)} B per interior point per CG iteration",
@@ -191,7 +189,7 @@ def kernel_rooflines(form, stages, pairs, npts, stats, cell, n_pairs, tune, wbyt
     return out
 
 
-def cg_roofline(form, cg_ms, stats, npts):
+def cg_roofline(form, cg_ms, stats, npts, tune):
     """The CG kernel of a form against the HBM roofline: 6 state words per
     interior point per iteration (None when the form iterates nowhere)."""
     import numpy as np
@@ -200,7 +198,8 @@ def cg_roofline(form, cg_ms, stats, npts):
     if b == 0.0 or cg_ms <= 0.0:
         return None
     gbs = b / (cg_ms * 1e-3) / 1e9
-    return {"kernel": "k_cg_team and k_cg_zm<float>" if w == 4.0 else "k_cg64 (row tiles)", "ms": cg_ms, "bytes": b,
+    teams = "k_cg_team and " if tune and tune.get("teams") else ""
+    return {"kernel": f"{teams}k_cg_zm<float>" if w == 4.0 else "k_cg64 (row tiles)", "ms": cg_ms, "bytes": b,
             "achieved_gbs": gbs, "frac": gbs / HBM_PEAK_GBS}
 
 
@@ -394,7 +393,7 @@ def main():
                     "cg_iters_mean": float(stats["iters"].mean()), "E_xx": E, "E_ace": E_ace,
                     "dE_vs_oracle": (E - golden["E"]) if golden else None,
                     "dE_ace_vs_oracle": (E_ace - golden["E"]) if golden else None,
-                    "cg_kernel": cg_roofline(form, stages["cg"], stats, npts),
+                    "cg_kernel": cg_roofline(form, stages["cg"], stats, npts, tune),
                     "action_frac": action["frac"]}}
     # ACE precision sweep on this step's W: xi and K psi on the matrix cores in
     # FP32 and BF16 (M, Cholesky and energy stay FP64), errors vs the FP64 path
@@ -426,7 +425,7 @@ def main():
                 continue
             c2 = make_ctx(fname)
             ws2 = c2.workspace(c2.exx_workspace_bytes(cell.N, cell.L, cell.n_occ, pairs))
-            pick_variant(c2, fname, [(phi, cell.N, cell.L, pairs)], ws2)
+            tune2 = pick_variant(c2, fname, [(phi, cell.N, cell.L, pairs)], ws2)
             r2 = c2.exx_action(phi, cell.N, cell.L, pairs, ws=ws2, W=W, exx_dev=exx_dev, want_host=True)
             torch.cuda.synchronize()
             # median of form_calls calls, HIP events around each on the context's stream
@@ -447,7 +446,7 @@ def main():
             forms[fname] = {"vxx_ms_per_call": vms, "calls": args.form_calls, "cg_ms": cgms,
                             "guess_ms": s2["guess"], "cg_iters_mean": float(r2[2]["iters"].mean()), "E_xx": r2[1],
                             "dE_vs_oracle": (r2[1] - golden["E"]) if golden else None,
-                            "cg_kernel": cg_roofline(fname, cgms, r2[2], npts),
+                            "cg_kernel": cg_roofline(fname, cgms, r2[2], npts, tune2),
                             "action_frac": fb / (vms * 1e-3) / 1e9 / HBM_PEAK_GBS}
             log(f"form {fname}: {vms:.1f} ms (median of {args.form_calls}), iters "
                 f"{forms[fname]['cg_iters_mean']:.1f}, CG kernel "

@@ -93,17 +93,16 @@ typedef struct {
     int32_t cg_variant;     /* F32 state: z-march kernel variant; -1 = the     */
                             /* context's autotuned choice, else the default;  */
                             /* 0..sea_cg_variant_count()-1 = that variant.    */
-                            /* With -1, domains of 90000 points and more (up  */
-                            /* to 64 an axis) are solved by teams of          */
-                            /* workgroups where those are faster than the     */
-                            /* variant, by the domain's planes (53 and more   */
-                            /* always, beside the default variant) and the    */
-                            /* number of pairs, in the arithmetic of the      */
-                            /* variants without -xc.  Teams are made of       */
-                            /* workgroups that run at the same time; pairs    */
-                            /* for which none come together within 20 ms (a   */
-                            /* stream restricted to a few CUs, CUs held by    */
-                            /* other work) are solved by the variant          */
+                            /* With -1, large domains (cubes from 45 points   */
+                            /* on, 64 x 64 x 52, up to 64 an axis) are solved */
+                            /* by teams of workgroups, in the arithmetic of   */
+                            /* the variants without -xc, unless the autotuner */
+                            /* has found a variant that is faster alone.      */
+                            /* Teams are made of workgroups that run at the   */
+                            /* same time; pairs for which none come together  */
+                            /* within 20 ms (a stream restricted to a few     */
+                            /* CUs, CUs held by other work) are solved by the */
+                            /* variant                                        */
     int32_t profile;        /* non-zero: time each stage with HIP events       */
     sea_dtype nn_weight_dtype; /* learned start: network weights F32 or BF16   */
     void *hip_stream;       /* hipStream_t; NULL = default stream              */
@@ -278,17 +277,20 @@ const char *sea_cg_variant_name(int variant);
  * of these cells (zero start, exactly `iters` iterations each, so every
  * variant does the same work) once per variant, times each launch with HIP
  * events, and keeps the fastest as the context's choice (used while
- * opts.cg_variant is -1).  Its time beside the default variant's also says from
- * which domains on teams are the faster form.  ms_host (sea_cg_variant_count()
- * floats, nullable) receives the times and *best the chosen index.  The workspace must hold
+ * opts.cg_variant is -1).  Where teams of workgroups take some of the sampled
+ * domains, teams with the fastest variant for the rest are timed as well, and the
+ * context uses teams from then on only if they were faster.  ms_host
+ * (sea_cg_variant_count() floats, nullable) receives the variants' times and
+ * *best the fastest one's index.  The workspace must hold
  * sea_exx_batched_workspace_bytes of the same cells; W_dev may be NULL.
  * Synchronizes.  SEA_E_ARG for cells that the FP32 state cannot run (grids
  * not cubic, domains wider than 64 points in x or y). */
 sea_status sea_exx_autotune(sea_ctx *ctx, int n_cells, const sea_cell *cells, void *ws_dev, size_t ws_bytes,
                             int sample_pairs, int iters, float *ms_host, int *best);
-/* Sets a context's choice from an earlier run of the autotuner: the variant and
- * its time, the default variant's being 1.  SEA_E_ARG out of range. */
-sea_status sea_set_cg_choice(sea_ctx *ctx, int variant, double cost);
+/* The autotuner's choice of a context (variant -1: none yet; teams 0 or 1; nullable
+ * outputs), and the same set from an earlier one.  SEA_E_ARG out of range. */
+sea_status sea_get_cg_choice(sea_ctx *ctx, int *variant, int *teams);
+sea_status sea_set_cg_choice(sea_ctx *ctx, int variant, int teams);
 
 /* Kernel variants of the spectral start's sine-transform passes (one plane
  * kernel and one z-line kernel per call): workgroups per pair and how a

@@ -521,7 +521,7 @@ __global__ __launch_bounds__(NT) void k_cg_zm(ExxArgs a) {
             int qi, pid = -1;
             while ((qi = atomicAdd(a.queue_ctr, 1)) < a.n_pairs) {
                 pid = a.order ? a.order[qi] : qi;  // largest domains first
-                if (!a.team || !cg_team_takes(a.pairs[pid], a.team) || a.stats[pid].converged == CG_TEAM_LEFT) break;
+                if (!a.team || !cg_team_takes(a.pairs[pid]) || a.stats[pid].converged == CG_TEAM_LEFT) break;
             }
             pid_sh = qi < a.n_pairs ? pid : -1;
         }
@@ -569,7 +569,7 @@ constexpr int TM_JOIN_MS = 20;
 static_assert(TM_G * TM_ZP >= CG_TEAM_MAX && TM_ZP >= SEA_HALO, "planes of the largest domain; halos from the neighbours");
 struct TeamCtl {
     unsigned flag[TM_G];        // meetings reached by each workgroup
-    int pid[2];                 // queue index of the team's pair, by parity
+    int pid[2];                 // the team's pair, by parity (-1: none left)
     int pad[6];
     double part[4][TM_G];       // parts of four successive sums
 };
@@ -967,7 +967,7 @@ __global__ __launch_bounds__(256) void k_team_start(ExxArgs a, int* __restrict__
     const int t0 = blockIdx.x * 256 + threadIdx.x, nt = gridDim.x * 256;
     for (int t = t0; t < n_ctl; t += nt) ctl[t] = 0;
     for (int t = t0; t < a.n_pairs; t += nt)
-        if (cg_team_takes(a.pairs[t], a.team)) {
+        if (cg_team_takes(a.pairs[t])) {
             a.stats[t].iters = 0;
             a.stats[t].converged = CG_TEAM_LEFT;
             a.stats[t].rel_res = __builtin_nan("");
@@ -1006,12 +1006,17 @@ __global__ __launch_bounds__(TM_NT) void k_cg_team(ExxArgs a, char* ctl, int n_t
     const TeamIO cc(fs, planes, threadIdx.x), ph(fs + planes, planes, threadIdx.x);
     double* r64 = a.slots + (size_t)team * 4 * a.slot_stride + planes;
     for (int turn = 0;; turn ^= 1) {
-        if (lead) st_dev(&tm.ctl->pid[turn], atomicAdd(queue, 1));
+        if (lead) {   // the next of the pairs that are for teams, largest domains first
+            int qi, pid = -1;
+            while ((qi = atomicAdd(queue, 1)) < a.n_pairs) {
+                pid = a.order ? a.order[qi] : qi;
+                if (cg_team_takes(a.pairs[pid])) break;
+            }
+            st_dev(&tm.ctl->pid[turn], qi < a.n_pairs ? pid : -1);
+        }
         if (!tm.sync()) break;
-        const int qi = ld_dev(&tm.ctl->pid[turn]);
-        if (qi >= a.n_pairs) break;
-        const int pid = a.order ? a.order[qi] : qi;   // largest domains first
-        if (!cg_team_takes(a.pairs[pid], a.team)) continue;
+        const int pid = __builtin_amdgcn_readfirstlane(ld_dev(&tm.ctl->pid[turn]));
+        if (pid < 0) break;
         // solved when all of the team say so: a member whose last wait ran out does
         // not come to this meeting, and its planes may be unfinished
         TeamEnd end;

@@ -305,7 +305,7 @@ ExxLayout exx_layout(const sea_ctx* ctx, const CellSet& S, bool with_v, bool eag
     L.cg_active = tiled64 ? take(((size_t)ctx->opts.max_iter + 1) * sizeof(int)) : 0;
     L.refine = refine ? take((REFINE_MAX + 1) * (np + 1) * sizeof(int)) : 0;   // counts, then lists
     bool teams = false;
-    for (int k = 0; k < n_pairs; ++k) teams = teams || cg_team_takes(pairs[k], cg_team_min_nz(n_pairs, ctx->n_cu, 1.0));
+    for (int k = 0; k < n_pairs; ++k) teams = teams || cg_team_takes(pairs[k]);
     if (teams && ctx->opts.stencil_dtype == SEA_F32 && !refine) {
         L.team = take(cg_teams(ctx->n_cu) * CG_TEAM_CTL + CG_TEAM_TAIL);
         L.slot_stride = std::max(L.slot_stride, CG_TEAM_SLOT);
@@ -666,6 +666,14 @@ static bool whole_device(hipStream_t s, int n_cu) {
     return bits == 0 || bits >= n_cu;
 }
 
+// How many pairs of a call are for teams, on a device that can run them.
+static int team_pairs(const sea_ctx* ctx, const CellSet& S) {
+    int n = 0;
+    if (cg_teams(ctx->n_cu) > 0 && cg_team_lds_bytes() + 1024 <= ctx->max_lds)
+        for (const auto& p : S.pairs) n += cg_team_takes(p);
+    return n;
+}
+
 // The whole kernel sequence of one call, on stream s (capturable).
 static sea_status exx_enqueue(sea_ctx* ctx, const CellSet& S, const ExxLayout& Ly, char* base, const ExxArgs& a,
                               const ExxFlags& f, hipStream_t s) {
@@ -795,15 +803,12 @@ static sea_status exx_enqueue(sea_ctx* ctx, const CellSet& S, const ExxLayout& L
             // norms decide first, and bres is only there for the pairs they fail)
             az.start_res = ctx->opts.start == SEA_START_SPECTRAL ? 1 : 0;
             az.rnorm = (az.start_res && residual_zm_lds_bytes() <= ctx->max_lds) ? (double*)(base + Ly.rnorm) : nullptr;
-            // teams of workgroups take the domains that fit them, unless the caller has
-            // fixed a variant; an autotuned one moves the line to where they are faster
-            // than it
-            const int min_nz = cg_team_min_nz(n_pairs, ctx->n_cu, ctx->cg_cost);
+            // teams of workgroups take the domains made for them, unless the caller has
+            // fixed a variant or the autotuner found one that is faster alone
             int n_team = 0;
-            if (ctx->opts.cg_variant < 0 && cg_teams(ctx->n_cu) > 0 && cg_team_lds_bytes() + 1024 <= ctx->max_lds &&
-                (!nocap || whole_device(s, ctx->n_cu)))
-                for (const auto& p : S.pairs) n_team += cg_team_takes(p, min_nz);
-            az.team = n_team > 0 ? min_nz : 0;
+            if (ctx->opts.cg_variant < 0 && ctx->cg_teams && (!nocap || whole_device(s, ctx->n_cu)))
+                n_team = team_pairs(ctx, S);
+            az.team = n_team > 0;
             if (n_team) SEA_HIP_CHECK(ctx, launch_cg_team(az, n_team, base + Ly.team, ctx->n_cu, s));
             SEA_HIP_CHECK(ctx, launch_cg_zm(az, var, s));   // the rest, and what no team took
             timer_off(SEA_STAGE_CG);
@@ -1839,43 +1844,63 @@ extern "C" sea_status sea_exx_autotune(sea_ctx* ctx, int n_cells, const sea_cell
         (void)hipEventDestroy(e0);
         return fail(ctx, SEA_E_HIP, "event creation failed");
     }
-    const int nv = cg_variant_count();
-    int arg = 0;
-    float tbest = 0.0f, t0 = 0.0f;
+    // a candidate: variant v alone, or behind the teams (c.team)
+    const int n_team = Ly.team ? team_pairs(ctx, S) : 0;
     hipError_t err = hipSuccess;
-    for (int v = 0; v < nv && err == hipSuccess; ++v) {
+    auto time_cg = [&](const ExxArgs& c, int v) {
         float ms = 0.0f;
         for (int rep = 0; rep < 2 && err == hipSuccess; ++rep) {  // rep 0 warms the code object
-            err = launch_moments_final(a, nullptr, s);            // resets the pair queue
+            err = launch_moments_final(c, nullptr, s);            // resets the pair queue
             if (err == hipSuccess) err = hipEventRecord(e0, s);
-            if (err == hipSuccess) err = launch_cg_zm(a, v, s);
+            if (err == hipSuccess && c.team) err = launch_cg_team(c, n_team, base + Ly.team, ctx->n_cu, s);
+            if (err == hipSuccess) err = launch_cg_zm(c, v, s);
             if (err == hipSuccess) err = hipEventRecord(e1, s);
             if (err == hipSuccess) err = hipEventSynchronize(e1);
             if (err == hipSuccess) err = hipEventElapsedTime(&ms, e0, e1);
         }
+        return ms;
+    };
+    const int nv = cg_variant_count();
+    int arg = 0;
+    float tbest = 0.0f;
+    for (int v = 0; v < nv && err == hipSuccess; ++v) {
+        const float ms = time_cg(a, v);
         if (ms_host) ms_host[v] = ms;
-        if (v == 0) t0 = ms;
         if (v == 0 || ms < tbest) {
             tbest = ms;
             arg = v;
         }
     }
+    // teams for the domains made for them and the fastest variant for the rest
+    bool teams = true;
+    if (n_team) {
+        ExxArgs at = a;
+        at.team = 1;
+        teams = time_cg(at, arg) < tbest;
+    }
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     if (err != hipSuccess) return fail(ctx, SEA_E_HIP, "autotune: %s", hipGetErrorString(err));
     ctx->cg_tuned = arg;
-    ctx->cg_cost = tbest > 0.0f ? (double)tbest / t0 : 1.0;
+    ctx->cg_teams = teams ? 1 : 0;
     if (best) *best = arg;
     return SEA_OK;
 }
 
-extern "C" sea_status sea_set_cg_choice(sea_ctx* ctx, int variant, double cost) {
+extern "C" sea_status sea_get_cg_choice(sea_ctx* ctx, int* variant, int* teams) {
     if (!ctx) return SEA_E_ARG;
-    if (variant < 0 || variant >= cg_variant_count())
+    if (variant) *variant = ctx->cg_tuned;
+    if (teams) *teams = ctx->cg_teams;
+    return SEA_OK;
+}
+
+extern "C" sea_status sea_set_cg_choice(sea_ctx* ctx, int variant, int teams) {
+    if (!ctx) return SEA_E_ARG;
+    if (variant < -1 || variant >= cg_variant_count())
         return fail(ctx, SEA_E_ARG, "CG variant %d out of range (%d variants)", variant, cg_variant_count());
-    if (!(cost > 0.0 && cost <= 1.0)) return fail(ctx, SEA_E_ARG, "cost must be in (0, 1]");
+    if (teams != 0 && teams != 1) return fail(ctx, SEA_E_ARG, "teams must be 0 or 1");
     ctx->cg_tuned = variant;
-    ctx->cg_cost = cost;
+    ctx->cg_teams = teams;
     return SEA_OK;
 }
 

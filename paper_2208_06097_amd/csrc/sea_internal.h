@@ -38,7 +38,7 @@ struct sea_ctx {
     bool ev_ready = false;
     const void* nn_state = nullptr;   // attached network (learned start)
     int cg_tuned = -1;                // z-march variant chosen by sea_exx_autotune
-    double cg_cost = 1.0;             // its time there, the default variant's being 1
+    int cg_teams = 1;                 // teams take the domains made for them (its choice too)
     void* noalloc_scratch = nullptr;  // device address of this device's static scratch array
     // sine-transform kernel variants (spectral start): the autotuner's choice
     // and a fixed choice (-1: none; the fixed one wins)
@@ -130,8 +130,7 @@ struct ExxArgs {
     double xc_beta_min;   // paired-update CG: smallest beta for recovering a pending step
     int max_iter;
     int lmax;
-    int team;             // FP32 z-march: leave the pairs that teams have taken, of those with
-                          // this many planes (0: no teams)
+    int team;             // FP32 z-march: leave the pairs that teams have taken
     int* queue_ctr;       // persistent-kernel pair counter (zeroed before the CG launch)
     const int* order;     // CG queue order: pair ids by decreasing domain size (nullable)
     const int* dbox;      // per pair 12 ints: boxes where W_i and W_j take the pair
@@ -358,32 +357,23 @@ __device__ __forceinline__ void lds_sync() { asm volatile("s_waitcnt lgkmcnt(0)\
 // z-marching CG (k_cg.hip): needs every pair with n[0], n[1] <= 64.
 bool cg_zm_fits(const sea_pair* pairs, int n_pairs, const double* h);
 size_t cg_zm_lds_bytes(int state_f32);
-// FP32 CG by teams of workgroups (k_cg.hip): domains of up to 64 points an axis and
-// of at least min_nz planes (cg_team_min_nz).
+// FP32 CG by teams of workgroups (k_cg.hip): domains of up to 64 points an axis,
+// from where on a team is the faster form for every length of list (the line lies
+// with the domain alone, so that a pair's result does not depend on its batch).  A
+// team's iteration costs nearly the same for every domain, the z-march's follows the
+// planes.  Teams over z-march, 40 iterations of 32, 256, 288, 512 and 1000 pairs: 45^3
+// 0.22, 1.02, 0.72, 1.01, 0.99; 53^3 0.20, 0.92, 0.65, 0.91, 0.90; 63^3 0.20, 0.84, 0.57,
+// 0.83, 0.82 (70.5 ms against 86.5); 64 x 64 x 31 0.31, 1.34, 0.94, 1.34, 1.32; x 48
+// 0.23, 1.01, 0.70, 0.99, 0.98 (2396 pairs: 1.03); x 52 0.22, 0.95, 0.68, 0.93, 0.94.  The
+// line is drawn through 45^3 and 64 x 64 x 52.
 constexpr int CG_TEAM_MAX = 64, CG_TEAM_MIN_PTS = 90000;
 constexpr size_t CG_TEAM_CTL = 2048;            // bytes of a team's control block
 constexpr size_t CG_TEAM_TAIL = 640;            // and of what follows the last one
 constexpr int CG_TEAM_LEFT = -2;                // DevStat::converged of a pair that no team has taken
 constexpr size_t CG_TEAM_SLOT = 32 * 64 * 64;   // least slot_stride: c, p (FP32) and r64 of 64 planes in four of them
-__host__ __device__ inline bool cg_team_takes(const sea_pair& P, int min_nz) {
-    return P.n[0] <= CG_TEAM_MAX && P.n[1] <= CG_TEAM_MAX && P.n[2] <= CG_TEAM_MAX && P.n[2] >= min_nz &&
-           P.n[0] * P.n[1] * P.n[2] >= CG_TEAM_MIN_PTS;
-}
-// The planes from which a team is the faster form in a call of n_pairs pairs.  A
-// team's iteration costs the same for every domain; the z-march's follows the
-// planes, with a part for each round of a pair per CU and a part for each pair.
-// Fitted to 40 iterations of 32 to 1600 pairs of 48 to 64 points in x and y and 22
-// to 64 planes: z-march nz (0.19 rounds + 0.0007 n) ms, teams 0.07 n; the line keeps to
-// the z-march's side.  Teams over z-march: 64 pairs of 22 planes 0.69, of 64
-// planes 0.34; 256 of 48 1.09, of 54 0.99, of 64 0.88; 288 of 31 0.99, of 48 0.77;
-// 1000 of 48 1.05, of 54 0.98, of 64 0.87.  From 53 planes on the domain alone
-// decides (cost 1); below, a pair's FP64 sums, and so the last digits of its result, can
-// depend on the length of its list.
-// cost: time of the z-march variant in use, the default one's being 1 (the fit's).
-inline int cg_team_min_nz(int n_pairs, int n_cu, double cost) {
-    const long n = n_pairs, rounds = (n + n_cu - 1) / n_cu;
-    const double nz = n > 0 ? 1000.0 * n / (cost * (9.0 * n_cu * rounds + 10.0 * n)) : 0.0;
-    return nz < CG_TEAM_MAX ? (int)nz + 1 : CG_TEAM_MAX + 1;
+__host__ __device__ inline bool cg_team_takes(const sea_pair& P) {
+    return P.n[0] <= CG_TEAM_MAX && P.n[1] <= CG_TEAM_MAX && P.n[2] <= CG_TEAM_MAX &&
+           P.n[0] * P.n[1] * P.n[2] >= CG_TEAM_MIN_PTS && 300 * P.n[2] >= P.n[0] * P.n[1] + 11400;
 }
 size_t cg_team_lds_bytes();
 int cg_teams(int n_cu);   // teams that run at once

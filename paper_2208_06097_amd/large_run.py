@@ -58,7 +58,7 @@ def main():
         if tuned is None:
             tuned = ctx.autotune([(phi, cell.N, cell.L, pairs)], sample_pairs=2048, iters=20, ws=ws)
         else:
-            ctx.cg_choice(tuned["variant"], tuned["ms"])
+            ctx.cg_choice(tuned["variant"], tuned["teams"])
         _, E, stats, status = ctx.exx_action(phi, cell.N, cell.L, pairs, ws=ws, W=W)
         ms = ctx.stage_times()
         vxx = sum(ms[k] for k in ("gather", "boundary", "guess", "cg", "finish", "scatter", "energy"))

@@ -31,7 +31,8 @@ EXPORTS = [
     "sea_nn_workspace_bytes", "sea_nn_forward", "sea_nn_train_step", "sea_nn_attach",
     "sea_exx_nn_samples", "sea_exx_batched_workspace_bytes", "sea_exx_action_batched",
     "sea_exx_plan_create", "sea_exx_plan_launch", "sea_exx_plan_results", "sea_exx_plan_destroy",
-    "sea_cg_variant_count", "sea_cg_variant_name", "sea_exx_autotune", "sea_set_cg_choice",
+    "sea_cg_variant_count", "sea_cg_variant_name", "sea_exx_autotune", "sea_get_cg_choice",
+    "sea_set_cg_choice",
     "sea_nn_infer_workspace_bytes", "sea_nn_infer", "sea_eps_workspace_bytes", "sea_build_pairs_eps",
     "sea_successive_idempotency", "sea_scdm_workspace_bytes", "sea_scdm", "sea_rotate",
     "sea_ace_apply_noalloc", "sea_spectral_variant_count", "sea_spectral_variant_name",
@@ -159,7 +160,8 @@ def load() -> C.CDLL:
     lib.sea_cg_variant_name.argtypes = [i]
     lib.sea_cg_variant_name.restype = C.c_char_p
     lib.sea_exx_autotune.argtypes = [vp, i, vp, vp, sz, i, i, vp, P(i)]
-    lib.sea_set_cg_choice.argtypes = [vp, i, C.c_double]
+    lib.sea_get_cg_choice.argtypes = [vp, P(i), P(i)]
+    lib.sea_set_cg_choice.argtypes = [vp, i, i]
     lib.sea_spectral_variant_count.argtypes = []
     lib.sea_spectral_variant_count.restype = i
     lib.sea_spectral_variant_name.argtypes = [i]
@@ -391,50 +393,51 @@ class Context:
         return [self.lib.sea_cg_variant_name(k).decode() for k in range(self.lib.sea_cg_variant_count())]
 
     def autotune(self, cells, sample_pairs=2048, iters=20, ws=None, cache=None):
-        """Pick the FP32-state CG kernel variant for this workload.
+        """Pick the FP32-state CG kernel for this workload.
 
         Times every variant on a strided sample of the cells' pairs (same
-        work for each) and keeps the fastest for this context; its time also
-        says from which domains on teams of workgroups are faster still.  With
-        ``cache`` (a JSON path), a stored choice for the same device, variant
-        set and domain shapes is reused without timing, and new results are
-        stored.  Returns {"variant": name, "ms": {name: ms} or None, "cached": bool}."""
+        work for each), and teams of workgroups with the fastest variant
+        behind them where they take some of the domains, and keeps the
+        fastest for this context.  With ``cache`` (a JSON path), a stored
+        choice for the same device, variant set, number of pairs and domain
+        shapes is reused without timing, and new results are stored.  Returns
+        {"variant": name, "teams": bool, "ms": {name: ms} or None, "cached": bool}."""
         import json
         torch = self._torch
         names = self.cg_variants()
         shapes = sorted({tuple(int(v) for v in n) for c in cells for n in np.asarray(c[3]["n"]).reshape(-1, 3)})
         key = "|".join([torch.cuda.get_device_name(), ",".join(names), f"sample={sample_pairs}", f"iters={iters}",
-                        ";".join("x".join(map(str, t)) for t in shapes[:8])])
+                        f"pairs={sum(len(c[3]) for c in cells)}", ";".join("x".join(map(str, t)) for t in shapes[:8])])
         store = {}
         if cache and os.path.exists(cache):
             with open(cache) as f:
                 store = json.load(f)
             hit = store.get(key)
-            if hit and hit.get("variant") in names:
-                self.cg_choice(hit["variant"], hit.get("ms"))
-                return {"variant": hit["variant"], "ms": hit.get("ms"), "cached": True}
+            if hit and hit.get("variant") in names and "teams" in hit:
+                self.cg_choice(hit["variant"], hit["teams"])
+                return {"variant": hit["variant"], "teams": hit["teams"], "ms": hit.get("ms"), "cached": True}
         arr, _, keep = self._cells(cells, need_W=False)
         if ws is None:
             ws = self.workspace(self.exx_batched_workspace_bytes(cells))
         ms = np.zeros(len(names), dtype=np.float32)
-        best = C.c_int(-1)
+        best, teams = C.c_int(-1), C.c_int(0)
         self._check(self.lib.sea_exx_autotune(self.h, len(cells), arr, ws.data_ptr(), ws.numel(), sample_pairs,
                                               iters, ms.ctypes.data, C.byref(best)))
+        self._check(self.lib.sea_get_cg_choice(self.h, None, C.byref(teams)))
         self.set_opts(cg_variant=-1)
-        out = {"variant": names[best.value], "ms": {n: float(t) for n, t in zip(names, ms)}, "cached": False}
+        out = {"variant": names[best.value], "teams": bool(teams.value),
+               "ms": {n: float(t) for n, t in zip(names, ms)}, "cached": False}
         if cache:
-            store[key] = {"variant": out["variant"], "ms": out["ms"]}
+            store[key] = {"variant": out["variant"], "teams": out["teams"], "ms": out["ms"]}
             with open(cache, "w") as f:
                 json.dump(store, f, indent=1)
         return out
 
-    def cg_choice(self, variant, ms=None):
-        """Set what an earlier ``autotune`` chose: the variant's name and the
-        times {name: ms} that it returned."""
-        names = self.cg_variants()
-        cost = min(1.0, ms[variant] / ms[names[0]]) if ms else 1.0
+    def cg_choice(self, variant, teams):
+        """Set what an earlier ``autotune`` chose: the variant's name, and
+        whether teams take the domains made for them."""
         self.set_opts(cg_variant=-1)
-        self._check(self.lib.sea_set_cg_choice(self.h, names.index(variant), cost))
+        self._check(self.lib.sea_set_cg_choice(self.h, self.cg_variants().index(variant), int(bool(teams))))
 
     def spectral_variants(self):
         """(plane variant names, z-line variant names) of the sine-transform passes."""

@@ -1,7 +1,6 @@
-"""Which pairs the FP32 CG gives to teams: by their planes and the length of the
-list.  The two forms add their FP64 sums in another order, so the reported residual
-says which one solved a pair: the one-workgroup form's is reproduced bit for bit,
-and over a dozen pairs a team's is not.
+"""Which pairs the FP32 CG gives to teams: by their domain alone, so that a pair's
+result is the same bit for bit in a list of any length.  The two forms add their FP64
+sums in another order, which the residual history shows at some iteration.
 """
 import numpy as np
 import pytest
@@ -10,6 +9,10 @@ from paper_2208_06097_amd import sea, synth
 
 pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
+
+# on either side of the line, and a domain with many points and few planes
+BOXES = {(44, 44, 45): False, (45, 45, 45): True, (64, 64, 51): False, (64, 64, 52): True, (64, 64, 31): False,
+         (48, 48, 45): False, (64, 22, 64): True, (64, 21, 64): False}
 
 
 def _pairs(cell, boxes):
@@ -20,26 +23,25 @@ def _pairs(cell, boxes):
     return pairs
 
 
-# planes taken by teams at each length: 12 pairs from 5 on, 270 from 37, 600 from 47
-@pytest.mark.parametrize("n_pairs,planes", [(12, {22: True, 48: True, 64: True}),
-                                            (270, {31: False, 40: True, 64: True}),
-                                            (600, {22: False, 44: False, 53: True})])
-def test_line_between_teams_and_one_workgroup(n_pairs, planes):
+def test_line_between_teams_and_one_workgroup():
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
-    print(f"case cg team rule {n_pairs}", flush=True)
+    print("case cg team rule", flush=True)
     cell = synth.mini(seed=5)
     phi = torch.from_numpy(cell.phi).cuda()
-    nzs = list(planes)
-    boxes = [(64, 64, nzs[k % len(nzs)]) for k in range(n_pairs)]
-    pairs = _pairs(cell, boxes)
-    rel = {}
-    for v in (-1, 0):
+    m, reps = len(BOXES), 36                     # 36 x 8 pairs: a multiple of the three orbital pairs
+    pairs = _pairs(cell, list(BOXES) * reps)
+    hist, stats = {}, {}
+    for v, n in ((-1, m), (-1, m * reps), (0, m)):
         ctx = sea.Context(rel_tol=1e-6, stencil_dtype=sea.SEA_F32, cg_variant=v)
-        _, _, stats, st = ctx.exx_action(phi, cell.N, cell.L, pairs)
-        assert st == sea.SEA_OK and np.all(stats["converged"] == 1)
-        rel[v] = stats["rel_res"]
+        h = ctx.residual_history(n, 500)
+        _, _, s, st = ctx.exx_action(phi, cell.N, cell.L, pairs[:n])
+        assert st == sea.SEA_OK and np.all(s["converged"] == 1)
+        hist[v, n], stats[v, n] = h.cpu().numpy(), s
         ctx.close()
-    for q, nz in enumerate(nzs):
-        same = np.array_equal(rel[-1][q::len(nzs)], rel[0][q::len(nzs)])
-        assert same != planes[nz], (n_pairs, nz)
+    for k, (box, team) in enumerate(BOXES.items()):
+        assert np.array_equal(hist[-1, m][k], hist[0, m][k], equal_nan=True) != team, box
+    assert np.array_equal(hist[-1, m * reps][:m], hist[-1, m], equal_nan=True)
+    assert np.array_equal(stats[-1, m * reps][:m], stats[-1, m])
+    for q in range(0, m * reps, 3 * m):          # and in every place of the list
+        assert np.array_equal(stats[-1, m * reps][q:q + m], stats[-1, m])

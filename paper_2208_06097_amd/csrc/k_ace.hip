@@ -160,8 +160,9 @@ __global__ __launch_bounds__(256) void k_chol_syrk(int n, int kb, double* __rest
 // substitution, x_i = (delta_ic - sum_{c<=k<i} L[i][k] x_k) / L[i][i].  Lane l
 // holds x_k, k = l mod 64, in R registers (n <= 64 R) and rows of L are loaded
 // TR_AHEAD steps before their dot product, so that a step is a wave sum and a
-// division and no trip to memory (256: 180 -> 111 us; 32: 17 -> 13 us).  Larger
-// matrices keep the column in LDS.
+// division and no trip to memory (32: 17 -> 13 us, 256: 180 -> 103, 257: 163 -> 131, 512:
+// 432 -> 265, 513: 427 -> 367, 1024: 1372 -> 748).  At R = 16 that takes 230
+// registers; larger matrices keep the column in LDS.
 constexpr int TR_MAX = 4096, TR_AHEAD = 4;
 template <int R>
 __global__ __launch_bounds__(64) void k_trtri_small(const double* __restrict__ L, int n, double* __restrict__ X) {
@@ -383,6 +384,8 @@ hipError_t ace_trtri(const double* L, int n, double* X, hipStream_t s) {
     if (n > TR_MAX) return hipErrorInvalidValue;
     if (n <= 64) hipLaunchKernelGGL(k_trtri_small<1>, dim3(n), dim3(64), 0, s, L, n, X);
     else if (n <= 256) hipLaunchKernelGGL(k_trtri_small<4>, dim3(n), dim3(64), 0, s, L, n, X);
+    else if (n <= 512) hipLaunchKernelGGL(k_trtri_small<8>, dim3(n), dim3(64), 0, s, L, n, X);
+    else if (n <= 1024) hipLaunchKernelGGL(k_trtri_small<16>, dim3(n), dim3(64), 0, s, L, n, X);
     else hipLaunchKernelGGL(k_trtri_lower, dim3(n), dim3(64), 0, s, L, n, X);
     return hipGetLastError();
 }

@@ -541,10 +541,12 @@ __global__ __launch_bounds__(NT) void k_cg_zm(ExxArgs a) {
 // (read and written once an iteration) and p's planes go through it to the
 // neighbours.  Same recurrences, point for point, as the z-march above with
 // reliable updates; only the FP64 sums are added in another order.
-// Measured per iteration of a 63^3 domain: 36 us on 8 CUs, 47 with all 32 teams
-// at work, against 300 us and more on one; 288 such pairs 289 -> 159 ms, 8 of
-// them 107 -> 13 ms.  About 17 us of it are the vector ALUs, the rest the three
-// meetings and a third of r and A p, which the compiler spills.
+// Measured per iteration of a 63^3 domain: 36 us on 8 CUs alone, 47 with all 32
+// teams at work, which is 1.5 us a pair on the whole chip; the z-march with a pair on
+// every CU takes 2.0 us a pair.  288 such pairs 289 -> 160 ms, 8 of them 107 -> 13 ms;
+// over long lists, without a nearly empty last round, 0.8 of the z-march's time.
+// About 17 of the 47 us are the vector ALUs, the rest the three meetings and a third
+// of r and A p, which the compiler spills.
 //
 // What a workgroup writes for others (p's planes, c, flags, partial sums) goes
 // past the caches that are not shared, in both directions (device scope).  Two

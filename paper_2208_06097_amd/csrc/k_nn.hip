@@ -150,7 +150,7 @@ __device__ __forceinline__ void tc_stage(const TcGeo& G, const float* __restrict
 // multiply-add per k in order, twice the rate of the vector FMAs): 16 voxels
 // x 16 output channels per instruction.  The input block with its halo and
 // the weight block lie in LDS (channel stride 848 floats: 16 banks apart), a
-// weight read serves four voxel blocks, and 80 KB a workgroup leaves two per
+// weight read serves a wavefront's two voxel blocks, and 80 KB a workgroup leaves two per
 // CU, one staging while the other multiplies.  Bound by the matrix pipe.
 //   Forward: K = the three taps of a row (the middle, the left, the right) and
 // a zero, the row's sum added to the total afterwards; bias, channels and

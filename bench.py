@@ -101,7 +101,7 @@ PROFILE_OF = {
     "k_dst_zline": "k_dst_zline_spectral_c2.md",
     "k_residual_zm": "k_residual_zm_spectral_c2.md",
     "k_gather_cart": "k_gather_cart_spectral_c2.md",
-    "k_cg_zm": "k_cg_zm_learned_c2.md",
+    "k_cg_zm": "k_cg_learned_c2.md",
     "k_cg64": "k_cg64_plain_c2.md",
 }
 

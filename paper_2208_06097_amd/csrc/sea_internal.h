@@ -282,14 +282,19 @@ hipError_t launch_cg64_init(const ExxArgs& a, hipStream_t s);
 hipError_t launch_cg64_sweep(const ExxArgs& a, int sweep, hipStream_t s);
 hipError_t launch_cg64_exit(const ExxArgs& a, hipStream_t s);
 // Small domains of the FP64 CG, cut along z as well (k_cg.hip).  The line lies
-// with the domain alone, so that a pair's result does not depend on its batch,
-// and where a full chip of pairs stops gaining: 300 pairs of 32^3 80.9 -> 41.6
-// ms, of 40^3 144 -> 96, of 48^3 200 -> 167, but of 56^3 275 -> 310 (HBM then
-// carries the two more words); 8 pairs gain 3 to 4 times at every size.
+// with the domain alone, so that a pair's result does not depend on its batch.
+// The row tiles' sweeps follow the planes, the small form's the points (two more
+// words each) and, from 49 rows on, a fourth row tile with its halo.  Small form over
+// row tiles, 32 iterations of 16, 300 and 1500 pairs: 29^3 0.32, 0.35, 0.32; 33^3
+// 0.36, 0.66, 0.67; 41^3 0.41, 0.74, 0.78; 47^3 0.40, 0.84, 0.89; 49^3 0.40, 1.03, 1.09;
+// 64 x 44 x 32 0.41, 0.91, 0.96; 64 x 48 x 32 0.43, 0.96, 1.02; 33 x 64 x 40 0.45, 0.92,
+// 0.97; 36 x 64 x 32 0.41, 0.95, 1.03; 64 x 64 x 32 0.47, 1.16, 1.24.  So planes of up to
+// 64 x 44 points with at most 48 rows, of 33 x 64 with more.
 constexpr int CG64_PART = 256;            // partial sums of a pair
 constexpr int CG64_SMALL_PTS = 131072, CG64_SMALL_NZ = 128;
 __host__ __device__ inline bool cg64_small(const sea_pair& P) {
-    return (long)P.n[0] * P.n[1] * P.n[2] <= CG64_SMALL_PTS && P.n[2] <= CG64_SMALL_NZ;
+    return P.n[0] * P.n[1] <= (P.n[1] <= 48 ? 64 * 44 : 33 * 64) &&
+           (long)P.n[0] * P.n[1] * P.n[2] <= CG64_SMALL_PTS && P.n[2] <= CG64_SMALL_NZ;
 }
 struct Cg64Small {
     int n, packed;                        // how many, and of those with two rows to a wavefront

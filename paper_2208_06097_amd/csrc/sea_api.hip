@@ -302,7 +302,7 @@ ExxLayout exx_layout(const sea_ctx* ctx, const CellSet& S, bool with_v, bool eag
     L.cg_part = tiled64 ? take(np * CG64_PART * sizeof(double)) : 0;
     L.cg_rho = tiled64 ? take(np * 2 * sizeof(double)) : 0;
     L.cg_done = tiled64 ? take(np * sizeof(int)) : 0;
-    L.cg_active = tiled64 ? take(((size_t)ctx->opts.max_iter + 1) * sizeof(int)) : 0;
+    L.cg_active = tiled64 ? take(2 * ((size_t)ctx->opts.max_iter + 1) * sizeof(int)) : 0;
     L.refine = refine ? take((REFINE_MAX + 1) * (np + 1) * sizeof(int)) : 0;   // counts, then lists
     bool teams = false;
     for (int k = 0; k < n_pairs; ++k) teams = teams || cg_team_takes(pairs[k]);
@@ -420,7 +420,17 @@ sea_status sea_create(const sea_opts* opts, sea_ctx** out) {
     return SEA_OK;
 }
 
+static void side_release(sea_ctx* ctx) {
+    if (ctx->side) (void)hipStreamDestroy(ctx->side);
+    for (hipEvent_t& e : ctx->side_ev) {
+        if (e) (void)hipEventDestroy(e);
+        e = nullptr;
+    }
+    ctx->side = nullptr;
+}
+
 sea_status sea_destroy(sea_ctx* ctx) {
+    if (ctx) side_release(ctx);
     if (ctx && ctx->ev_ready)
         for (int k = 0; k < SEA_STAGE_COUNT; ++k)
             for (int e = 0; e < 2; ++e) (void)hipEventDestroy(ctx->ev[k][e]);
@@ -595,36 +605,99 @@ static ExxArgs exx_args(sea_ctx* ctx, const CellSet& S, const ExxLayout& Ly, cha
     return a;
 }
 
-// The FP64 row-tile CG: init, then two sweeps per iteration until every pair
-// has stopped (checked from the per-iteration counters every few
-// iterations, which synchronizes), then the true residual's norms into
-// rel_res.
-static sea_status cg64_run(sea_ctx* ctx, const CellSet& S, const ExxArgs& a0, double* rnorm, hipStream_t s) {
-    ExxArgs a = a0;
-    a.rnorm = nullptr;
-    SEA_HIP_CHECK(ctx, launch_fill_int(a.cg_active, (size_t)a.max_iter + 1, s));
-    const Cg64Small small = cg64_small_extents(S.pairs.data(), a.n_pairs);
-    const bool large = small.n < a.n_pairs;
-    if (small.n) SEA_HIP_CHECK(ctx, launch_cg64_small(a, small, -1, s));
-    if (large) SEA_HIP_CHECK(ctx, launch_cg64_init(a, s));
-    constexpr int every = 16;
-    for (int k = 0;; ++k) {
-        a.cg_it = k;
-        if (small.n) SEA_HIP_CHECK(ctx, launch_cg64_small(a, small, 0, s));
-        if (large) SEA_HIP_CHECK(ctx, launch_cg64_sweep(a, 0, s));
-        if (k >= a.max_iter) break;
-        if (small.n) SEA_HIP_CHECK(ctx, launch_cg64_small(a, small, 1, s));
-        if (large) SEA_HIP_CHECK(ctx, launch_cg64_sweep(a, 1, s));
-        if (k % every == every - 1) {
-            int active = 0;
-            SEA_HIP_CHECK(ctx, hipMemcpyAsync(&active, a.cg_active + k, sizeof(int), hipMemcpyDeviceToHost, s));
-            SEA_HIP_CHECK(ctx, hipStreamSynchronize(s));
-            if (active == 0) break;
+// Whether stream s may use every CU.  On a stream restricted to a few CUs teams
+// may not come together, and the time they wait for that is saved (a captured
+// sequence can be replayed on any stream and finds out there).
+static bool whole_device(hipStream_t s, int n_cu) {
+    uint32_t mask[32] = {};
+    if (hipExtStreamGetCUMask(s, 32, mask) != hipSuccess) {
+        (void)hipGetLastError();
+        return true;
+    }
+    int bits = 0;
+    for (uint32_t w : mask) bits += __builtin_popcount(w);
+    return bits == 0 || bits >= n_cu;
+}
+
+// The context's second stream and its fork and join events, made when a call first
+// needs them; nullptr if that fails (the call then runs on one stream).
+static hipStream_t side_stream(sea_ctx* ctx) {
+    if (!ctx->side) {
+        bool ok = hipStreamCreateWithFlags(&ctx->side, hipStreamNonBlocking) == hipSuccess;
+        for (hipEvent_t& e : ctx->side_ev) ok = ok && hipEventCreateWithFlags(&e, hipEventDisableTiming) == hipSuccess;
+        if (!ok) {
+            (void)hipGetLastError();
+            side_release(ctx);
         }
     }
-    a.rnorm = rnorm;
-    SEA_HIP_CHECK(ctx, launch_residual_zm(a, s, false));
-    SEA_HIP_CHECK(ctx, launch_cg64_exit(a, s));
+    return ctx->side;
+}
+
+// The FP64 CG by sweeps over all pairs: init, then two sweeps per iteration
+// until every pair has stopped (checked from the per-iteration counters every few
+// iterations, which synchronizes), then the true residual's norms into rel_res.
+// Small domains have sweeps of their own.  In a call with both kinds their loop
+// runs beside the row tiles' on a second stream, from the init to the norms: either
+// is a chain of latencies that leaves most of the chip idle, and one after the
+// other they add up (36 pairs of 9 to 63 points an axis 45 ms by row tiles alone, 61
+// in turn).  A stream restricted to some CUs keeps both.
+static sea_status cg64_run(sea_ctx* ctx, const CellSet& S, const ExxArgs& a0, double* rnorm, hipStream_t s) {
+    const Cg64Small small = cg64_small_extents(S.pairs.data(), a0.n_pairs);
+    const size_t n_it = (size_t)a0.max_iter + 1;
+    SEA_HIP_CHECK(ctx, launch_fill_int(a0.cg_active, 2 * n_it, s));
+    bool run[2] = {small.n > 0, small.n < a0.n_pairs};   // small domains, the others
+    hipStream_t q[2] = {s, s};
+    if (run[0] && run[1] && whole_device(s, ctx->n_cu) && side_stream(ctx)) q[0] = ctx->side;
+    const bool forked = q[0] != s;
+    ExxArgs a[2] = {a0, a0};
+    for (int p = 0; p < 2; ++p) {
+        a[p].rnorm = nullptr;
+        a[p].cg_active = a0.cg_active + p * n_it;
+    }
+    auto sweep = [&](int p, int which) {   // -1: init
+        if (p == 0) return launch_cg64_small(a[0], small, which, q[0]);
+        return which < 0 ? launch_cg64_init(a[1], q[1]) : launch_cg64_sweep(a[1], which, q[1]);
+    };
+    auto sweeps = [&](int which) {
+        hipError_t e = hipSuccess;
+        for (int p = 0; p < 2 && e == hipSuccess; ++p)
+            if (run[p]) e = sweep(p, which);
+        return e;
+    };
+    auto solve = [&]() -> hipError_t {
+        hipError_t e = hipSuccess;
+        if (forked && (e = hipEventRecord(ctx->side_ev[0], s)) != hipSuccess) return e;
+        if (forked && (e = hipStreamWaitEvent(q[0], ctx->side_ev[0], 0)) != hipSuccess) return e;
+        if ((e = sweeps(-1)) != hipSuccess) return e;
+        constexpr int every = 16;
+        for (int k = 0;; ++k) {
+            a[0].cg_it = a[1].cg_it = k;
+            if ((e = sweeps(0)) != hipSuccess) return e;
+            if (k >= a0.max_iter) break;
+            if ((e = sweeps(1)) != hipSuccess) return e;
+            if (k % every == every - 1) {
+                int active[2] = {0, 0};
+                for (int p = 0; p < 2; ++p) {
+                    if (!run[p]) continue;
+                    e = hipMemcpyAsync(active + p, a[p].cg_active + k, sizeof(int), hipMemcpyDeviceToHost, q[p]);
+                    if (e == hipSuccess) e = hipStreamSynchronize(q[p]);
+                    if (e != hipSuccess) return e;
+                }
+                for (int p = 0; p < 2; ++p) run[p] = active[p] > 0;
+                if (!run[0] && !run[1]) break;
+            }
+        }
+        if (forked && (e = hipEventRecord(ctx->side_ev[1], q[0])) != hipSuccess) return e;
+        if (forked) e = hipStreamWaitEvent(s, ctx->side_ev[1], 0);
+        return e;
+    };
+    const hipError_t e = solve();
+    if (e != hipSuccess && forked) (void)hipStreamSynchronize(q[0]);   // nothing of the call's goes on past it
+    SEA_HIP_CHECK(ctx, e);
+    ExxArgs an = a0;
+    an.rnorm = rnorm;
+    SEA_HIP_CHECK(ctx, launch_residual_zm(an, s, false));
+    SEA_HIP_CHECK(ctx, launch_cg64_exit(an, s));
     return SEA_OK;
 }
 
@@ -650,20 +723,6 @@ static sea_status refine_run(sea_ctx* ctx, const ExxArgs& a0, double* rnorm, dou
         SEA_HIP_CHECK(ctx, launch_refine_flags(a, lists, counts, k + 1, k + 1 == n, s));
     }
     return SEA_OK;
-}
-
-// Whether stream s may use every CU.  On a stream restricted to a few CUs teams
-// may not come together, and the time they wait for that is saved (a captured
-// sequence can be replayed on any stream and finds out there).
-static bool whole_device(hipStream_t s, int n_cu) {
-    uint32_t mask[32] = {};
-    if (hipExtStreamGetCUMask(s, 32, mask) != hipSuccess) {
-        (void)hipGetLastError();
-        return true;
-    }
-    int bits = 0;
-    for (uint32_t w : mask) bits += __builtin_popcount(w);
-    return bits == 0 || bits >= n_cu;
 }
 
 // How many pairs of a call are for teams, on a device that can run them.

@@ -36,6 +36,8 @@ struct sea_ctx {
     hipEvent_t ev[SEA_STAGE_COUNT][2] = {};
     bool ev_used[SEA_STAGE_COUNT] = {};
     bool ev_ready = false;
+    hipStream_t side = nullptr;       // FP64 CG: the small domains' loop beside the others'
+    hipEvent_t side_ev[2] = {};       // its fork and join
     const void* nn_state = nullptr;   // attached network (learned start)
     int cg_tuned = -1;                // z-march variant chosen by sea_exx_autotune
     int cg_teams = 1;                 // teams take the domains made for them (its choice too)
@@ -148,7 +150,7 @@ struct ExxArgs {
     double* cg_part;      // n_pairs x CG64_PART partial sums (k_cg.hip)
     double* cg_rho;       // n_pairs x 2: |r|^2 of the last two iterations
     int* cg_done;         // n_pairs: the pair has stopped; null outside the row-tile CG
-    int* cg_active;       // max_iter + 1 counters: pairs still iterating at each iteration
+    int* cg_active;       // max_iter + 1 counters: pairs still iterating at each iteration (of one kind)
     int cg_it;            // the iteration a sweep launch performs
     double* hist;         // n_pairs x (hist_len + 1) relative residuals per iteration (nullable)
     int hist_len;

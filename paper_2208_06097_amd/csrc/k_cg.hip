@@ -521,7 +521,8 @@ __global__ __launch_bounds__(NT) void k_cg_zm(ExxArgs a) {
             int qi, pid = -1;
             while ((qi = atomicAdd(a.queue_ctr, 1)) < a.n_pairs) {
                 pid = a.order ? a.order[qi] : qi;  // largest domains first
-                if (!a.team || !cg_team_takes(a.pairs[pid]) || a.stats[pid].converged == CG_TEAM_LEFT) break;
+                const bool team = a.team != ZM_ALL && cg_team_takes(a.pairs[pid]);
+                if (team ? a.team != ZM_BESIDE && a.stats[pid].converged == CG_TEAM_LEFT : a.team != ZM_LEFT) break;
             }
             pid_sh = qi < a.n_pairs ? pid : -1;
         }
@@ -967,6 +968,7 @@ __device__ __forceinline__ bool team_solve(const ExxArgs& a, int pid, Team& tm, 
 // is solved yet.
 __global__ __launch_bounds__(256) void k_team_start(ExxArgs a, int* __restrict__ ctl, int n_ctl) {
     const int t0 = blockIdx.x * 256 + threadIdx.x, nt = gridDim.x * 256;
+    if (t0 == 0) a.queue_ctr[16] = 0;
     for (int t = t0; t < n_ctl; t += nt) ctl[t] = 0;
     for (int t = t0; t < a.n_pairs; t += nt)
         if (cg_team_takes(a.pairs[t])) {
@@ -1111,6 +1113,10 @@ bool cg_zm_fits(const sea_pair* pairs, int n_pairs, const double* h) {
 
 size_t cg_team_lds_bytes() { return (size_t)TM_ZP * LW * LH * sizeof(float); }
 int cg_teams(int n_cu) { return n_cu / TM_G; }
+int cg_team_beside(int n_cu, int n_eligible) {
+    const int teams = std::min(cg_teams(n_cu), n_eligible), per_xcd = (teams + RZ_XCD - 1) / RZ_XCD * TM_G;
+    return std::max(0, n_cu / RZ_XCD - per_xcd) * RZ_XCD;
+}
 
 size_t cg_zm_lds_bytes(int state_f32) { return (size_t)2 * LW * LH * (state_f32 ? sizeof(float) : sizeof(double)); }
 

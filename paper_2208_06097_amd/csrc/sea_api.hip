@@ -733,6 +733,29 @@ static int team_pairs(const sea_ctx* ctx, const CellSet& S) {
     return n;
 }
 
+// The FP32 CG of a call with few pairs for teams: the teams on the context's second
+// stream, the others on the z-march meanwhile, then what the teams have left.  One
+// after the other the two forms' longest pairs would add up (78 pairs of 9 to 63
+// points an axis: 69.6 ms by the z-march alone, 75 in turn).  There is room for both
+// (cg_team_beside), so the z-march keeps no team from forming.  The teams have the
+// first n_team slots, the z-march the others.
+static hipError_t cg32_beside(sea_ctx* ctx, const ExxArgs& a, int n_team, int rest, char* ctl, int var, hipStream_t s) {
+    ExxArgs ab = a, al = a;
+    ab.team = ZM_BESIDE;
+    ab.slots += (size_t)n_team * 4 * a.slot_stride;
+    ab.n_slots = rest;
+    al.team = ZM_LEFT;
+    al.queue_ctr += 16;
+    hipError_t e = hipEventRecord(ctx->side_ev[0], s);
+    if (e == hipSuccess) e = hipStreamWaitEvent(ctx->side, ctx->side_ev[0], 0);
+    if (e == hipSuccess) e = launch_cg_team(a, n_team, ctl, ctx->n_cu, ctx->side);
+    if (e == hipSuccess) e = launch_cg_zm(ab, var, s);
+    if (e == hipSuccess) e = hipEventRecord(ctx->side_ev[1], ctx->side);
+    if (e == hipSuccess) e = hipStreamWaitEvent(s, ctx->side_ev[1], 0);
+    if (e == hipSuccess) e = launch_cg_zm(al, var, s);
+    return e;
+}
+
 // The whole kernel sequence of one call, on stream s (capturable).
 static sea_status exx_enqueue(sea_ctx* ctx, const CellSet& S, const ExxLayout& Ly, char* base, const ExxArgs& a,
                               const ExxFlags& f, hipStream_t s) {
@@ -867,9 +890,18 @@ static sea_status exx_enqueue(sea_ctx* ctx, const CellSet& S, const ExxLayout& L
             int n_team = 0;
             if (ctx->opts.cg_variant < 0 && ctx->cg_teams && (!nocap || whole_device(s, ctx->n_cu)))
                 n_team = team_pairs(ctx, S);
-            az.team = n_team > 0;
-            if (n_team) SEA_HIP_CHECK(ctx, launch_cg_team(az, n_team, base + Ly.team, ctx->n_cu, s));
-            SEA_HIP_CHECK(ctx, launch_cg_zm(az, var, s));   // the rest, and what no team took
+            // the others beside them where each has a CU of its own there, else behind
+            const int rest = n_pairs - n_team;
+            const bool beside = n_team && rest && nocap && rest <= cg_team_beside(ctx->n_cu, n_team) && side_stream(ctx);
+            if (beside) {
+                const hipError_t e = cg32_beside(ctx, az, n_team, rest, base + Ly.team, var, s);
+                if (e != hipSuccess) (void)hipStreamSynchronize(ctx->side);   // nothing of the call's goes on past it
+                SEA_HIP_CHECK(ctx, e);
+            } else {
+                az.team = n_team ? ZM_BEHIND : ZM_ALL;
+                if (n_team) SEA_HIP_CHECK(ctx, launch_cg_team(az, n_team, base + Ly.team, ctx->n_cu, s));
+                SEA_HIP_CHECK(ctx, launch_cg_zm(az, var, s));
+            }
             timer_off(SEA_STAGE_CG);
             if (!f.action) {
                 timer_on(SEA_STAGE_FINISH);
@@ -1934,7 +1966,7 @@ extern "C" sea_status sea_exx_autotune(sea_ctx* ctx, int n_cells, const sea_cell
     bool teams = true;
     if (n_team) {
         ExxArgs at = a;
-        at.team = 1;
+        at.team = ZM_BEHIND;
         teams = time_cg(at, arg) < tbest;
     }
     (void)hipEventDestroy(e0);

@@ -132,8 +132,9 @@ struct ExxArgs {
     double xc_beta_min;   // paired-update CG: smallest beta for recovering a pending step
     int max_iter;
     int lmax;
-    int team;             // FP32 z-march: leave the pairs that teams have taken
-    int* queue_ctr;       // persistent-kernel pair counter (zeroed before the CG launch)
+    int team;             // FP32 z-march: which pairs it takes (ZM_*)
+    int* queue_ctr;       // persistent-kernel pair counter (zeroed before the CG launch; [16]: of ZM_LEFT,
+                          // by the teams' launch)
     const int* order;     // CG queue order: pair ids by decreasing domain size (nullable)
     const int* dbox;      // per pair 12 ints: boxes where W_i and W_j take the pair
     int x_nonzero;        // v holds a start guess on entry to the CG
@@ -377,6 +378,9 @@ constexpr int CG_TEAM_MAX = 64, CG_TEAM_MIN_PTS = 90000;
 constexpr size_t CG_TEAM_CTL = 2048;            // bytes of a team's control block
 constexpr size_t CG_TEAM_TAIL = 640;            // and of what follows the last one
 constexpr int CG_TEAM_LEFT = -2;                // DevStat::converged of a pair that no team has taken
+// Pairs of a z-march launch: all; behind teams, those that no team has taken; beside
+// teams, those that are not for them; behind both, those that the teams have left.
+enum { ZM_ALL = 0, ZM_BEHIND, ZM_BESIDE, ZM_LEFT };
 constexpr size_t CG_TEAM_SLOT = 32 * 64 * 64;   // least slot_stride: c, p (FP32) and r64 of 64 planes in four of them
 __host__ __device__ inline bool cg_team_takes(const sea_pair& P) {
     return P.n[0] <= CG_TEAM_MAX && P.n[1] <= CG_TEAM_MAX && P.n[2] <= CG_TEAM_MAX &&
@@ -384,8 +388,10 @@ __host__ __device__ inline bool cg_team_takes(const sea_pair& P) {
 }
 size_t cg_team_lds_bytes();
 int cg_teams(int n_cu);   // teams that run at once
+// workgroups of a kernel that have a CU each beside the teams of n_eligible pairs
+int cg_team_beside(int n_cu, int n_eligible);
 // ctl: cg_teams(n_cu) control blocks and their tail (cleared here).  Pairs that no
-// team took are left for launch_cg_zm with a.team set.
+// team took are left for launch_cg_zm (ZM_BEHIND or ZM_LEFT).
 hipError_t launch_cg_team(const ExxArgs& a, int n_eligible, char* ctl, int n_cu, hipStream_t s);
 // part: eps_marginals_part_doubles(N, n_occ) of scratch
 size_t eps_marginals_part_doubles(const int* N, int n_occ);
